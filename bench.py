@@ -74,7 +74,7 @@ KERNEL_CLASS = [  # rocprofv3 kernel name (namespace and arguments stripped) -> 
     ("k_scan_counts2", "scan_counts"), ("k_sort_pass", "sort_pass"), ("k_keygen", "keygen"),
     ("k_digit_offsets", "digit_offsets"), ("k_zero", "zero"), ("k_leaf", "leaf"),
     ("k_level", "level"), ("k_max_occupancy", "max_occupancy"), ("k_tab_count", "tab_count"),
-    ("k_tab_scan", "tab_scan"), ("k_tab_write", "leaf"), ("k_tab_masks", "level"),
+    ("k_tab_scan", "tab_scan"), ("k_tab_write", "leaf"), ("k_tab_nodes", "level"),
     ("k_pack_sources", "near_pack"), ("k_near_field", "near_sparse"),
     ("k_near_dense", "near_dense")]
 KERNEL_SOURCE = {"list_fill": "lists.hip", "list_count": "lists.hip", "scan_counts": "lists.hip",

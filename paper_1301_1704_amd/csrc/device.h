@@ -87,10 +87,48 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return v;
 }
 
+// The same within each 32-lane half of the wave, in data-parallel-primitive
+// moves (lane shifts inside the adder, no LDS round trip per step): shifts of
+// 1, 2, 4 and 8 within each 16-lane row, then the last lane of rows 0 and 2
+// to the next row. Lanes 31 and 63 end with their half's total.
+__device__ __forceinline__ uint32_t half_incl_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  return v;
+}
+
+// Bitwise OR over each 32-lane half, in lanes 31 and 63.
+__device__ __forceinline__ uint32_t half_or_last(uint32_t v) {
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+  return v;
+}
+
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor(v, o, 64));
   return v;
+}
+
+// ---------------------------------------------------------------------------
+// What the list kernels need to know of a box of levels 1..L-1, in one
+// 16-byte record (uint4), so that a neighbor costs one gather: x = first
+// child, y = child octant mask | (key & 63) << 8 (the box's two lowest octal
+// digits), z and w = the 64-bit occupancy of its grandchildren as a
+// 4 x 4 x 4 grid, cell (x, y, z) at bit 16 z + 4 y + x (levels 1..L-2 only).
+// ---------------------------------------------------------------------------
+// Grid bits of one child's grandchildren: octant o, their octant mask m.
+__device__ __forceinline__ uint64_t node_grid(uint32_t o, uint32_t m) {
+  // m's bits (bz, by, bx) to bits 16 bz + 4 by + bx, then the child's corner
+  const uint32_t lo = (m & 3u) | (m & 0xCu) << 2, hi = (m >> 4 & 3u) | (m >> 2 & 0x30u);
+  const uint64_t g = (uint64_t)(lo | hi << 16);
+  return g << (2 * (o & 1u) + 8 * (o >> 1 & 1u) + 32 * (o >> 2));
 }
 
 // ---------------------------------------------------------------------------

@@ -84,7 +84,7 @@ void launch_leaf(bool packed, bool key64, const uint64_t* sk, const uint32_t* sv
 // rebuild): phase 0 counts box starts per tile and level (cnt: (L + 1) x
 // tab_tiles(n)), 1 scans them (pre, same shape; n_boxes[l] = boxes of level
 // l), 2 writes permutation, coordinates, keys, bookmarks, parents and first
-// children, 3 the child masks (mask_cap: capacity of level L - 1). With
+// children, 3 the nodes (node_cap: capacity of level L - 2). With
 // set_off (a batch), keys carry the set id from bit set_shift up and the
 // permutation is written relative to each set's first point.
 struct TabLevels {
@@ -92,13 +92,13 @@ struct TabLevels {
   uint32_t* begin[kMaxLevel + 1];
   uint32_t* parent[kMaxLevel + 1];
   uint32_t* child[kMaxLevel + 1];
-  uint8_t* mask[kMaxLevel + 1];
+  uint4* node[kMaxLevel + 1];  // the list kernels' records (device.h), levels 1..L-1
 };
 uint32_t tab_tiles(uint32_t n);
 void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* sv,
                    const float* xyz, uint32_t n, uint32_t L, uint32_t* cnt, uint32_t* pre,
                    const TabLevels& T, uint32_t* perm, float* sorted_xyz, uint32_t* n_boxes,
-                   uint32_t mask_cap, hipStream_t s, int phase,
+                   uint32_t node_cap, hipStream_t s, int phase,
                    const uint64_t* set_off = nullptr, uint32_t set_shift = 0);
 void launch_max_occupancy(const uint32_t* begin, const uint32_t* n_in, uint32_t cap,
                           uint32_t* out, hipStream_t s);
@@ -107,39 +107,32 @@ void launch_max_occupancy(const uint32_t* begin, const uint32_t* n_in, uint32_t 
 struct ListLevelArgs {
   uint32_t level;               // lists are built for receiver boxes of this level
   uint32_t n_recv_up;           // receiver boxes at level - 1 (the parents)
-  const void* recv_key_up;      // level - 1 receiver keys
-  const uint8_t* recv_mask_up;  // level - 1 receiver child masks
-  const uint32_t* recv_child_up;// level - 1 receiver first children
-  const void* src_key_up;       // level - 1 source keys
-  const uint8_t* src_mask_up;   // level - 1 source child masks
-  const uint32_t* src_child_up; // level - 1 source first children
+  const uint4* recv_node_up;    // level - 1 receiver nodes (device.h)
+  const uint4* src_node_up;     // level - 1 source nodes
   const uint32_t* e2_off_up;    // E2 lists at level - 1 (unused when up_all)
   const uint32_t* e2_ent_up;
   uint32_t up_all;              // level - 1 == 1: E2 there is every source box
   uint32_t n_src_up;            // source boxes at level - 1
-  // Batch only (first_up == nullptr otherwise): keys carry the set id from
-  // bit 3 * (level - 1) up (at level - 1); a set's boxes at a level occupy
-  // ranks [first[set], first[set + 1]); sets shallower than `level` get empty
-  // lists; entries are written relative to first_cur[set].
+  // Batch only (first_up == nullptr otherwise): recv_key_up are the level - 1
+  // keys, with the set id from bit 3 * (level - 1) up; a set's boxes at a
+  // level occupy ranks [first[set], first[set + 1]); sets shallower than
+  // `level` get empty lists; entries are written relative to first_cur[set].
+  const uint64_t* recv_key_up;
   const uint32_t* first_up;     // level - 1
   const uint32_t* first_cur;    // level
   const uint8_t* set_level;     // per set
-  uint32_t key_bits_up;         // bits of the level - 1 keys including the set id
   const uint32_t* n_recv_up_dev;// if set, the parent count is read here and
                                 // n_recv_up is only the capacity
   const uint32_t* n_src_up_dev; // if set (up_all), the level - 1 source count
   // Fill only: with cnt2_next set, the fill also writes the E2 / E4 counts of
   // the receiver boxes of level + 1 (what the count kernel would compute
   // there), from the lists it builds for their parents.
-  const uint8_t* src_mask_cur;   // level source child masks
-  const uint8_t* recv_mask_cur;  // level receiver child masks
-  const uint32_t* recv_child_cur;// level receiver first children
+  const uint4* recv_node_cur;    // level receiver nodes
   uint32_t* cnt2_next;
   uint32_t* cnt4_next;
 };
-void launch_list_count(bool key64, const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4,
-                       hipStream_t s);
-void launch_list_fill(bool key64, const ListLevelArgs& a, const uint32_t* off2,
+void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, hipStream_t s);
+void launch_list_fill(const ListLevelArgs& a, const uint32_t* off2,
                       const uint32_t* off4, uint32_t* ent2, uint32_t* ent4, hipStream_t s);
 uint32_t scan_tiles(uint32_t n);
 void launch_scan_counts2(const uint32_t* cnt2, const uint32_t* cnt4, uint32_t n, uint32_t* off2,

@@ -23,10 +23,16 @@
 
 namespace fmmds {
 
-// Counting: one half-wave (32 lanes) per receiver box p of level l - 1; lane
-// j takes the j-th entry s of E2(p) (at most 27). The lane computes the
-// offset of s from p, s's child mask and, for each of the 8 child octants q,
-// the number of s's children adjacent to a receiver child in octant q; two
+// A box's 16-byte node (device.h) holds what a neighbor needs of it: first
+// child, child octant mask, and the two lowest octal digits of its key, which
+// give the offset of two boxes at most one apart: per axis the two digits'
+// bits, kept in place, subtract to 0, to the axis' lowest bit (+1) or to both
+// of its bits (-1).
+//
+// Counting (level 2 only; the fill of each level counts the next): one
+// half-wave (32 lanes) per receiver box p of level l - 1; lane j takes the
+// j-th entry s of E2(p) (at most 27) and counts, for each of the 8 receiver
+// octants q, the children of s adjacent to a receiver child in octant q; two
 // packed half-wave scans give the E2 count of every receiver child of p at
 // once (E4 = all children minus E2).
 //
@@ -37,33 +43,39 @@ namespace fmmds {
 // octants it is adjacent to. Then the whole wave takes each p in turn: each
 // lane keeps its share of U in registers, and for each receiver child the
 // wave splits U into the child's E2 and E4 lists with one ballot per 64
-// entries: order is kept, so both come out ascending, and each chunk is
-// stored to two contiguous ranges.
-//
-// Offsets per axis come from dilated-integer subtraction on the Morton keys:
-// with only one axis' bits kept in both operands, borrows run through the
-// cleared bits between them, so ((a & M) - (b & M)) & M is the dilated
-// difference of the two coordinates on that axis. Here it is 0, +1 or -1,
-// i.e. 0, the axis' lowest bit, or all of the axis' bits.
-constexpr uint64_t kAxisX = 0x1249249249249249ull;
-constexpr int kUnion = 256;  // >= 27 * 8 children of E2(p)
+// entries: order is kept, so both come out ascending.
+// The lists of p's children are consecutive in memory, so the split goes to
+// LDS and leaves in 16-byte stores. Measured on the 2 x 2^24-point uniform
+// build, finest level (7.7 GB of entries): splitting straight to memory with
+// 4-byte stores, with a neighbor's key, mask and first child in three arrays,
+// took 2041 us, half of a wave's time in its loads; one node per neighbor and
+// staged lists take 1640 us (4.7 TB/s; as many bytes stored the same way from
+// registers, by a kernel that does nothing else, 1280 us).
+// What bounds it now: the stores share the path to memory with the neighbor
+// loads (the loads and the split without the stores take 880 us). Neither
+// persistent waves that load ahead (2170 us) nor larger staging buffers and so
+// fewer waves (all levels together: 2.19 ms with 8 waves per SIMD, 2.22 with 7,
+// 2.46 with 5) overlap them better.
+constexpr int kUnion = 220;      // >= 27 * 8 children of E2(p), and a slot for absent octants
+constexpr uint32_t kFillE2 = 436;  // LDS words for E2 entries of two parents (<= 2 * 216 + 3)
+constexpr uint32_t kFillE4 = 844;  // LDS words for staged E4 entries
+constexpr uint32_t kFillWords = kFillE2 + kFillE4;
+static_assert(2 * 2 * kUnion + 128 <= kFillWords, "U and the count slots share the staging space");
 
-template <typename A>
-__device__ __forceinline__ int axis_delta(A sk, A pk, A axis_mask, A axis_low) {
-  const A d = (A)((sk & axis_mask) - (pk & axis_mask)) & axis_mask;
-  return d == 0 ? 0 : (d == axis_low ? 1 : -1);
+// Offset of a neighbor from p: low digits of both keys -> per axis 0, 1 or
+// (-1) both bits of the axis.
+struct Offset {
+  uint32_t x, y, z;  // 0, +1: 1 / 2 / 4, -1: 9 / 18 / 36
+};
+__device__ __forceinline__ Offset node_offset(uint32_t sk, uint32_t pk) {
+  return {((sk & 0x09u) - (pk & 0x09u)) & 0x09u, ((sk & 0x12u) - (pk & 0x12u)) & 0x12u,
+          ((sk & 0x24u) - (pk & 0x24u)) & 0x24u};
 }
-
-
-// Inclusive scan within each 32-lane half of the wave.
-__device__ __forceinline__ uint32_t half_incl_scan(uint32_t v) {
-  const uint32_t j = lane_id() & 31u;
-#pragma unroll
-  for (int o = 1; o < 32; o <<= 1) {
-    const uint32_t t = __shfl_up(v, o, 32);
-    if (j >= (uint32_t)o) v += t;
-  }
-  return v;
+// v0, v+ or v- by an axis offset d of node_offset with lowest bit `low`.
+__device__ __forceinline__ uint32_t by_offset(uint32_t d, uint32_t low, uint32_t v0, uint32_t vp,
+                                              uint32_t vm) {
+  const uint32_t v = d == low ? vp : vm;
+  return d == 0 ? v0 : v;
 }
 
 // E2 count of octant q from the packed words: octants 0..3 sit in bits
@@ -73,11 +85,8 @@ __device__ __forceinline__ uint32_t octant_field(uint32_t a, uint32_t b, uint32_
   return q < 4 ? (a >> (8 + 6 * q)) & 63u : (b >> (6 * (q - 4))) & 63u;
 }
 
-template <typename KeyT, typename A>
 __global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* __restrict__ cnt2,
                                                     uint32_t* __restrict__ cnt4) {
-  const KeyT* __restrict__ pkey = (const KeyT*)a.recv_key_up;
-  const KeyT* __restrict__ skey = (const KeyT*)a.src_key_up;
   const uint32_t j = threadIdx.x & 31u, h = threadIdx.x >> 5;
   const uint64_t p = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * 8 + h;
   const uint32_t n_up = a.n_recv_up_dev ? *a.n_recv_up_dev : a.n_recv_up;
@@ -93,31 +102,28 @@ __global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* _
     cnt = a.e2_off_up[p + 1] - j0;
   }
   if (a.first_up) {
-    const uint32_t set = (uint32_t)((uint64_t)pkey[p] >> (3 * (a.level - 1)));
+    const uint32_t set = (uint32_t)(a.recv_key_up[p] >> (3 * (a.level - 1)));
     upbase = a.first_up[set];
     if (a.up_all) cnt = a.first_up[set + 1] - upbase;
     if (a.set_level[set] < a.level) cnt = 0;  // the set's lists stop above this level
   }
-  const uint32_t rmask = a.recv_mask_up[p];
-  const uint32_t rfirst = a.recv_child_up[p];
+  const uint2 np = *(const uint2*)&a.recv_node_up[p];
+  const uint32_t rmask = np.y & 0xFFu, rfirst = np.x;
   uint32_t wa = 0, wb = 0;
   if (j < cnt) {
     const uint32_t s = upbase + (a.up_all ? j : a.e2_ent_up[j0 + j]);
-    const A sk = (A)skey[s], pk = (A)pkey[p];
-    const A X = (A)kAxisX;
-    const int dx = axis_delta<A>(sk, pk, X, (A)1);
-    const int dy = axis_delta<A>(sk, pk, (A)(X << 1), (A)2);
-    const int dz = axis_delta<A>(sk, pk, (A)(X << 2), (A)4);
-    const uint32_t m = a.src_mask_up[s];
+    const uint2 ns = *(const uint2*)&a.src_node_up[s];
+    const Offset d = node_offset(ns.y >> 8, np.y >> 8);
+    const uint32_t m = ns.y & 0xFFu;
     // Children of s adjacent to a receiver child whose axis bit is 0 / 1:
     // offset 0: all; +1: child bit 0 and receiver bit 1; -1: child bit 1 and
     // receiver bit 0. Octants with the x / y / z bit clear: 0x55 / 0x33 / 0x0F.
-    const uint32_t ax0 = dx == 0 ? 0xFFu : (dx < 0 ? 0xAAu : 0u);
-    const uint32_t ax1 = dx == 0 ? 0xFFu : (dx > 0 ? 0x55u : 0u);
-    const uint32_t ay0 = dy == 0 ? 0xFFu : (dy < 0 ? 0xCCu : 0u);
-    const uint32_t ay1 = dy == 0 ? 0xFFu : (dy > 0 ? 0x33u : 0u);
-    const uint32_t az0 = dz == 0 ? 0xFFu : (dz < 0 ? 0xF0u : 0u);
-    const uint32_t az1 = dz == 0 ? 0xFFu : (dz > 0 ? 0x0Fu : 0u);
+    const uint32_t ax0 = by_offset(d.x, 1, 0xFFu, 0u, 0xAAu);
+    const uint32_t ax1 = by_offset(d.x, 1, 0xFFu, 0x55u, 0u);
+    const uint32_t ay0 = by_offset(d.y, 2, 0xFFu, 0u, 0xCCu);
+    const uint32_t ay1 = by_offset(d.y, 2, 0xFFu, 0x33u, 0u);
+    const uint32_t az0 = by_offset(d.z, 4, 0xFFu, 0u, 0xF0u);
+    const uint32_t az1 = by_offset(d.z, 4, 0xFFu, 0x0Fu, 0u);
     wa = (uint32_t)__popc(m);
 #pragma unroll
     for (uint32_t q = 0; q < 8; ++q) {
@@ -142,266 +148,328 @@ __global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* _
   }
 }
 
-// NEXT: also write the counts of level + 1 (see ListLevelArgs). E2(r) for a
-// receiver child r of p is the set of U entries marked for r. An entry u
-// (child o of the parent neighbor s at offset d' from p) sits at offset
-// 2 d' + o - q from r per axis (q: r's octant); the setup stores t - 1 with
-// t = 2 d' + o + 2 (2 bits per axis: for entries of some E2(r), t is 1..4).
-// During the split the E2 lanes also copy (child mask of u, t - 1) into a
-// small per-child LDS list; afterwards the lanes of the wave take one
-// (receiver child r, octant q' of r's children) pair each and count, over
-// E2(r), the children of u adjacent to r's child q', as the count kernel
-// does one level down. The lanes stay busy in that phase, instead of
-// counting inside the split where only the E2 lanes are.
-constexpr int kE2Max = 27;
+// LDS written by other lanes of this wave is read after this point (and the
+// other way round): the LDS serves one wave's accesses in order, so this only
+// keeps the compiler from moving them.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
-template <typename KeyT, typename A, bool NEXT>
-__global__ __launch_bounds__(256) void k_list_fill(ListLevelArgs a, const uint32_t* __restrict__ off2,
-                                                   const uint32_t* __restrict__ off4,
-                                                   uint32_t* __restrict__ ent2,
-                                                   uint32_t* __restrict__ ent4) {
-  __shared__ uint32_t s_rank[8][kUnion];
-  __shared__ uint8_t s_adj[8][kUnion];
-  __shared__ uint8_t s_off[NEXT ? 8 : 1][NEXT ? kUnion : 1];
-  __shared__ uint32_t s_e2[NEXT ? 4 : 1][NEXT ? 16 : 1][NEXT ? kE2Max : 1];
-  const KeyT* __restrict__ pkey = (const KeyT*)a.recv_key_up;
-  const KeyT* __restrict__ skey = (const KeyT*)a.src_key_up;
-  const uint32_t lane = threadIdx.x & 63u, j = lane & 31u, h = threadIdx.x >> 5;
-  const uint64_t blk = xcd_block(blockIdx.x, gridDim.x);
-  const uint64_t p = blk * 8 + h;
+// Staged words [b, e) at `lds` (b = g % 4 on the first flush of a run, later
+// 0) are entries [g, ...) of `ent`, which is 16-byte aligned: whole 16-byte
+// groups are stored, and where the run starts or ends inside a group its ragged
+// words in one 4-byte store (lanes 0..3 the head, 4..7 the tail). Unless the
+// run ends here (last), the words past the last whole group move to the front.
+// Leaves the new b, e and g.
+__device__ __forceinline__ void flush_entries(uint32_t* lds, uint32_t& b, uint32_t& e, uint32_t& g,
+                                              uint32_t* __restrict__ ent, bool last, uint32_t lane) {
+  wave_sync();
+  const uint32_t a4 = (b + 3u) & ~3u, e4 = max(e & ~3u, a4);
+  uint32_t* out = ent + ((uint64_t)g - b);  // entry of LDS word 0
+  for (uint32_t i = 4u * lane + a4; i < e4; i += 256u) *(uint4*)(out + i) = *(const uint4*)(lds + i);
+  if (last || b != 0) {
+    const uint32_t i = lane < 4 ? b + lane : e4 + lane - 4u;
+    const uint32_t stop = lane < 4 ? min(a4, e) : e;
+    if (lane < (last ? 8u : 4u) && i < stop) out[i] = lds[i];
+  }
+  if (!last) {  // (a4 <= e here: a flush that is not the last holds many words)
+    const uint32_t v = lds[e4 + (lane & 3u)];
+    wave_sync();
+    if (lane < 4) lds[lane] = v;
+    g += e4 - b;
+    b = 0;
+    e -= e4;
+  }
+  wave_sync();
+}
+
+// NEXT: also write the counts of level + 1 (see ListLevelArgs). Take a
+// receiver child r of p (octant q). E2 of r's children lies in the 4 x 4 x 4
+// boxes of level + 1 around r's 2 x 2 x 2 (cells -1..2 per axis), and the
+// candidates (the children of E2(r)) in the 6 x 6 x 6 around it. Lane j holds
+// the 4 x 4 x 4 grid of s_j's grandchildren (its node); with s_j at offset d
+// from p, its cell Y sits at 4d + Y - 2q from r per axis, so the part inside
+// r's 4 x 4 x 4 window is a mask of the grid (by d and q per axis) rotated by
+// one amount. ORing it over the lanes gives the window's occupancy W; the E2
+// count of r's child q' is the population of W under the 3 x 3 x 3 cells at
+// q'. The candidates' number is the sum over the lanes of the grid's
+// population under the child octants within E2(r).
+//
+// A wave takes PAIRS consecutive pairs of parents, all of whose loads (three
+// dependent ones: p's node and list range, then the list entries, then the
+// neighbors' nodes) are made before the first pair's stores, so that one wait
+// serves them all: with two pairs the sparse levels of a 2M-point level-13
+// build take 1.43 ms in all against 1.60 ms with one (uniform level 8: 1641 us
+// either way; its full level 7, 448 against 423 us).
+template <bool NEXT, bool BATCH, uint32_t PAIRS>
+__global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(ListLevelArgs a,
+                                                      const uint32_t* __restrict__ off2,
+                                                      const uint32_t* __restrict__ off4,
+                                                      uint32_t* __restrict__ ent2,
+                                                      uint32_t* __restrict__ ent4) {
+  // per wave: first U of both parents (8 bytes an entry), with NEXT also the
+  // windows of the receiver children; then the staged E2 and E4 entries
+  __shared__ __align__(16) uint32_t s_all[4][kFillWords];
+  const uint32_t lane = threadIdx.x & 63u, j = lane & 31u, hf = lane >> 5;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint32_t* lds = s_all[w];
   const uint32_t n_up = a.n_recv_up_dev ? *a.n_recv_up_dev : a.n_recv_up;
-  if (blk * 8 + (h & ~1u) >= n_up) return;  // whole wave: both parents absent
-  const bool live = p < n_up;
-  // Setup, one half-wave per parent p (lane j: the j-th entry s of E2(p)).
-  // upbase: batch rank of the set's first box at level - 1 (parent-level E2
-  // entries are stored relative to it); base: the same at level l.
-  uint32_t j0 = 0, cnt = 0, upbase = 0, base = 0, rmask = 0, rfirst = 0;
-  bool next_zero = false;  // the set has no lists at level + 1
-  if (live) {
-    if (a.up_all) {
-      cnt = a.n_src_up_dev ? *a.n_src_up_dev : a.n_src_up;
-    } else {
-      j0 = a.e2_off_up[p];
-      cnt = a.e2_off_up[p + 1] - j0;
+  const uint64_t p0 = ((uint64_t)xcd_block(blockIdx.x, gridDim.x) * 4 + w) * (2 * PAIRS);
+  if (p0 >= n_up) return;  // whole wave: no parent
+  // Per pair, one half-wave per parent p (lane j: the j-th entry s of E2(p)).
+  // Every load is made, from a place that is there where its value is not
+  // wanted (a branch around a load waits for it): absent parents repeat the
+  // last one, lanes past the list its last entry.
+  uint2 np_[PAIRS], nr_[PAIRS];    // p's node; NEXT: child j's first child and mask
+  uint4 ns_[PAIRS];                // s's node
+  uint32_t j0[PAIRS], cnt[PAIRS];  // E2(p)
+  uint32_t o2_[PAIRS], o4_[PAIRS]; // where the lists of p's children start
+  // batch: rank of the set's first box at level - 1 (entries of E2(p) are
+  // relative to it) and at level, and the set's own level
+  uint32_t upbase[PAIRS], base_[PAIRS], lev[PAIRS], ent[PAIRS];
+  uint64_t key[PAIRS];
+#pragma unroll
+  for (uint32_t i = 0; i < PAIRS; ++i) {
+    const uint32_t p = (uint32_t)min(p0 + 2 * i + hf, (uint64_t)n_up - 1);
+    np_[i] = *(const uint2*)&a.recv_node_up[p];
+    key[i] = BATCH ? a.recv_key_up[p] : 0;
+    j0[i] = cnt[i] = 0;
+    if (!a.up_all) {
+      j0[i] = a.e2_off_up[p];
+      cnt[i] = a.e2_off_up[p + 1];
     }
-    if (a.first_up) {
-      const uint32_t set = (uint32_t)((uint64_t)pkey[p] >> (3 * (a.level - 1)));
-      base = a.first_cur[set];
-      upbase = a.first_up[set];
-      if (a.up_all) cnt = a.first_up[set + 1] - upbase;
-      if (a.set_level[set] < a.level) cnt = 0;  // the set's lists stop above this level
-      next_zero = a.set_level[set] < a.level + 1;
-    }
-    rmask = a.recv_mask_up[p];
-    rfirst = a.recv_child_up[p];
   }
-  // Offsets of p's receiver children (lane j holds child j), and with NEXT
-  // their child masks and first children, loaded before any store: on this
-  // GPU a wait for a load also waits for earlier stores.
-  uint32_t my_o2 = 0, my_o4 = 0, my_rm = 0, my_rc = 0;
-  if (j < (uint32_t)__popc(rmask)) {
-    my_o2 = off2[rfirst + j];
-    my_o4 = off4[rfirst + j];
+  const uint32_t n_src_up = a.n_src_up_dev ? *a.n_src_up_dev : a.n_src_up;
+#pragma unroll
+  for (uint32_t i = 0; i < PAIRS; ++i) {
+    const uint2 np = np_[i];
+    o2_[i] = off2[np.x];
+    o4_[i] = off4[np.x];
+    upbase[i] = base_[i] = lev[i] = 0;
+    if (BATCH) {
+      const uint32_t set = (uint32_t)(key[i] >> (3 * (a.level - 1)));
+      base_[i] = a.first_cur[set];
+      upbase[i] = a.first_up[set];
+      lev[i] = a.set_level[set];
+      if (a.up_all) cnt[i] = a.first_up[set + 1];
+    } else if (a.up_all) {
+      cnt[i] = n_src_up;
+    }
+    if (!a.up_all) {
+      cnt[i] -= j0[i];
+      ent[i] = a.e2_ent_up[cnt[i] ? j0[i] + min(j, cnt[i] - 1u) : 0u];
+    }
+    nr_[i] = make_uint2(0, 0);
+    if (NEXT)
+      nr_[i] = *(const uint2*)&a.recv_node_cur[np.x + min(j, (uint32_t)__popc(np.y & 0xFFu) - 1u)];
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < PAIRS; ++i) {
+    if (BATCH) {
+      if (a.up_all) cnt[i] -= upbase[i];  // (it was the set's end)
+      if (lev[i] < a.level) cnt[i] = 0;  // the set's lists stop above this level
+    }
+    if (a.up_all) ent[i] = cnt[i] ? min(j, cnt[i] - 1u) : 0u;
+    const uint4* s = &a.src_node_up[cnt[i] ? upbase[i] + ent[i] : 0u];
+    ns_[i] = make_uint4(0, 0, 0, 0);
     if (NEXT) {
-      my_rm = a.recv_mask_cur[rfirst + j];
-      my_rc = a.recv_child_cur[rfirst + j];
+      ns_[i] = *s;
+    } else {
+      const uint2 v = *(const uint2*)s;
+      ns_[i].x = v.x, ns_[i].y = v.y;
     }
   }
-  uint32_t m = 0, cb = 0, xm0 = 0, xm1 = 0, ym0 = 0, ym1 = 0, zm0 = 0, zm1 = 0;
-  int dx = 0, dy = 0, dz = 0;
-  if (j < cnt) {
-    const uint32_t s = upbase + (a.up_all ? j : a.e2_ent_up[j0 + j]);
-    const A sk = (A)skey[s], pk = (A)pkey[p];
-    const A X = (A)kAxisX;
-    dx = axis_delta<A>(sk, pk, X, (A)1);
-    dy = axis_delta<A>(sk, pk, (A)(X << 1), (A)2);
-    dz = axis_delta<A>(sk, pk, (A)(X << 2), (A)4);
-    m = a.src_mask_up[s];
-    cb = a.src_child_up[s] - base;
-    // Receiver octants a child with axis bit 0 / 1 is adjacent to, per axis:
-    // offset 0: all; +1 (s above p on the axis): a child with bit 0 touches
-    // the receivers with bit 1; -1: a child with bit 1 touches the receivers
-    // with bit 0. Receivers with the x / y / z bit set: 0xAA / 0xCC / 0xF0.
-    xm0 = dx == 0 ? 0xFFu : (dx > 0 ? 0xAAu : 0u);
-    xm1 = dx == 0 ? 0xFFu : (dx < 0 ? 0x55u : 0u);
-    ym0 = dy == 0 ? 0xFFu : (dy > 0 ? 0xCCu : 0u);
-    ym1 = dy == 0 ? 0xFFu : (dy < 0 ? 0x33u : 0u);
-    zm0 = dz == 0 ? 0xFFu : (dz > 0 ? 0xF0u : 0u);
-    zm1 = dz == 0 ? 0xFFu : (dz < 0 ? 0x0Fu : 0u);
+
+#pragma unroll 1
+  for (uint32_t i = 0; i < PAIRS; ++i) {
+  if (PAIRS > 1 && p0 + 2 * i >= n_up) return;
+  const bool live = p0 + 2 * i + hf < n_up;
+  const uint2 np = make_uint2(np_[0].x, live ? np_[0].y : 0u), nr = nr_[0];
+  uint4 ns = ns_[0];
+  if (!live || j >= cnt[0]) ns.y = ns.z = ns.w = 0;  // lanes without an entry: no children
+  const uint32_t my_o2 = o2_[0], my_o4 = o4_[0], base = base_[0];
+  const bool next_zero = BATCH && lev[0] < a.level + 1;  // the set has no lists at level + 1
+#pragma unroll
+  for (uint32_t t = 0; t + 1 < PAIRS; ++t) {
+    np_[t] = np_[t + 1], nr_[t] = nr_[t + 1], ns_[t] = ns_[t + 1], cnt[t] = cnt[t + 1];
+    o2_[t] = o2_[t + 1], o4_[t] = o4_[t + 1], base_[t] = base_[t + 1], lev[t] = lev[t + 1];
   }
+  const uint32_t rmask = np.y & 0xFFu;
+  const Offset d = node_offset(ns.y >> 8, np.y >> 8);
+  const uint32_t m = ns.y & 0xFFu;  // (no children on lanes without an entry)
+  const uint32_t pm0 = (uint32_t)__builtin_amdgcn_readlane(rmask, 0),
+                 pm1 = (uint32_t)__builtin_amdgcn_readlane(rmask, 32);
+
+  if (NEXT) {
+    // per axis and receiver octant bit: the grid cells inside the window (K)
+    // and those of the child octants within E2 (C)
+    const uint32_t kx[2] = {by_offset(d.x, 1, 0x77777777u, 0u, 0x88888888u),
+                            by_offset(d.x, 1, 0xEEEEEEEEu, 0x11111111u, 0u)};
+    const uint32_t ky[2] = {by_offset(d.y, 2, 0x0FFF0FFFu, 0u, 0xF000F000u),
+                            by_offset(d.y, 2, 0xFFF0FFF0u, 0x000F000Fu, 0u)};
+    const uint32_t kl[2] = {by_offset(d.z, 4, 0xFFFFFFFFu, 0u, 0u),
+                            by_offset(d.z, 4, 0xFFFF0000u, 0x0000FFFFu, 0u)};
+    const uint32_t kh[2] = {by_offset(d.z, 4, 0x0000FFFFu, 0u, 0xFFFF0000u),
+                            by_offset(d.z, 4, 0xFFFFFFFFu, 0u, 0u)};
+    const uint32_t cx[2] = {by_offset(d.x, 1, 0xFFFFFFFFu, 0u, 0xCCCCCCCCu),
+                            by_offset(d.x, 1, 0xFFFFFFFFu, 0x33333333u, 0u)};
+    const uint32_t cy[2] = {by_offset(d.y, 2, 0xFFFFFFFFu, 0u, 0xFF00FF00u),
+                            by_offset(d.y, 2, 0xFFFFFFFFu, 0x00FF00FFu, 0u)};
+    const uint32_t cl[2] = {by_offset(d.z, 4, 0xFFFFFFFFu, 0u, 0u),
+                            by_offset(d.z, 4, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u)};
+    const uint32_t ch[2] = {by_offset(d.z, 4, 0xFFFFFFFFu, 0u, 0xFFFFFFFFu),
+                            by_offset(d.z, 4, 0xFFFFFFFFu, 0u, 0u)};
+    // rotation: per axis 4 d + 1 - 2 q cells of stride 1, 4, 16
+    const uint32_t rot = 21u + by_offset(d.x, 1, 0u, 4u, 60u) + by_offset(d.y, 2, 0u, 16u, 48u);
+    uint32_t* slot = lds + 4 * kUnion + 32 * hf;  // 4 words per octant
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      if (!(((pm0 | pm1) >> q) & 1u)) continue;
+      const uint32_t qx = q & 1u, qy = (q >> 1) & 1u, qz = q >> 2;
+      const uint64_t in = (uint64_t)(ns.z & kx[qx] & ky[qy] & kl[qz]) |
+                          (uint64_t)(ns.w & kx[qx] & ky[qy] & kh[qz]) << 32;
+      const uint32_t sh = (rot - 2u * qx - 8u * qy - 32u * qz) & 63u;
+      const uint64_t w = in << sh | in >> ((64u - sh) & 63u);
+      const uint32_t all = (uint32_t)__popc(ns.z & cx[qx] & cy[qy] & cl[qz]) +
+                           (uint32_t)__popc(ns.w & cx[qx] & cy[qy] & ch[qz]);
+      const uint32_t wl = half_or_last((uint32_t)w), wh = half_or_last((uint32_t)(w >> 32));
+      const uint32_t sum = half_incl_scan(all);
+      if (j == 31u) *(uint4*)(slot + 4 * q) = make_uint4(wl, wh, sum, 0u);
+    }
+    wave_sync();
+    // lane 8 q + q': child q' of p's child in octant q, each parent in turn
+    const uint32_t q = lane >> 3, qq = lane & 7u;
+    const uint32_t ex = (qq & 1u) ? 0xEEEEEEEEu : 0x77777777u,
+                   ey = (qq & 2u) ? 0xFFF0FFF0u : 0x0FFF0FFFu,
+                   el = (qq & 4u) ? 0xFFFF0000u : 0xFFFFFFFFu,
+                   eh = (qq & 4u) ? 0xFFFFFFFFu : 0x0000FFFFu;
+#pragma unroll
+    for (uint32_t hh = 0; hh < 2; ++hh) {
+      const uint32_t pm = hh ? pm1 : pm0;
+      const bool nz = __builtin_amdgcn_readlane(next_zero ? 1 : 0, 32 * hh) != 0;
+      const uint32_t i = (uint32_t)__popc(pm & ((1u << q) - 1u));
+      const uint32_t rm = (uint32_t)__shfl((int)(nr.y & 0xFFu), (int)(32 * hh + i));
+      const uint32_t rc = (uint32_t)__shfl((int)nr.x, (int)(32 * hh + i));
+      if (((pm >> q) & 1u) && ((rm >> qq) & 1u)) {
+        const uint4 v = *(const uint4*)(lds + 4 * kUnion + 32 * hh + 4 * q);
+        const uint32_t c2 = (uint32_t)__popc(v.x & ex & ey & el) + (uint32_t)__popc(v.y & ex & ey & eh);
+        const uint32_t at = rc + (uint32_t)__popc(rm & ((1u << qq) - 1u));
+        a.cnt2_next[at] = nz ? 0u : c2;
+        a.cnt4_next[at] = nz ? 0u : v.z - c2;
+      }
+    }
+  }
+
+  // U: per child of s_j its rank and the receiver octants it is adjacent to.
+  // Per axis, receiver octants (bits: receivers with the x / y / z bit set
+  // 0xAA / 0xCC / 0xF0) a child with axis bit 0 / 1 touches: offset 0: all;
+  // +1 (s above p on the axis): a child with bit 0 touches the receivers with
+  // bit 1; -1: a child with bit 1 touches the receivers with bit 0. Laid out
+  // as one byte per child octant, octants 0..3 in lo, 4..7 in hi.
   const uint32_t c = (uint32_t)__popc(m);
   const uint32_t incl = half_incl_scan(c);
-  const uint32_t total = __shfl(incl, 31, 32);  // |U| of this half's parent, <= 216
   {
-    uint32_t* U = s_rank[h];
-    uint8_t* ADJ = s_adj[h];
-    const uint32_t pos = incl - c;
+    const uint32_t ax = by_offset(d.x, 1, 0xFFFFFFFFu, 0x00AA00AAu, 0x55005500u);
+    const uint32_t ay = by_offset(d.y, 2, 0xFFFFFFFFu, 0x0000CCCCu, 0x33330000u);
+    const uint32_t lo = ax & ay & by_offset(d.z, 4, 0xFFFFFFFFu, 0xF0F0F0F0u, 0u);
+    const uint32_t hi = ax & ay & by_offset(d.z, 4, 0xFFFFFFFFu, 0u, 0x0F0F0F0Fu);
+    uint2* U = (uint2*)lds + kUnion * hf;
+    uint32_t at = incl - c, rank = ns.x - base;
 #pragma unroll
     for (uint32_t o = 0; o < 8; ++o) {
-      if (m & (1u << o)) {
-        const uint32_t r = (uint32_t)__popc(m & ((1u << o) - 1u));
-        U[pos + r] = cb + r;
-        ADJ[pos + r] = (uint8_t)(((o & 1u) ? xm1 : xm0) & ((o & 2u) ? ym1 : ym0) &
-                                 ((o & 4u) ? zm1 : zm0));
-        if (NEXT) {
-          const uint32_t tx = (uint32_t)(2 * dx + 1) + (o & 1u);
-          const uint32_t ty = (uint32_t)(2 * dy + 1) + ((o >> 1) & 1u);
-          const uint32_t tz = (uint32_t)(2 * dz + 1) + ((o >> 2) & 1u);
-          s_off[h][pos + r] = (uint8_t)((tx & 3u) | (ty & 3u) << 2 | (tz & 3u) << 4);
-        }
-      }
+      const uint32_t bit = (m >> o) & 1u;
+      // absent octants write to a slot past U
+      U[bit ? at : (uint32_t)kUnion - 1u] = make_uint2(rank, (o < 4 ? lo : hi) >> (8 * (o & 3u)));
+      at += bit;
+      rank += bit;
     }
   }
-  __builtin_amdgcn_wave_barrier();
-  // Both parents' U into registers; with NEXT also the child masks of the U
-  // entries (global loads, issued before any store).
-  uint32_t u[2][4], ad[2], uo[2], um[2], T[2];
+  wave_sync();
+  // Both parents' U into registers (slots past its end: adjacent to none).
+  uint32_t u[2][4], ad[2][4], T[2];
 #pragma unroll
   for (uint32_t hh = 0; hh < 2; ++hh) {
-    T[hh] = (uint32_t)__builtin_amdgcn_readlane(total, 32 * hh);
-    const uint32_t* U = s_rank[(h & ~1u) + hh];
-    const uint8_t* ADJ = s_adj[(h & ~1u) + hh];
-    ad[hh] = uo[hh] = 0;
+    T[hh] = (uint32_t)__builtin_amdgcn_readlane(incl, 32 * hh + 31);
+    const uint2* U = (const uint2*)lds + kUnion * hh;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (uint32_t k = 0; k < 4; ++k) {
       const uint32_t idx = 64u * k + lane;
-      u[hh][k] = idx < T[hh] ? U[idx] : 0u;
-      ad[hh] |= (idx < T[hh] ? (uint32_t)ADJ[idx] : 0u) << (8 * k);
-      if (NEXT) uo[hh] |= (idx < T[hh] ? (uint32_t)s_off[(h & ~1u) + hh][idx] : 0u) << (8 * k);
+      const uint2 v = U[min(idx, (uint32_t)kUnion - 1u)];
+      u[hh][k] = v.x;
+      ad[hh][k] = idx < T[hh] ? v.y : 0u;
     }
   }
-  if (NEXT) {
-#pragma unroll
-    for (uint32_t hh = 0; hh < 2; ++hh) {
-      const uint32_t gbase = (uint32_t)__builtin_amdgcn_readlane(base, 32 * hh);
-      um[hh] = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (64u * k + lane < T[hh])
-          um[hh] |= (uint32_t)a.src_mask_cur[gbase + u[hh][k]] << (8 * k);
-    }
-  }
-  // Split, the whole wave on one parent at a time.
-  uint32_t my_n2 = 0;  // NEXT: lane 32 hh + i holds |E2| of child i of parent hh
-  uint32_t* E2L = NEXT ? &s_e2[threadIdx.x >> 6][0][0] : nullptr;
+  wave_sync();
+  // Split, the whole wave on one parent at a time, into LDS. Lanes past U's
+  // end write past the staged E4 entries, where the next chunk (or nothing)
+  // writes again. Both parents' lists are one run (the second's children
+  // follow the first's).
+  uint32_t* st2 = lds;
+  uint32_t* st4 = lds + kFillE2;
+  uint32_t g2 = (uint32_t)__builtin_amdgcn_readlane((int)my_o2, 0),
+           g4 = (uint32_t)__builtin_amdgcn_readlane((int)my_o4, 0);
+  uint32_t b2 = g2 & 3u, b4 = g4 & 3u, e2 = b2, e4 = b4;  // staged: [b, e) of st2 / st4
 #pragma unroll
   for (uint32_t hh = 0; hh < 2; ++hh) {
-    const uint32_t n_chunks = (T[hh] + 63u) >> 6;
-    uint32_t qm = (uint32_t)__builtin_amdgcn_readlane(rmask, 32 * hh), child = 32 * hh;
+    uint32_t qm = hh ? pm1 : pm0;
 #pragma unroll 1
     while (qm) {
-      const uint32_t q = __builtin_ctz(qm);
+      const uint32_t bit = (uint32_t)__builtin_amdgcn_readfirstlane((int)(qm & (0u - qm)));
       qm &= qm - 1;
-      // next free slot of each list (wave-uniform)
-      uint32_t* d2 = ent2 + (uint32_t)__builtin_amdgcn_readlane(my_o2, child);
-      uint32_t* d4 = ent4 + (uint32_t)__builtin_amdgcn_readlane(my_o4, child);
-      uint32_t n2r = 0;
-      uint32_t* el = NEXT ? E2L + (8 * hh + (child & 7u)) * kE2Max : nullptr;
+      if (e4 + T[hh] + 64u > kFillE4)  // the child might not fit
+        flush_entries(st4, b4, e4, g4, ent4, false, lane);
 #pragma unroll
       for (uint32_t k = 0; k < 4; ++k) {
-        if (k < n_chunks) {
-          const uint32_t rem = T[hh] - 64u * k;  // valid lanes: 0 .. rem - 1
-          const bool is2 = (ad[hh] >> (8 * k + q)) & 1u;  // 0 on invalid lanes
-          const uint64_t b2 = __ballot(is2);
-          const uint32_t i2 = mbcnt(b2);
-          // E2 lanes go to d2 in order; the other valid lanes (a prefix of
-          // the wave minus the E2 lanes) go to d4 in order.
-          uint32_t* dst = is2 ? d2 + i2 : d4 + (lane - i2);
-          if (lane < rem) *dst = u[hh][k];
-          if (NEXT && is2)
-            el[n2r + i2] = ((um[hh] >> (8 * k)) & 0xFFu) | ((uo[hh] >> (8 * k)) & 0xFFu) << 8;
-          const uint32_t n2 = (uint32_t)__popcll(b2);
-          d2 += n2;
-          d4 += min(rem, 64u) - n2;
-          n2r += n2;
+        if (64u * k < T[hh]) {
+          const bool is2 = (ad[hh][k] & bit) != 0u;
+          const uint64_t bal = __ballot(is2);
+          const uint32_t i2 = __builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, e2));
+          lds[is2 ? i2 : kFillE2 + e2 + e4 + lane - i2] = u[hh][k];
+          const uint32_t n2 = (uint32_t)__popcll(bal);
+          e2 += n2;
+          e4 += min(T[hh] - 64u * k, 64u) - n2;
         }
       }
-      if (NEXT && lane == child) my_n2 = n2r;
-      ++child;
     }
   }
-  if (NEXT) {
-    __builtin_amdgcn_wave_barrier();
-    // Lane 8 i + q': receiver child i of each parent in turn, octant q' of
-    // its children.
-    const uint32_t i = lane >> 3, qq = lane & 7u;
-    const uint32_t qx = qq & 1u, qy = (qq >> 1) & 1u, qz = (qq >> 2) & 1u;
-#pragma unroll
-    for (uint32_t hh = 0; hh < 2; ++hh) {
-      const uint32_t pm = (uint32_t)__builtin_amdgcn_readlane(rmask, 32 * hh);
-      const bool nz = __builtin_amdgcn_readlane(next_zero ? 1 : 0, 32 * hh) != 0;
-      const uint32_t rm = (uint32_t)__shfl(my_rm, 32 * hh + i);
-      const uint32_t rc = (uint32_t)__shfl(my_rc, 32 * hh + i);
-      const uint32_t n2 = (uint32_t)__shfl(my_n2, 32 * hh + i);
-      if (i < (uint32_t)__popc(pm) && ((rm >> qq) & 1u)) {
-        uint32_t mm = pm;
-        for (uint32_t t = 0; t < i; ++t) mm &= mm - 1;
-        const uint32_t q = (uint32_t)__builtin_ctz(mm);  // octant of r
-        // Per axis, the children of u adjacent to r's child q' for offsets
-        // -1, 0, +1 of u from r, in bytes 0, 1, 2 (offset -1: u's children
-        // with the bit set, if q' has it clear; +1: those with it clear, if
-        // q' has it set), shifted up one byte when r's own axis bit is 1, so
-        // that byte t - 1 is the mask.
-        const uint32_t Wx = ((qx ? 0u : 0xAAu) | 0xFF00u | (qx ? 0x55u : 0u) << 16) << (8 * (q & 1u));
-        const uint32_t Wy = ((qy ? 0u : 0xCCu) | 0xFF00u | (qy ? 0x33u : 0u) << 16)
-                            << (8 * ((q >> 1) & 1u));
-        const uint32_t Wz = ((qz ? 0u : 0xF0u) | 0xFF00u | (qz ? 0x0Fu : 0u) << 16)
-                            << (8 * ((q >> 2) & 1u));
-        const uint32_t* el = E2L + (8 * hh + i) * kE2Max;
-        uint32_t c_all = 0, c2 = 0;
-        for (uint32_t e = 0; e < n2; ++e) {
-          const uint32_t v = el[e];
-          const uint32_t adj = __builtin_amdgcn_ubfe(Wx, ((v >> 8) & 3u) * 8, 8) &
-                               __builtin_amdgcn_ubfe(Wy, ((v >> 10) & 3u) * 8, 8) &
-                               __builtin_amdgcn_ubfe(Wz, ((v >> 12) & 3u) * 8, 8);
-          c_all += (uint32_t)__popc(v & 0xFFu);
-          c2 += (uint32_t)__popc(v & adj);
-        }
-        const uint32_t slot = rc + (uint32_t)__popc(rm & ((1u << qq) - 1u));
-        a.cnt2_next[slot] = nz ? 0u : c2;
-        a.cnt4_next[slot] = nz ? 0u : c_all - c2;
-      }
-    }
+  flush_entries(st4, b4, e4, g4, ent4, true, lane);
+  flush_entries(st2, b2, e2, g2, ent2, true, lane);
   }
 }
 
-void launch_list_count(bool key64, const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4,
-                       hipStream_t s) {
+void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, hipStream_t s) {
   if (a.n_recv_up == 0) return;  // with n_recv_up_dev: the capacity
-  const uint32_t grid = div_up(a.n_recv_up, 8);
-  const bool narrow = a.key_bits_up <= 32;  // parent-level keys fit 32 bits
-  if (key64 && narrow)
-    hipLaunchKernelGGL((k_list_count<uint64_t, uint32_t>), dim3(grid), dim3(256), 0, s, a, cnt2,
-                       cnt4);
-  else if (key64)
-    hipLaunchKernelGGL((k_list_count<uint64_t, uint64_t>), dim3(grid), dim3(256), 0, s, a, cnt2,
-                       cnt4);
-  else
-    hipLaunchKernelGGL((k_list_count<uint32_t, uint32_t>), dim3(grid), dim3(256), 0, s, a, cnt2,
-                       cnt4);
+  hipLaunchKernelGGL(k_list_count, dim3(div_up(a.n_recv_up, 8)), dim3(256), 0, s, a, cnt2, cnt4);
 }
 
-template <bool NEXT>
-static void list_fill(bool key64, const ListLevelArgs& a, const uint32_t* off2,
-                      const uint32_t* off4, uint32_t* ent2, uint32_t* ent4, hipStream_t s) {
-  const uint32_t grid = div_up(a.n_recv_up, 8);
-  const bool narrow = a.key_bits_up <= 32;
-  if (key64 && narrow)
-    hipLaunchKernelGGL((k_list_fill<uint64_t, uint32_t, NEXT>), dim3(grid), dim3(256), 0, s, a,
-                       off2, off4, ent2, ent4);
-  else if (key64)
-    hipLaunchKernelGGL((k_list_fill<uint64_t, uint64_t, NEXT>), dim3(grid), dim3(256), 0, s, a,
-                       off2, off4, ent2, ent4);
-  else
-    hipLaunchKernelGGL((k_list_fill<uint32_t, uint32_t, NEXT>), dim3(grid), dim3(256), 0, s, a,
-                       off2, off4, ent2, ent4);
-}
+constexpr uint32_t kFillTwoPairs = 1u << 16;
 
-void launch_list_fill(bool key64, const ListLevelArgs& a, const uint32_t* off2,
-                      const uint32_t* off4, uint32_t* ent2, uint32_t* ent4, hipStream_t s) {
+void launch_list_fill(const ListLevelArgs& a, const uint32_t* off2, const uint32_t* off4,
+                      uint32_t* ent2, uint32_t* ent4, hipStream_t s) {
   if (a.n_recv_up == 0) return;
-  if (a.cnt2_next) list_fill<true>(key64, a, off2, off4, ent2, ent4, s);
-  else list_fill<false>(key64, a, off2, off4, ent2, ent4, s);
+  // Two pairs of parents per wave once that still fills the chip's 8192 wave
+  // slots twice; below, the level is one round of waves and takes as long as
+  // one of them does.
+  const bool two = a.n_recv_up >= kFillTwoPairs;
+  const dim3 grid(div_up(a.n_recv_up, two ? 16 : 8));
+#define FMMDS_FILL(N, B, P)                                                                      \
+  hipLaunchKernelGGL((k_list_fill<N, B, P>), grid, dim3(256), 0, s, a, off2, off4, ent2, ent4)
+#define FMMDS_FILL_P(N, B)                                                                       \
+  do {                                                                                           \
+    if (two) FMMDS_FILL(N, B, 2);                                                                \
+    else FMMDS_FILL(N, B, 1);                                                                    \
+  } while (0)
+  if (a.cnt2_next) {
+    if (a.first_up) FMMDS_FILL_P(true, true);
+    else FMMDS_FILL_P(true, false);
+  } else {
+    if (a.first_up) FMMDS_FILL_P(false, true);
+    else FMMDS_FILL_P(false, false);
+  }
+#undef FMMDS_FILL_P
+#undef FMMDS_FILL
 }
 
 // ---------------------------------------------------------------------------

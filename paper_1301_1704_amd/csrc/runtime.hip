@@ -268,7 +268,8 @@ struct LevelBufs {
   uint32_t* begin = nullptr;
   uint32_t* parent = nullptr;
   uint32_t* child = nullptr;
-  uint8_t* mask = nullptr;
+  uint8_t* mask = nullptr;  // dense variant only: child octant masks
+  uint4* node = nullptr;    // the list kernels' records, levels 1..L-1
   uint32_t cap = 0;
 };
 
@@ -558,8 +559,8 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     const uint32_t n_max = std::max(sets[0].n, sets[nsets - 1].n);
     SortBufs sb{};
     SortBufs& sb0 = sb;
-    sb.k[0] = temps.get<uint64_t>(n_max);
-    sb.k[1] = temps.get<uint64_t>(n_max);
+    sb.k[0] = temps.get<uint64_t>(2 * (size_t)round_up(n_max, 2));
+    sb.k[1] = sb.k[0] + round_up(n_max, 2);
     if (!packed || prev) {
       sb.v[0] = temps.get<uint32_t>(n_max);
       sb.v[1] = temps.get<uint32_t>(n_max);
@@ -634,8 +635,8 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     uint32_t* inc_fvs[2] = {inc_fv, inc_fv};
     float* full_x[2] = {nullptr, nullptr};    // incremental fallback: original order
     if (two) {
-      sb1.k[0] = temps.get<uint64_t>(n_max);
-      sb1.k[1] = temps.get<uint64_t>(n_max);
+      sb1.k[0] = temps.get<uint64_t>(2 * (size_t)round_up(n_max, 2));
+      sb1.k[1] = sb1.k[0] + round_up(n_max, 2);
       if (!packed || prev) {
         sb1.v[0] = temps.get<uint32_t>(n_max);
         sb1.v[1] = temps.get<uint32_t>(n_max);
@@ -658,7 +659,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         const size_t c = level_cap(n, l);
         tb += round_up(c * ksz, 256) + round_up((c + 1) * 4, 256);
         if (l >= 1) tb += round_up(c * 4, 256);
-        if (l < L) tb += round_up((c + 1) * 4, 256) + round_up(c, 256);
+        if (l < L) tb += round_up((c + 1) * 4, 256) + (dense ? round_up(c, 256) : 0);
       }
       char* tp = impl->outs.get<char>(tb);
       for (uint32_t l = 0; l <= L; ++l) {
@@ -676,9 +677,22 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         if (l < L) {
           B.child = (uint32_t*)tp;
           tp += round_up((c + 1) * 4, 256);
-          B.mask = (uint8_t*)tp;
-          tp += round_up(c, 256);
+          if (dense) {
+            B.mask = (uint8_t*)tp;
+            tp += round_up(c, 256);
+          }
         }
+      }
+    }
+    // The list kernels' records are written after the last read of the sorted
+    // elements: in their space where they fit (two 8-byte buffers a point).
+    for (int s = 0; !dense && s < nsets; ++s) {
+      size_t nodes = 0;
+      for (uint32_t l = 1; l < L; ++l) nodes += sets[s].lv[l].cap;
+      uint4* q = nodes <= n_max ? (uint4*)(s == 1 ? sb1 : sb).k[0] : temps.get<uint4>(nodes);
+      for (uint32_t l = 1; l < L; ++l) {
+        sets[s].lv[l].node = q;
+        q += sets[s].lv[l].cap;
       }
     }
     // keygen's per-block digit-count rows, per set
@@ -846,7 +860,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
           T.begin[l] = S.lv[l].begin;
           T.parent[l] = S.lv[l].parent;
           T.child[l] = S.lv[l].child;
-          T.mask[l] = S.lv[l].mask;
+          T.node[l] = S.lv[l].node;
         }
         const uint32_t tiles = tab_tiles(n);
         uint32_t* tcnt = tabbuf[s];
@@ -856,10 +870,10 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         uint32_t* nbox = &meta->n_boxes[s][0];
         auto tab = [&](int phase) {
           launch_tables(packed, key64, fin_k, fin_v, leaf_xyz, n, L, tcnt, tpre, T, S.perm,
-                        S.sorted_xyz, nbox, L > 0 ? S.lv[L - 1].cap : 0, st, phase);
+                        S.sorted_xyz, nbox, S.lv[L - 2].cap, st, phase);
         };
         // sorted elements in, per-tile counts out; the counts scanned; then
-        // (box counts known) the tables, and the child masks
+        // (box counts known) the tables, and the list kernels' records
         P.run(K_TCOUNT, (double)n * elem_b + cnt_b, [&] { tab(0); });
         P.run(K_TSCAN, 2 * cnt_b, [&] { tab(1); });
         P.run(K_LEAF, (double)n * (elem_b + 4 + (leaf_xyz ? 12 + 12 : 0)) + cnt_b,
@@ -1015,15 +1029,10 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         a.n_recv_up_dev = &meta->n_boxes[rs][l - 1];
         a.n_src_up_dev = &meta->n_boxes[0][l - 1];
       }
-      a.recv_key_up = sets[rs].lv[l - 1].key;
-      a.recv_mask_up = sets[rs].lv[l - 1].mask;
-      a.recv_child_up = sets[rs].lv[l - 1].child;
-      a.src_key_up = sets[0].lv[l - 1].key;
-      a.src_mask_up = sets[0].lv[l - 1].mask;
-      a.src_child_up = sets[0].lv[l - 1].child;
+      a.recv_node_up = sets[rs].lv[l - 1].node;
+      a.src_node_up = sets[0].lv[l - 1].node;
       a.up_all = (l - 1 == 1) ? 1u : 0u;
       a.n_src_up = lcap[0][l - 1];
-      a.key_bits_up = 3 * (l - 1);
       if (!a.up_all) {
         a.e2_off_up = impl->lists[l - 1].off[0];
         a.e2_ent_up = impl->lists[l - 1].ent[0];
@@ -1040,7 +1049,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
                              nullptr, nullptr, nullptr, st);
         });
       else if (l == 2)
-        P.run(K_COUNT, 0.0, [&] { launch_list_count(key64, a, cnt, cnt + round_up(nr, 4), st); },
+        P.run(K_COUNT, 0.0, [&] { launch_list_count(a, cnt, cnt + round_up(nr, 4), st); },
               kListSet, (int)l);
       LB.off[0] = carve((size_t)nr + 1);
       LB.off[1] = carve((size_t)nr + 1);
@@ -1076,14 +1085,12 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         continue;
       }
       if (l < D) {  // the next level's counts
-        a.src_mask_cur = sets[0].lv[l].mask;
-        a.recv_mask_cur = sets[rs].lv[l].mask;
-        a.recv_child_cur = sets[rs].lv[l].child;
+        a.recv_node_cur = sets[rs].lv[l].node;
         a.cnt2_next = cnt;
         a.cnt4_next = cnt + round_up(lcap[rs][l + 1], 4);
       }
       P.run(K_FILL, 0.0,
-            [&] { launch_list_fill(key64, a, LB.off[0], LB.off[1], LB.ent[0], LB.ent[1], st); },
+            [&] { launch_list_fill(a, LB.off[0], LB.off[1], LB.ent[0], LB.ent[1], st); },
             kListSet, (int)l);
     }
     for (uint32_t l = 2; l <= D; ++l) impl->n_recv_boxes[l] = nb[rs][l];
@@ -1118,9 +1125,10 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
           b += (double)c[l] * (ksz + 4 + (l >= 1 ? 4 : 0) + (l < L ? 4 : 0)) + 4 + (l < L ? 4 : 0);
         return b;
       }
-      if (r.cls == K_LEVEL && r.level < 0) {  // masks: first children in, children's keys in
+      if (r.cls == K_LEVEL && r.level < 0) {  // nodes: first children and keys in, 16 bytes out
         double b = 0;
-        for (uint32_t l = 0; l < L; ++l) b += (double)c[l] * (4 + 1) + 4 + (double)c[l + 1] * ksz;
+        for (uint32_t l = 0; l < L; ++l)
+          b += (double)c[l] * (4 + (l >= 1 ? 16 : 0)) + 4 + (double)c[l + 1] * ksz;
         return b;
       }
       if (r.cls == K_LEVEL)
@@ -1214,6 +1222,7 @@ struct BatchImpl {
   float* sxyz = nullptr;
   uint32_t* tabbuf = nullptr;  // per-tile box-start counts of every level, and their scan
   LevelBufs g[kMaxLevel + 1];
+  uint4* node[kMaxLevel + 1] = {};
   uint64_t* fkey[kMaxLevel + 1] = {};
   uint32_t* fbegin[kMaxLevel + 1] = {};
   uint32_t* fparent[kMaxLevel + 1] = {};
@@ -1308,14 +1317,14 @@ void batch_enqueue(BatchImpl& B, const float* xyz, Prof& P) {
       T.begin[l] = B.g[l].begin;
       T.parent[l] = B.g[l].parent;
       T.child[l] = B.g[l].child;
-      T.mask[l] = B.g[l].mask;
+      T.node[l] = B.node[l];
     }
     const uint32_t tiles = tab_tiles(B.P);
     uint32_t* tcnt = B.tabbuf;
     uint32_t* tpre = B.tabbuf + (size_t)(L + 1) * tiles;
     auto tab = [&](int phase) {
       launch_tables(B.packed, true, B.sb.k[fin], B.sb.v[fin], xyz, B.P, L, tcnt, tpre, T, B.perm,
-                    B.sxyz, &meta->n_boxes[0][0], L > 0 ? B.cap[L - 1] : 0, st, phase, B.d_off,
+                    B.sxyz, &meta->n_boxes[0][0], B.cap[L - 2], st, phase, B.d_off,
                     3 * L);
     };
     P.run(K_TCOUNT, 0.0, [&] { tab(0); });
@@ -1354,12 +1363,9 @@ void batch_enqueue(BatchImpl& B, const float* xyz, Prof& P) {
     a.level = l;
     a.n_recv_up = B.cap[l - 1];
     a.n_recv_up_dev = &meta->n_boxes[0][l - 1];
-    a.recv_key_up = B.g[l - 1].key;
-    a.recv_mask_up = B.g[l - 1].mask;
-    a.recv_child_up = B.g[l - 1].child;
-    a.src_key_up = B.g[l - 1].key;
-    a.src_mask_up = B.g[l - 1].mask;
-    a.src_child_up = B.g[l - 1].child;
+    a.recv_key_up = (const uint64_t*)B.g[l - 1].key;
+    a.recv_node_up = B.node[l - 1];
+    a.src_node_up = B.node[l - 1];
     a.up_all = l == 2 ? 1u : 0u;
     if (!a.up_all) {
       a.e2_off_up = B.goff[l - 1][0];
@@ -1368,10 +1374,9 @@ void batch_enqueue(BatchImpl& B, const float* xyz, Prof& P) {
     a.first_up = B.first_l(l - 1);
     a.first_cur = B.first_l(l);
     a.set_level = B.d_lev;
-    a.key_bits_up = B.setbits + 3 * (l - 1);
     uint32_t* c2 = B.cnt;
     uint32_t* c4 = B.cnt + round_up(B.cap[l], 4);
-    if (l == 2) P.run(K_COUNT, 0.0, [&] { launch_list_count(true, a, c2, c4, st); });
+    if (l == 2) P.run(K_COUNT, 0.0, [&] { launch_list_count(a, c2, c4, st); });
     {
       uint64_t* st2 = sa.take_words(scan_tiles(B.cap[l]));
       uint64_t* st4 = sa.take_words(scan_tiles(B.cap[l]));
@@ -1383,14 +1388,12 @@ void batch_enqueue(BatchImpl& B, const float* xyz, Prof& P) {
       });
     }
     if (l < L) {  // the next level's counts (batch ranks; sets ending at l get zeros)
-      a.src_mask_cur = B.g[l].mask;
-      a.recv_mask_cur = B.g[l].mask;
-      a.recv_child_cur = B.g[l].child;
+      a.recv_node_cur = B.node[l];
       a.cnt2_next = B.cnt;
       a.cnt4_next = B.cnt + round_up(B.cap[l + 1], 4);
     }
     P.run(K_FILL, 0.0, [&] {
-      launch_list_fill(true, a, B.goff[l][0], B.goff[l][1], B.ent[l][0], B.ent[l][1], st);
+      launch_list_fill(a, B.goff[l][0], B.goff[l][1], B.ent[l][0], B.ent[l][1], st);
     });
   }
   {
@@ -1555,12 +1558,20 @@ void batch_layout(BatchImpl& B, Carve& M) {
     o += B.n_tiles[k];
   }
   B.d_goff = M.get<uint32_t>((size_t)n_sets * B.n_pass * 256);
-  B.sb.k[0] = M.get<uint64_t>(P);
-  B.sb.k[1] = M.get<uint64_t>(P);
+  B.sb.k[0] = M.get<uint64_t>(2 * round_up(P, 2));
+  B.sb.k[1] = B.sb.k[0] ? B.sb.k[0] + round_up(P, 2) : nullptr;
   B.sb.v[0] = B.sb.v[1] = nullptr;
   if (!B.packed) {
     B.sb.v[0] = M.get<uint32_t>(P);
     B.sb.v[1] = M.get<uint32_t>(P);
+  }
+  // (the list kernels' records go where the sorted elements were, if they fit)
+  size_t nodes = 0;
+  for (uint32_t l = 1; l < L; ++l) nodes += B.cap[l];
+  uint4* node = nodes <= P ? (uint4*)B.sb.k[0] : M.get<uint4>(nodes);
+  for (uint32_t l = 1; l < L; ++l) {
+    B.node[l] = node;
+    if (node) node += B.cap[l];
   }
   B.perm = M.get<uint32_t>(P);
   B.sxyz = M.get<float>(3 * (size_t)P);
@@ -1577,7 +1588,6 @@ void batch_layout(BatchImpl& B, Carve& M) {
     if (l >= 1) G.parent = M.get<uint32_t>(c);
     if (l < L) {
       G.child = M.get<uint32_t>(c + 1);
-      G.mask = M.get<uint8_t>(c);
     }
     B.fkey[l] = M.get<uint64_t>(c);
     B.fbegin[l] = M.get<uint32_t>(c + n_sets);

@@ -1,5 +1,5 @@
 // Nonempty-box tables: box boundaries of every level, parents, children and
-// child masks, from the sorted points.
+// the list kernels' records, from the sorted points.
 //
 // The paper scans a dense histogram of all 8^lmax boxes (Section 2.3,
 // Algorithm 3), which costs memory and time in the number of boxes. Here the
@@ -113,8 +113,8 @@ void launch_leaf(bool packed, bool key64, const uint64_t* sk, const uint32_t* sv
 //                level l >= d(e) the box's key, bookmark (the point itself),
 //                parent (the level l - 1 box holding the point) and first
 //                child (the level l + 1 box starting at the point);
-//   k_tab_masks  per box of levels 0..L-1, the 8-bit mask of its children's
-//                octants, from the children's keys.
+//   k_tab_nodes  per box of levels 1..L-1, the record the list kernels read
+//                (first child, child octants, low key digits, grandchildren).
 // The tile prefixes come from the scan, so no kernel waits on another tile.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t new_box_level(uint64_t k, uint64_t kp, uint32_t L) {
@@ -283,20 +283,51 @@ __global__ __launch_bounds__(kCompBlock) void k_tab_write(
   }
 }
 
-// Child octant masks of every box of levels 0..L-1 (grid y = level).
+// The list kernels' records of the boxes of levels 1..L-1 (device.h), from the
+// boxes of level l = 0..L-2 (grid y = level): a box's i-th child's children
+// give the child's octant mask and its first two words; the children's masks
+// laid out as a grid are the box's own last two words. So every key is read
+// once. G lanes share a box, each taking every G-th child: 8 where boxes have
+// many children, 1 where most have one or two and eight lanes would idle.
+template <typename KeyT, uint32_t G>
+__device__ __forceinline__ void tab_nodes(const TabLevels& T, uint32_t l, uint32_t nl) {
+  const uint32_t i = threadIdx.x & (G - 1u);
+  const uint32_t* __restrict__ child = T.child[l];
+  const uint32_t* __restrict__ child1 = T.child[l + 1];
+  const KeyT* __restrict__ key1 = (const KeyT*)T.key[l + 1];
+  const KeyT* __restrict__ key2 = (const KeyT*)T.key[l + 2];
+  uint4* __restrict__ node = T.node[l];
+  uint4* __restrict__ node1 = T.node[l + 1];
+  constexpr uint32_t kBoxes = 256u / G;
+  for (uint64_t j = (uint64_t)blockIdx.x * kBoxes + threadIdx.x / G; j < nl;
+       j += (uint64_t)gridDim.x * kBoxes) {
+    const uint32_t c0 = child[j], c1 = child[j + 1];
+    uint64_t grid = 0;
+    for (uint32_t c = c0 + i; c < c1; c += G) {
+      const uint32_t k = (uint32_t)key1[c];
+      const uint32_t g0 = child1[c], g1 = child1[c + 1];
+      uint32_t m = 0;
+      for (uint32_t g = g0; g < g1; ++g) m |= 1u << ((uint32_t)key2[g] & 7u);
+      *(uint2*)&node1[c] = make_uint2(g0, m | (k & 63u) << 8);
+      grid |= node_grid(k & 7u, m);
+    }
+    if (l == 0) continue;  // (level 0 has no record)
+    uint32_t lo = (uint32_t)grid, hi = (uint32_t)(grid >> 32);
+#pragma unroll
+    for (int o = 1; o < (int)G; o <<= 1) {
+      lo |= (uint32_t)__shfl_xor((int)lo, o, (int)G);
+      hi |= (uint32_t)__shfl_xor((int)hi, o, (int)G);
+    }
+    if (i == 0) ((uint2*)&node[j])[1] = make_uint2(lo, hi);
+  }
+}
+
 template <typename KeyT>
-__global__ __launch_bounds__(256) void k_tab_masks(TabLevels T, const uint32_t* __restrict__ n_boxes) {
+__global__ __launch_bounds__(256) void k_tab_nodes(TabLevels T, const uint32_t* __restrict__ n_boxes) {
   const uint32_t l = blockIdx.y;
   const uint32_t nl = n_boxes[l];
-  const uint32_t* __restrict__ child = T.child[l];
-  const KeyT* __restrict__ ck = (const KeyT*)T.key[l + 1];
-  uint8_t* __restrict__ mask = T.mask[l];
-  for (uint64_t j = blockIdx.x * 256ull + threadIdx.x; j < nl; j += gridDim.x * 256ull) {
-    const uint32_t c0 = child[j], c1 = child[j + 1];
-    uint32_t m = 0;
-    for (uint32_t c = c0; c < c1; ++c) m |= 1u << ((uint32_t)ck[c] & 7u);
-    mask[j] = (uint8_t)m;
-  }
+  if (n_boxes[l + 1] < 3ull * nl) tab_nodes<KeyT, 1>(T, l, nl);
+  else tab_nodes<KeyT, 8>(T, l, nl);
 }
 
 uint32_t tab_tiles(uint32_t n) { return div_up(n, kCompTile); }
@@ -304,7 +335,7 @@ uint32_t tab_tiles(uint32_t n) { return div_up(n, kCompTile); }
 void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* sv,
                    const float* xyz, uint32_t n, uint32_t L, uint32_t* cnt, uint32_t* pre,
                    const TabLevels& T, uint32_t* perm, float* sorted_xyz, uint32_t* n_boxes,
-                   uint32_t mask_cap, hipStream_t s, int phase, const uint64_t* set_off,
+                   uint32_t node_cap, hipStream_t s, int phase, const uint64_t* set_off,
                    uint32_t set_shift) {
   const uint32_t tiles = tab_tiles(n);
   if (phase == 0) {
@@ -324,10 +355,10 @@ void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* 
     else if (key64) FMMDS_TABW(false, uint64_t);
     else FMMDS_TABW(false, uint32_t);
 #undef FMMDS_TABW
-  } else if (L > 0) {
-    const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(div_up(mask_cap, 256), 2048)), L);
-    if (key64) hipLaunchKernelGGL(k_tab_masks<uint64_t>, grid, dim3(256), 0, s, T, n_boxes);
-    else hipLaunchKernelGGL(k_tab_masks<uint32_t>, grid, dim3(256), 0, s, T, n_boxes);
+  } else if (L >= 2) {
+    const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(div_up(node_cap, 32), 2048)), L - 1);
+    if (key64) hipLaunchKernelGGL(k_tab_nodes<uint64_t>, grid, dim3(256), 0, s, T, n_boxes);
+    else hipLaunchKernelGGL(k_tab_nodes<uint32_t>, grid, dim3(256), 0, s, T, n_boxes);
   }
 }
 
