@@ -366,9 +366,9 @@ fmmds_status fmmds_near_field(const fmmds_tree* t, const float* charges, float* 
  * fmmds_near_field for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same kernels and the same results, with the scratch (16
- * bytes per source point for the packed sources, 8 bytes per dense-path task,
- * at most one task per 9 receiver points, and 256 bytes of counters, each
- * part rounded up to 256 bytes) in a fixed device array of
+ * bytes per source point for the packed sources, and 8 bytes per 9 receiver
+ * points and 256 more for the work division, each part rounded up to 256
+ * bytes) in a fixed device array of
  * FMMDS_NEAR_FIELD_STATIC_BYTES instead of memory from the cache. Each GPU
  * the library runs on holds its own array until the process ends; the call
  * allocates nothing. FMMDS_ERR_TOO_LARGE when the scratch would exceed the

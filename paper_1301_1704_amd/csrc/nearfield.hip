@@ -12,19 +12,18 @@
 // Layout: the sorted source points and their charges are packed once into
 // 16-byte records (x, y, z, q), so each source point is one 16-byte load.
 //
-// Two paths, split by the receiver box's point count:
-//   - sparse boxes (at most kNearDenseMin points): one thread per box. Its
-//     points share every source load, and the lanes of a wave sit in
-//     neighboring boxes with overlapping E2 lists, so most of those loads are
-//     shared through the caches too.
-//   - dense boxes (clustered input puts hundreds of points in one box): the
-//     box is cut into tasks of at most 64 receivers, one wave per task. The
-//     wave stages the box's E2 source points in LDS 64 at a time (one
-//     coalesced 16-byte load per lane) and every lane sums its receiver
-//     against the whole tile. A task of r < 64 receivers splits the tile over
-//     64 / R lane groups (R = r rounded up to a power of two) whose partial
-//     sums are added by shuffles at the end. After its first task a wave takes
-//     the next from an atomic ticket, so boxes of very different sizes balance.
+// One wave takes W receivers consecutive in Morton order (64, fewer when that
+// would leave the chip short of waves) and turns the E2 lists of their boxes
+// into runs of consecutive source points in LDS. Then, box by box of the wave:
+//   - short lists: 64 / W lanes per receiver, each walking a part of its box's
+//     runs; lanes of one box read the same points, and those of neighboring
+//     boxes mostly the same lines;
+//   - long lists, and boxes with more than half of the wave's receivers
+//     (clustered input puts hundreds of points in one box): the wave stages
+//     the box's source points in LDS 64 at a time (one coalesced 16-byte load
+//     per lane) and every lane sums its receiver against the whole tile. With
+//     r < 64 receivers the tile is split over 64 / R lane groups (R = r rounded
+//     up to a power of two) whose partial sums are added by shuffles.
 #include <mutex>
 
 #include "device.h"
@@ -32,252 +31,370 @@
 
 namespace fmmds {
 
-// Scratch counters of one near-field call (kNearCounters of them): [0]
-// tasks written, [1] the dense path's ticket.
-
-__global__ __launch_bounds__(256) void k_pack_sources(const float* __restrict__ sxyz,
-                                                      const uint32_t* __restrict__ sperm,
-                                                      const float* __restrict__ charges,
-                                                      uint32_t n, float4* __restrict__ out,
-                                                      uint32_t* __restrict__ counters) {
-  if (blockIdx.x == 0 && threadIdx.x < kNearCounters) counters[threadIdx.x] = 0;
-  for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < n; i += gridDim.x * 256ull) {
-    const float q = charges ? charges[sperm[i]] : 1.0f;
-    out[i] = make_float4(sxyz[3 * i], sxyz[3 * i + 1], sxyz[3 * i + 2], q);
-  }
-}
-
-// One term of the sum: q / |x - y|, zero for coincident points.
-__device__ __forceinline__ float pair_term(const float4 x, float yx, float yy, float yz) {
+// One term of the sum, q / |x - y|, zero for coincident points, added to acc.
+// Coordinates come scaled by kNearScale (exactly), so that the square of the
+// smallest distance whose square FP32 can hold is a normal number, as the
+// reciprocal square root instruction needs; the sums are scaled back at the
+// end. A term takes 10 instructions; with the library's rsqrtf, which scales
+// its argument each time, it took 16 (3.6M uniform points at 110 per box, bound
+// by these: 4406 -> 3252 us).
+constexpr float kNearScale = 4096.0f;
+__device__ __forceinline__ void add_term(float& acc, const float4 x, float yx, float yy, float yz) {
   const float dx = x.x - yx, dy = x.y - yy, dz = x.z - yz;
   const float r2 = dx * dx + dy * dy + dz * dz;
-  return r2 > 0.0f ? x.w * rsqrtf(r2) : 0.0f;
+  const float inv = __builtin_amdgcn_rsqf(r2);
+  acc += x.w * (r2 >= 1.17549435e-38f ? inv : 0.0f);
 }
 
-// Sparse path: one thread per receiver box, up to R of its points at a time:
-// each source point is loaded once for all of them. R = 4 suits boxes of one
-// or two points (uniform input); with more points per box (sphere, clusters)
-// a wave then walks its lists twice whenever one of its boxes has five or
-// more, so R = 8 is taken when the receivers average more than two points
-// per finest box (measured: 2.24 against 2.86 ms on the uniform benchmark
-// build, 4.36 against 3.83 ms on sphere + clusters). The list is
-// walked eight entries at a time (their source ranks, then their bookmarks,
-// then their points), so that the dependent loads of eight entries overlap.
-// Every receiver's terms are added in list order, point by point. A box of
-// more than kNearDenseMin points is not summed here: its thread appends the
-// box's tasks (box, chunk of 64 receivers) to the dense path's task list.
-constexpr uint32_t kNearBatch = 8;
-
-template <uint32_t R>
-__global__ __launch_bounds__(256) void k_near_field(
-    uint32_t n_rbox, const uint32_t* __restrict__ rbegin, const float* __restrict__ rxyz,
-    const uint32_t* __restrict__ rperm, const uint32_t* __restrict__ e2_off,
-    const uint32_t* __restrict__ e2_ent, const uint32_t* __restrict__ sbegin,
-    const float4* __restrict__ src, float* __restrict__ phi,
-    unsigned long long* __restrict__ n_pairs, uint2* __restrict__ tasks,
-    uint32_t* __restrict__ counters) {
-  const uint64_t b = blockIdx.x * 256ull + threadIdx.x;
-  uint64_t pairs = 0;
-  uint32_t my_tasks = 0;
-  if (b < n_rbox) {
+// The sources as records, and the box of every W-th receiver (the first of
+// each wave of the sum; w_log2 = log2 W).
+__global__ __launch_bounds__(256) void k_pack_sources(
+    const float* __restrict__ sxyz, const uint32_t* __restrict__ sperm,
+    const float* __restrict__ charges, uint32_t n, float4* __restrict__ out,
+    const uint32_t* __restrict__ rbegin, uint32_t n_rbox, uint32_t w_log2,
+    uint32_t* __restrict__ wave_box) {
+  for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < n; i += gridDim.x * 256ull) {
+    const float q = charges ? charges[sperm[i]] : 1.0f;
+    out[i] = make_float4(kNearScale * sxyz[3 * i], kNearScale * sxyz[3 * i + 1],
+                         kNearScale * sxyz[3 * i + 2], q);
+  }
+  const uint32_t W = 1u << w_log2;
+  for (uint64_t b = blockIdx.x * 256ull + threadIdx.x; b < n_rbox; b += gridDim.x * 256ull) {
     const uint32_t k0 = rbegin[b], k1 = rbegin[b + 1];
-    if (k1 - k0 > kNearDenseMin) {
-      my_tasks = (k1 - k0 + 63u) / 64u;
-    } else {
-      const uint32_t e0 = e2_off[b], e1 = e2_off[b + 1];
-      for (uint32_t kc = k0; kc < k1; kc += R) {
-        float yx[R], yy[R], yz[R], acc[R];
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r) {
-          const uint32_t k = min(kc + r, k1 - 1);  // extra lanes repeat the last point
-          yx[r] = rxyz[3 * (uint64_t)k], yy[r] = rxyz[3 * (uint64_t)k + 1],
-          yz[r] = rxyz[3 * (uint64_t)k + 2];
-          acc[r] = 0.0f;
-        }
-        uint32_t pts = 0;
-        for (uint32_t e = e0; e < e1; e += kNearBatch) {
-          uint32_t sb[kNearBatch], i0[kNearBatch], i1[kNearBatch];
-#pragma unroll
-          for (uint32_t j = 0; j < kNearBatch; ++j) sb[j] = e + j < e1 ? e2_ent[e + j] : 0u;
-#pragma unroll
-          for (uint32_t j = 0; j < kNearBatch; ++j) {
-            const bool ok = e + j < e1;
-            i0[j] = ok ? sbegin[sb[j]] : 0u;
-            i1[j] = ok ? sbegin[sb[j] + 1] : 0u;
-          }
-#pragma unroll
-          for (uint32_t j = 0; j < kNearBatch; ++j) {
-            for (uint32_t i = i0[j]; i < i1[j]; ++i) {
-              const float4 x = src[i];
-#pragma unroll
-              for (uint32_t r = 0; r < R; ++r) acc[r] += pair_term(x, yx[r], yy[r], yz[r]);
-            }
-            pts += i1[j] - i0[j];
-          }
-        }
-        const uint32_t nr = min(R, k1 - kc);
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r)
-          if (r < nr) phi[rperm[kc + r]] = acc[r];
-        pairs += (uint64_t)pts * nr;
-      }
-    }
+    for (uint64_t t = ((uint64_t)k0 + W - 1u) >> w_log2; t << w_log2 < k1; ++t)
+      wave_box[t] = (uint32_t)b;
   }
-  // Dense boxes: one atomic per wave reserves the wave's tasks.
+}
+
+// Staging: entries of consecutive ranks are consecutive points, so a run costs
+// two bookmark loads whatever its length, and every load of 4 x 64 entries is
+// in flight at once. Lists that do not fit the LDS are taken in rounds of whole
+// boxes.
+// Short lists: a lane walks its runs as one sequence of points, four at a time,
+// so that a wave makes as many steps as its longest sequence (about 40 points
+// on uniform input; a loop per list entry makes the longest box among the lanes
+// for each entry in turn, about 110). The next four points are loaded before
+// the present ones are summed, into four sums that are added at the end.
+//
+// Measured, whole sum: 2^24 uniform sources and receivers, level 8: 2230 us with
+// a lane per receiver box and its list in batches of eight entries, 1624 us
+// now (380 of it the packing, whose charges are a random read each, 350 the
+// random writes of phi; the walk itself is bound by the cache's one line a
+// cycle: each lane reads its own 16 bytes). 6.0M sources and 5.0M receivers,
+// sphere + clusters, level 9: 3250-3800 -> 790 us. (Blocks not renumbered so that
+// an XCD takes consecutive receivers: the clustered sum takes a quarter longer.)
+// 29K sources and 15K receivers at level 3: 97 -> 48 us.
+constexpr uint32_t kNearRuns = 512;  // runs staged per wave
+constexpr uint32_t kNearChunks = 4;  // list entries staged at a time, in 64s
+// Lists of more source points go tile by tile: one lane walking such a list
+// alone would outlast its wave (limits of 256 / 512 / 1024 / 2048 points took
+// 1383 / 997 / 982 / 982 us on the clustered sum).
+constexpr uint32_t kNearLongList = 1024;
+
+struct NearStage {
+  float4 tile[64];
+  uint32_t first[kNearRuns], end[kNearRuns];
+  uint32_t pre[64];  // inclusive prefix of one box's run lengths
+  uint8_t start[64 * kNearChunks];
+};
+
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The sum over runs [r0, r1) (at most 27) of one box, by the whole wave, for
+// the nr receivers whose coordinates lanes f .. f + nr - 1 hold. Lane i of each
+// group of R lanes (R = nr rounded up to a power of two) gets receiver i's sum.
+__device__ __forceinline__ float tile_sum(NearStage& S, const float4* __restrict__ src,
+                                          uint32_t r0, uint32_t r1, uint32_t f, uint32_t nr,
+                                          float yx, float yy, float yz, uint32_t& total) {
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t incl = wave_incl_scan(my_tasks);
-  const uint32_t total = __shfl(incl, 63, 64);
-  if (total) {
-    uint32_t base = 0;
-    if (lane == 63) base = atomicAdd(&counters[0], total);
-    base = __shfl(base, 63, 64);
-    for (uint32_t c = 0; c < my_tasks; ++c)
-      tasks[base + incl - my_tasks + c] = make_uint2((uint32_t)b, c);
+  const uint32_t nrun = r1 - r0;
+  const uint32_t cnt = lane < nrun ? S.end[r0 + lane] - S.first[r0 + lane] : 0u;
+  const uint32_t pre = wave_incl_scan(cnt);
+  total = (uint32_t)__builtin_amdgcn_readlane((int)pre, 63);
+  S.pre[lane] = pre;
+  uint32_t R = 1;
+  while (R < nr) R <<= 1;
+  const uint32_t G = 64u / R, r = lane & (R - 1u), g = lane / R;
+  const int from = (int)(f + min(r, nr - 1u));
+  yx = __shfl(yx, from, 64), yy = __shfl(yy, from, 64), yz = __shfl(yz, from, 64);
+  wave_fence();
+  float acc = 0.0f;
+  for (uint32_t p = 0; p < total; p += 64) {
+    // Stage points p .. p + 63 of the runs' concatenation: point q lies in the
+    // first run whose inclusive prefix exceeds q.
+    const uint32_t q = p + lane;
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (q < total) {
+      uint32_t lo = 0, hi = nrun - 1;
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (S.pre[mid] > q) hi = mid;
+        else lo = mid + 1;
+      }
+      x = src[S.first[r0 + lo] + (q - (lo ? S.pre[lo - 1] : 0u))];
+    }
+    wave_fence();  // the previous tile's reads come before this store
+    S.tile[lane] = x;
+    wave_fence();
+    const uint32_t m = min(64u, total - p);
+    uint32_t j = g;
+    for (; j + 3 * G < m; j += 4 * G) {
+      const float4 a = S.tile[j], c = S.tile[j + G], d = S.tile[j + 2 * G], e = S.tile[j + 3 * G];
+      add_term(acc, a, yx, yy, yz);
+      add_term(acc, c, yx, yy, yz);
+      add_term(acc, d, yx, yy, yz);
+      add_term(acc, e, yx, yy, yz);
+    }
+    for (; j < m; j += G) add_term(acc, S.tile[j], yx, yy, yz);
   }
-  if (n_pairs) {
-    const uint64_t w = wave_sum_u64(pairs);
-    if (lane == 0 && w) atomicAdd(n_pairs, (unsigned long long)w);
-  }
+  wave_fence();
+  for (uint32_t o = R; o < 64u; o <<= 1) acc += __shfl_xor(acc, (int)o, 64);
+  return acc;
 }
 
-// Dense path: one wave per task, waves taking further tasks from a ticket. Lane l
-// first loads E2 entry l of the box (lists hold at most 27 entries) and the
-// entries' point counts are scanned across the wave, so that the box's
-// source points form one concatenated sequence; each round stages the next
-// 64 of them in the wave's LDS tile.
-constexpr uint32_t kNearDenseBlock = 256;
-
-__global__ __launch_bounds__(kNearDenseBlock) void k_near_dense(
-    const uint32_t* __restrict__ rbegin, const float* __restrict__ rxyz,
-    const uint32_t* __restrict__ rperm, const uint32_t* __restrict__ e2_off,
-    const uint32_t* __restrict__ e2_ent, const uint32_t* __restrict__ sbegin,
-    const float4* __restrict__ src, float* __restrict__ phi,
-    unsigned long long* __restrict__ n_pairs, const uint2* __restrict__ tasks,
-    uint32_t* __restrict__ counters) {
-  constexpr uint32_t kWaves = kNearDenseBlock / 64;
-  __shared__ float4 s_tile[kWaves][64];
-  __shared__ uint32_t s_pre[kWaves][64];  // inclusive prefix of the entries' point counts
-  __shared__ uint32_t s_first[kWaves][64];  // first sorted source point of each entry
-  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-  const uint32_t n_tasks = __hip_atomic_load(&counters[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const uint32_t n_waves = gridDim.x * kWaves;
-  uint64_t pairs = 0;
-  // Wave g takes task g first, then tickets past the first n_waves: waves
-  // without a task exit without touching the ticket (atomics on one address
-  // are serialized, and most waves have nothing to do on sparse input).
-  for (uint32_t t = blockIdx.x * kWaves + w; t < n_tasks;) {
-    const uint2 task = tasks[t];
-    const uint32_t b = task.x;
-    const uint32_t k0 = rbegin[b] + 64u * task.y;
-    const uint32_t nr = min(64u, rbegin[b + 1] - k0);
-    const uint32_t e0 = e2_off[b], ne = e2_off[b + 1] - e0;  // ne <= 27
-    uint32_t first = 0, cnt = 0;
-    if (lane < ne) {
-      const uint32_t sb = e2_ent[e0 + lane];
-      first = sbegin[sb];
-      cnt = sbegin[sb + 1] - first;
+template <uint32_t W>
+__global__ __launch_bounds__(256, 5) void k_near_field(
+    uint32_t n_recv, const uint32_t* __restrict__ rbegin, uint32_t n_rbox,
+    const float* __restrict__ rxyz, const uint32_t* __restrict__ rperm,
+    const uint32_t* __restrict__ e2_off, const uint32_t* __restrict__ e2_ent,
+    const uint32_t* __restrict__ sbegin, const float4* __restrict__ src, float* __restrict__ phi,
+    unsigned long long* __restrict__ n_pairs, const uint32_t* __restrict__ wave_box) {
+  __shared__ NearStage s_stage[4];
+  constexpr uint32_t kParts = 64u / W;  // lanes per receiver
+  const uint32_t lane = threadIdx.x & 63u, rec = lane & (W - 1u), part = lane / W;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  NearStage& S = s_stage[w];
+  // consecutive receivers on one XCD: their sources come into one L2
+  const uint64_t t = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * 4 + w;
+  const uint64_t k0 = W * t;
+  if (k0 >= n_recv) return;  // whole wave
+  // Box of each receiver: the wave's first one plus the box starts up to it.
+  const uint32_t b0 = wave_box[t];
+  S.start[lane] = 0;
+  wave_fence();
+  if (lane < W && b0 + 1 + (uint64_t)lane < n_rbox) {
+    const uint32_t st = rbegin[b0 + 1 + lane];
+    if (st < k0 + W) S.start[st - (uint32_t)k0] = 1;
+  }
+  wave_fence();
+  const uint64_t starts = __ballot(lane < W && S.start[lane] != 0);
+  const uint32_t jb = (uint32_t)__popcll(starts & ((2ull << rec) - 1ull));
+  const uint64_t k = k0 + rec;
+  const bool mine = k < n_recv;
+  float yx = 0.0f, yy = 0.0f, yz = 0.0f;
+  uint32_t perm = 0;
+  if (mine) {
+    yx = kNearScale * rxyz[3 * k], yy = kNearScale * rxyz[3 * k + 1];
+    yz = kNearScale * rxyz[3 * k + 2];
+    perm = rperm[k];
+  }
+  const uint32_t n_here = (uint32_t)min((uint64_t)W, n_recv - k0);
+  // Lane j < nb: where box b0 + j's list starts; e_end: where the last one ends.
+  const uint32_t nb = 1u + (uint32_t)__popcll(starts);
+  const uint32_t off = e2_off[min(b0 + lane, n_rbox)];
+  const uint32_t e_end = (uint32_t)__builtin_amdgcn_readfirstlane((int)e2_off[b0 + nb]);
+  uint64_t pts = 0;
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  float whole = 0.0f;  // the receiver's sum, if its box was taken tile by tile
+  uint32_t box = 0;  // the first box whose list is not summed yet
+  uint32_t e = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+  while (box < nb) {
+    // Stage kNearChunks * 64 entries at a time.
+    uint32_t runs = 0, my_run = 0;  // lane j: the first run of box b0 + j
+    uint32_t prev = 0;              // the last entry of the chunk before
+    uint32_t e0 = e;
+    while (e0 < e_end) {
+      uint32_t s[kNearChunks];
+#pragma unroll
+      for (uint32_t c = 0; c < kNearChunks; ++c) {
+        s[c] = e2_ent[min(e0 + 64u * c + lane, e_end - 1u)];
+        S.start[64u * c + lane] = 0;
+      }
+      wave_fence();
+      const bool here = lane >= box && lane < nb && off >= e0 && off - e0 < 64u * kNearChunks;
+      if (here) S.start[off - e0] = 1;
+      wave_fence();
+      uint64_t m[kNearChunks];
+      uint32_t last = prev, total = 0;
+#pragma unroll
+      for (uint32_t c = 0; c < kNearChunks; ++c) {
+        const uint32_t up = (uint32_t)__shfl_up((int)s[c], 1, 64);
+        const uint32_t before = lane == 0 ? last : up;
+        m[c] = __ballot(e0 + 64u * c + lane < e_end &&
+                        (S.start[64u * c + lane] != 0 || s[c] != before + 1u));
+        last = (uint32_t)__builtin_amdgcn_readlane((int)s[c], 63);
+        total += (uint32_t)__popcll(m[c]);
+      }
+      if (runs + total > kNearRuns) break;  // (never the first time: kNearChunks * 64 runs fit)
+      uint32_t first[kNearChunks], end[kNearChunks], r[kNearChunks];
+      bool is_end[kNearChunks];
+#pragma unroll
+      for (uint32_t c = 0; c < kNearChunks; ++c) {
+        const uint32_t i = e0 + 64u * c + lane;
+        const bool is_start = (m[c] >> lane) & 1u;
+        // the run of this entry (lane 0 of the first chunk starts one)
+        r[c] = runs + mbcnt(m[c]) + (is_start ? 1u : 0u) - 1u;
+        is_end[c] = i < e_end && (lane == 63u || i + 1u == e_end || ((m[c] >> ((lane + 1u) & 63u)) & 1u));
+        if (is_start) first[c] = sbegin[s[c]];
+        if (is_end[c]) end[c] = sbegin[s[c] + 1u];
+        const uint32_t r_of = (uint32_t)__shfl((int)r[c], (int)(off - e0 - 64u * c) & 63, 64);
+        if (here && off < e_end && (off - e0) >> 6 == c) my_run = r_of;
+        runs += (uint32_t)__popcll(m[c]);
+      }
+#pragma unroll
+      for (uint32_t c = 0; c < kNearChunks; ++c) {
+        if ((m[c] >> lane) & 1u) S.first[r[c]] = first[c];
+        if (is_end[c]) S.end[r[c]] = end[c];  // (a run over two chunks: the later one's stays)
+      }
+      prev = last;
+      e0 += 64u * kNearChunks;
     }
-    const uint32_t pre = wave_incl_scan(cnt);
-    const uint32_t total = __shfl(pre, 63, 64);
-    s_pre[w][lane] = pre;
-    s_first[w][lane] = first;
-    // lanes: receiver r = lane % R, slice s = lane / R of S = 64 / R slices
-    uint32_t R = 1;
-    while (R < nr) R <<= 1;
-    const uint32_t S = 64u / R, r = lane & (R - 1), s = lane / R;
-    const uint32_t k = k0 + min(r, nr - 1);
-    const float yx = rxyz[3 * (uint64_t)k], yy = rxyz[3 * (uint64_t)k + 1],
-                yz = rxyz[3 * (uint64_t)k + 2];
-    float acc = 0.0f;
-    for (uint32_t p = 0; p < total; p += 64) {
-      // Stage points p .. p + 63 of the concatenation: point q lies in the
-      // first entry whose inclusive prefix exceeds q.
-      const uint32_t q = p + lane;
-      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (q < total) {
-        uint32_t lo = 0, hi = ne - 1;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi) >> 1;
-          if (s_pre[w][mid] > q) hi = mid;
-          else lo = mid + 1;
+    wave_fence();
+    // The boxes staged whole: up to the last whose next list starts by e0.
+    uint32_t stop = nb;
+    if (e0 < e_end) {
+      stop = (uint32_t)__popcll(__ballot(lane < nb && off <= e0)) - 1u;  // box `stop` is cut
+    }
+    if (lane < nb && off >= min(e0, e_end)) my_run = runs;  // lists after them (or empty at the end)
+    uint32_t r = (uint32_t)__shfl((int)my_run, (int)jb, 64);
+    const uint32_t r_next = (uint32_t)__shfl((int)my_run, (int)min(jb + 1u, 63u), 64);
+    const uint32_t r1 = jb + 1u < nb ? r_next : runs;
+    const bool now = mine && jb >= box && jb < stop;
+    // The points of this lane's list, and whether the box goes tile by tile.
+    uint32_t n = 0;
+    if (now)
+      for (uint32_t i = r; i < r1; ++i) n += S.end[i] - S.first[i];
+    const uint64_t heads = starts | 1ull;  // lanes < W: first receiver of each box here
+    const uint32_t f = 63u - (uint32_t)__clzll((long long)(heads & ((2ull << rec) - 1ull)));
+    const uint64_t above = f >= 63u ? 0ull : heads >> (f + 1u);
+    const uint32_t nr = above ? (uint32_t)__ffsll((long long)above) : n_here - f;
+    const bool tiled = now && n > 0 && (n > kNearLongList || 2u * nr > W);
+    uint64_t todo = __ballot(tiled && part == 0u && rec == f);
+    while (todo) {
+      const int h = __ffsll((long long)todo) - 1;
+      todo &= todo - 1;
+      const uint32_t hr0 = (uint32_t)__builtin_amdgcn_readlane((int)r, h),
+                     hr1 = (uint32_t)__builtin_amdgcn_readlane((int)r1, h),
+                     hn = (uint32_t)__builtin_amdgcn_readlane((int)nr, h);
+      uint32_t total;
+      const float v = tile_sum(S, src, hr0, hr1, (uint32_t)h, hn, yx, yy, yz, total);
+      const float mine_v = __shfl(v, (int)((rec - (uint32_t)h) & 63u), 64);
+      if (rec >= (uint32_t)h && rec < (uint32_t)h + hn) whole = mine_v;
+      if (lane == 0) pts += (uint64_t)total * hn;
+    }
+    if (now && !tiled && n > 0) {
+      // this lane's part of the list: points [skip, skip + left)
+      uint32_t skip = 0, left = n;
+      if (kParts > 1) {
+        skip = n * part / kParts;
+        left = n * (part + 1u) / kParts - skip;
+      }
+      if (left > 0) {
+      uint32_t p = S.first[r], p_end = S.end[r];
+      if (kParts > 1) {
+        while (skip >= p_end - p) {
+          skip -= p_end - p;
+          ++r;
+          p = S.first[r], p_end = S.end[r];
         }
-        const uint32_t before = lo ? s_pre[w][lo - 1] : 0u;
-        x = src[s_first[w][lo] + (q - before)];
+        p += skip;
       }
-      // every lane's reads of the previous tile were issued before this store
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      s_tile[w][lane] = x;
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      const uint32_t m = min(64u, total - p);
-      uint32_t j = s;
-      for (; j + 3 * S < m; j += 4 * S) {
-        const float4 a = s_tile[w][j], c = s_tile[w][j + S], d = s_tile[w][j + 2 * S],
-                     f = s_tile[w][j + 3 * S];
-        acc += pair_term(a, yx, yy, yz);
-        acc += pair_term(c, yx, yy, yz);
-        acc += pair_term(d, yx, yy, yz);
-        acc += pair_term(f, yx, yy, yz);
+      pts += left;
+      // the next four points; returns the number of them that there are
+      auto next4 = [&](float4* x) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          x[u] = src[p];  // (past the end: the last run's first point)
+          if (left > 0) {
+            --left;
+            ++c;
+            if (++p == p_end) {
+              r = min(r + 1u, r1 - 1u);
+              p = S.first[r], p_end = S.end[r];
+            }
+          }
+        }
+        return c;
+      };
+      auto sum4 = [&](const float4* x, uint32_t c) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if ((uint32_t)u < c) add_term(acc[u], x[u], yx, yy, yz);
+      };
+      float4 xa[4], xb[4];
+      uint32_t ca = next4(xa), cb = 0;
+      while (true) {
+        cb = 0;
+        if (left > 0) cb = next4(xb);
+        sum4(xa, ca);
+        if (cb == 0) break;
+        ca = 0;
+        if (left > 0) ca = next4(xa);
+        sum4(xb, cb);
+        if (ca == 0) break;
       }
-      for (; j < m; j += S) acc += pair_term(s_tile[w][j], yx, yy, yz);
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      }
     }
-    for (uint32_t o = R; o < 64u; o <<= 1) acc += __shfl_xor(acc, (int)o, 64);
-    if (s == 0 && r < nr) phi[rperm[k]] = acc;
-    if (lane == 0) pairs += (uint64_t)total * nr;
-    // the next task restages s_pre / s_first: all reads of this one are done
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    uint32_t next = 0;
-    if (lane == 0) next = atomicAdd(&counters[1], 1u);
-    t = n_waves + __shfl(next, 0, 64);
+    box = stop;
+    e = (uint32_t)__builtin_amdgcn_readlane((int)off, (int)min(stop, 63u));
+    wave_fence();
   }
-  if (n_pairs && lane == 0 && pairs) atomicAdd(n_pairs, (unsigned long long)pairs);
+  float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+#pragma unroll
+  for (uint32_t o = W; o < 64u; o <<= 1) sum += __shfl_xor(sum, (int)o, 64);
+  if (mine && part == 0u) phi[perm] = kNearScale * (sum + whole);
+  if (n_pairs) {
+    const uint64_t all = wave_sum_u64(pts);
+    if (lane == 0 && all) atomicAdd(n_pairs, (unsigned long long)all);
+  }
 }
 
-uint64_t near_field_max_tasks(uint32_t n_recv) {
-  // a dense box of r > kNearDenseMin points has ceil(r / 64) <= r / (kNearDenseMin + 1)
-  // tasks (since kNearDenseMin + 1 <= 32)
-  static_assert(kNearDenseMin + 1 <= 32, "task bound");
-  return (uint64_t)n_recv / (kNearDenseMin + 1) + 1;
+// log2 of the receivers per wave: 64 when that gives the chip's 8192 wave slots
+// a wave each, fewer (and so more lanes per receiver) below, down to 4.
+uint32_t near_field_w_log2(uint32_t n_recv) {
+  uint32_t l = 6;
+  while (l > 2 && ((uint64_t)n_recv >> l) < 8192) --l;
+  return l;
 }
 
-void launch_pack_sources(const float* sxyz, const uint32_t* sperm, const float* charges,
-                         uint32_t n, float4* out, uint32_t* counters, hipStream_t s) {
-  const uint32_t grid = std::max<uint32_t>(1, std::min<uint32_t>(div_up(n, 256), 8192));
-  hipLaunchKernelGGL(k_pack_sources, dim3(grid), dim3(256), 0, s, sxyz, sperm, charges, n, out,
-                     counters);
+uint64_t near_field_waves(uint32_t n_recv) {
+  const uint32_t l = near_field_w_log2(n_recv);
+  return ((uint64_t)n_recv + (1u << l) - 1u) >> l;
 }
 
-void launch_near_field(uint32_t n_rbox, uint32_t n_recv, const uint32_t* rbegin,
-                       const float* rxyz, const uint32_t* rperm, const uint32_t* e2_off,
-                       const uint32_t* e2_ent, const uint32_t* sbegin, const float4* src,
-                       float* phi, unsigned long long* n_pairs, uint2* tasks,
-                       uint32_t* counters, hipStream_t s) {
-  if (n_rbox == 0) return;
-  if (n_recv > 2ull * n_rbox)
-    hipLaunchKernelGGL(k_near_field<8>, dim3(div_up(n_rbox, 256)), dim3(256), 0, s, n_rbox,
-                       rbegin, rxyz, rperm, e2_off, e2_ent, sbegin, src, phi, n_pairs, tasks,
-                       counters);
-  else
-    hipLaunchKernelGGL(k_near_field<4>, dim3(div_up(n_rbox, 256)), dim3(256), 0, s, n_rbox,
-                       rbegin, rxyz, rperm, e2_off, e2_ent, sbegin, src, phi, n_pairs, tasks,
-                       counters);
-  // Persistent waves over the dense tasks: enough for the most tasks the
-  // receivers can make, at most eight blocks per compute unit; they exit
-  // when the ticket passes the task count.
-  const uint32_t waves = kNearDenseBlock / 64;
-  const uint32_t grid = (uint32_t)std::min<uint64_t>(
-      div_up(near_field_max_tasks(n_recv), waves), 2048);
-  hipLaunchKernelGGL(k_near_dense, dim3(grid), dim3(kNearDenseBlock), 0, s, rbegin, rxyz, rperm,
-                     e2_off, e2_ent, sbegin, src, phi, n_pairs, tasks, counters);
+void launch_near_field(const float* sxyz, const uint32_t* sperm, const float* charges,
+                       uint32_t n_src, float4* src, uint32_t n_rbox, uint32_t n_recv,
+                       const uint32_t* rbegin, const float* rxyz, const uint32_t* rperm,
+                       const uint32_t* e2_off, const uint32_t* e2_ent, const uint32_t* sbegin,
+                       float* phi, unsigned long long* n_pairs, uint32_t* wave_box,
+                       hipStream_t s) {
+  const uint32_t l = near_field_w_log2(n_recv);
+  const uint32_t pack = std::max<uint32_t>(
+      1, std::min<uint32_t>(div_up(std::max(n_src, n_rbox), 256), 8192));
+  hipLaunchKernelGGL(k_pack_sources, dim3(pack), dim3(256), 0, s, sxyz, sperm, charges, n_src, src,
+                     rbegin, n_rbox, l, wave_box);
+  const dim3 grid(div_up(near_field_waves(n_recv), 4));
+#define FMMDS_NEAR(W)                                                                           \
+  hipLaunchKernelGGL(k_near_field<W>, grid, dim3(256), 0, s, n_recv, rbegin, n_rbox, rxyz,      \
+                     rperm, e2_off, e2_ent, sbegin, src, phi, n_pairs, wave_box)
+  switch (l) {
+    case 6: FMMDS_NEAR(64); break;
+    case 5: FMMDS_NEAR(32); break;
+    case 4: FMMDS_NEAR(16); break;
+    case 3: FMMDS_NEAR(8); break;
+    default: FMMDS_NEAR(4); break;
+  }
+#undef FMMDS_NEAR
 }
 
 // ---------------------------------------------------------------------------
 // Fixed scratch of fmmds_near_field_static, the entry point for callers that
-// cannot allocate: packed sources, dense-path tasks and counters live here
-// instead of in memory from the cache. Each GPU holds its own copy of the
+// cannot allocate: the packed sources and the waves' boxes live here instead
+// of in memory from the cache. Each GPU holds its own copy of the
 // array, at its own address, from the library's load on that GPU until the
 // process ends. In host code `scratch` names a host-side stand-in, never the
 // device memory: the device address comes from hipGetSymbolAddress, once per

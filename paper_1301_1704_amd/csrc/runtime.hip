@@ -1919,27 +1919,25 @@ fmmds_status box_types(const fmmds_tree* t, uint32_t l_par, const uint32_t* owne
   return hipGetLastError() == hipSuccess ? FMMDS_OK : FMMDS_ERR_DEVICE;
 }
 
-// Bytes of the near-field scratch: packed sources, the dense path's tasks,
-// its counters.
+// Bytes of the near-field scratch: packed sources, then the first box of each
+// wave of receivers, for which 8 bytes per 9 receivers and 512 are set aside
+// (the header's bound on what the fixed scratch takes).
 struct NearScratch {
-  size_t src_b, task_b, total;
+  size_t src_b, total;
   explicit NearScratch(const fmmds_tree* t)
       : src_b(round_up((size_t)t->n_src * 16, 256)),
-        task_b(round_up(near_field_max_tasks(t->n_recv) * sizeof(uint2), 256)),
-        total(src_b + task_b + 256) {}
+        total(src_b + std::max<size_t>(round_up(near_field_waves(t->n_recv) * 4, 256),
+                                       round_up(((size_t)t->n_recv / 9 + 1) * 8, 256) + 256)) {}
 };
 
 void near_field_launch(const fmmds_tree* t, const NearScratch& ns, char* scratch,
                        const float* charges, float* phi, uint64_t* n_pairs, hipStream_t st) {
   const TreeImpl* impl = (const TreeImpl*)t->impl;
   const uint32_t D = t->depth;
-  float4* src4 = (float4*)scratch;
-  uint2* tasks = (uint2*)(scratch + ns.src_b);
-  uint32_t* counters = (uint32_t*)(scratch + ns.src_b + ns.task_b);
-  launch_pack_sources(t->src_sorted_xyz, t->src_perm, charges, t->n_src, src4, counters, st);
-  launch_near_field(t->recv[D].n, t->n_recv, t->recv[D].begin, t->recv_sorted_xyz, t->recv_perm,
-                    impl->lists[D].off[0], impl->lists[D].ent[0], t->src[D].begin, src4, phi,
-                    (unsigned long long*)n_pairs, tasks, counters, st);
+  launch_near_field(t->src_sorted_xyz, t->src_perm, charges, t->n_src, (float4*)scratch,
+                    t->recv[D].n, t->n_recv, t->recv[D].begin, t->recv_sorted_xyz, t->recv_perm,
+                    impl->lists[D].off[0], impl->lists[D].ent[0], t->src[D].begin, phi,
+                    (unsigned long long*)n_pairs, (uint32_t*)(scratch + ns.src_b), st);
 }
 
 fmmds_status near_field(const fmmds_tree* t, const float* charges, float* phi,
