@@ -328,7 +328,7 @@ fmmds_status fmmds_displace(const fmmds_displace_set* sets, uint32_t n_sets, flo
  * EXPORT if a receiver box of another rank has it in its E4 list, else
  * DOMESTIC; elsewhere it is IMPORT if a receiver box of `rank` has it in its
  * E4 list, else OTHER. Uses a temporary device buffer from the library's
- * cache: 2 bytes per source box and 4 per receiver box of the largest level.
+ * cache: 4 bytes per receiver box of levels l_crit and below it.
  */
 enum {
   FMMDS_BOX_DOMESTIC = 0,

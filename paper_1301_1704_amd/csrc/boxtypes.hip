@@ -28,7 +28,7 @@
 
 namespace fmmds {
 
-constexpr uint32_t kMarkBlocks = 4096;  // step 2: 16384 waves walk the work list
+constexpr uint32_t kMarkBlocks = 2048;  // per level, 8192 waves walk its work list
 
 // Coordinate of a Morton index on one axis (bits 3b + axis).
 __device__ __forceinline__ uint32_t axis_coord(uint64_t key, int axis) {
@@ -57,166 +57,171 @@ __global__ __launch_bounds__(256) void k_partition(const KeyT* __restrict__ rkey
   }
 }
 
-__global__ __launch_bounds__(256) void k_fill_u8(uint8_t* __restrict__ p, uint32_t n, uint8_t v) {
-  for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < n; i += gridDim.x * 256ull) p[i] = v;
-}
-
-// Marks are bytes in two arrays (needed elsewhere / needed here), set with
-// plain stores: every writer stores the same value, so no atomics are needed.
+// Box types, every level in two launches (grid y = level - 2).
 //
-// Step 1 (per receiver): does the receiver have to read its E4 list? Those
-// that do are appended to a work list (one atomic per wave, at the end).
+// k_types_init: per source box, the type it has if no list names it (DOMESTIC or
+// OTHER; at the critical level IMPORT, ROOT or DOMESTIC), and per receiver,
+// whether its E4 list has to be read; those receivers go to the level's work
+// list, one atomic per block.
+// k_types_mark: one wave per listed receiver at a time; the source boxes its list
+// names become EXPORT or IMPORT. Every writer of a box stores the same value, so
+// plain byte stores do.
+//
 // Critical level: receivers with a nonempty receiver child on another rank.
+// Levels l >= l_par: the M2L region of r is, per axis, the level-l coordinates
+// 2(p - 1) .. 2(p + 1) + 1 around its parent coordinate p; their l_par ancestors
+// are that range shifted right by l - l_par. Marks need a region with another
+// rank than r's, and a receiver of another rank marks only boxes of `rank`, so
+// its region must also touch `rank`. The region is the parent's, and below l_par
+// so is r's owner: there one thread decides for all children of a parent.
+//
+// What bounds it: one read of every box's key and the lists near rank borders.
+// On the 2 x 2^24 uniform build (13M boxes a side, 64 ranks, l_par = 4), four
+// launches per level (marks cleared, receivers picked one by one, marked, types
+// written) took 340 us with the partition; these two take 140 us (105 us of kernels).
 template <typename KeyT>
-__global__ __launch_bounds__(256) void k_pick_crit(uint32_t n_recv,
-                                                   const uint32_t* __restrict__ rchild,
-                                                   const KeyT* __restrict__ rkey_par,
-                                                   const uint32_t* __restrict__ owner,
-                                                   uint32_t rank, uint32_t* __restrict__ work,
-                                                   uint32_t* __restrict__ n_work) {
-  const uint64_t r = blockIdx.x * 256ull + threadIdx.x;
-  bool pick = false;
-  if (r < n_recv)
-    for (uint32_t c = rchild[r]; c < rchild[r + 1]; ++c)
-      pick |= owner[(uint64_t)rkey_par[c]] != rank;
-  const uint64_t b = __ballot(pick);
-  if (!b) return;
-  uint32_t base = 0;
-  if ((threadIdx.x & 63u) == 0) base = atomicAdd(n_work, (uint32_t)__popcll(b));
-  base = (uint32_t)__builtin_amdgcn_readfirstlane(base);
-  if (pick) work[base + mbcnt(b)] = (uint32_t)r;
-}
-
-// Levels l >= l_par. The M2L region of r: per axis the level-l coordinates
-// 2(p - 1) .. 2(p + 1) + 1 around its parent coordinate p; their l_par
-// ancestors are that range shifted right by l - l_par. Marks need a region
-// with another rank than r's, and a receiver of another rank marks only boxes
-// of `rank`, so its region must also touch `rank`.
-template <typename KeyT>
-__global__ __launch_bounds__(256) void k_pick_deep(uint32_t n_recv, const KeyT* __restrict__ rkey,
-                                                   uint32_t level, uint32_t l_par,
-                                                   const uint32_t* __restrict__ owner,
-                                                   uint32_t rank, uint32_t* __restrict__ work,
-                                                   uint32_t* __restrict__ n_work) {
-  const uint64_t r = blockIdx.x * 256ull + threadIdx.x;
-  bool pick = false;
-  if (r < n_recv) {
-    const uint32_t sh = level - l_par;
-    const uint64_t kr = (uint64_t)rkey[r];
-    const uint32_t o_r = owner[kr >> (3 * sh)];
-    const int32_t top = (1 << l_par) - 1;
-    int32_t lo[3], hi[3];
-    for (int d = 0; d < 3; ++d) {
-      const int32_t p = (int32_t)(axis_coord(kr, d) >> 1);
-      lo[d] = max(0, (2 * (p - 1)) >> sh);
-      hi[d] = min(top, (2 * (p + 1) + 1) >> sh);
-    }
-    bool mixed = false, touches = o_r == rank;
-    for (int32_t z = lo[2]; z <= hi[2]; ++z)
-      for (int32_t y = lo[1]; y <= hi[1]; ++y)
-        for (int32_t x = lo[0]; x <= hi[0]; ++x) {
-          const uint32_t o = owner[spread3((uint32_t)x) | (spread3((uint32_t)y) << 1) |
-                                   (spread3((uint32_t)z) << 2)];
-          mixed |= o != o_r;
-          touches |= o == rank;
-        }
-    pick = mixed && touches;
+__device__ __forceinline__ bool region_picked(const BoxTypes& a, uint64_t kp, uint32_t sh,
+                                              uint32_t o_r) {
+  const int32_t top = (1 << a.l_par) - 1;
+  int32_t lo[3], hi[3];
+  for (int d = 0; d < 3; ++d) {
+    const int32_t p = (int32_t)axis_coord(kp, d);
+    lo[d] = max(0, (2 * (p - 1)) >> sh);
+    hi[d] = min(top, (2 * (p + 1) + 1) >> sh);
   }
-  const uint64_t b = __ballot(pick);
-  if (!b) return;
-  uint32_t base = 0;
-  if ((threadIdx.x & 63u) == 0) base = atomicAdd(n_work, (uint32_t)__popcll(b));
-  base = (uint32_t)__builtin_amdgcn_readfirstlane(base);
-  if (pick) work[base + mbcnt(b)] = (uint32_t)r;
+  bool mixed = false, touches = o_r == a.rank;
+  for (int32_t z = lo[2]; z <= hi[2]; ++z)
+    for (int32_t y = lo[1]; y <= hi[1]; ++y)
+      for (int32_t x = lo[0]; x <= hi[0]; ++x) {
+        const uint32_t o = a.owner[spread3((uint32_t)x) | (spread3((uint32_t)y) << 1) |
+                                   (spread3((uint32_t)z) << 2)];
+        mixed |= o != o_r;
+        touches |= o == a.rank;
+      }
+  return mixed && touches;
 }
 
-// Step 2: one wave per listed receiver at a time; its E4 entries (at most
-// 189) are read three 64-entry chunks at once, every load before any store
-// (on this GPU a wait for a load also waits for earlier stores). At the
-// critical level (deep == false) every entry is needed elsewhere.
-template <typename KeyT, bool DEEP>
-__global__ __launch_bounds__(256) void k_mark(const uint32_t* __restrict__ work,
-                                              const uint32_t* __restrict__ n_work,
-                                              const KeyT* __restrict__ rkey,
-                                              const KeyT* __restrict__ skey, uint32_t sh,
-                                              const uint32_t* __restrict__ owner, uint32_t rank,
-                                              const uint32_t* __restrict__ e4_off,
-                                              const uint32_t* __restrict__ e4_ent,
-                                              uint8_t* __restrict__ elsewhere,
-                                              uint8_t* __restrict__ here) {
+// The block's picks [first, first + n) of each thread to the level's work list.
+__device__ __forceinline__ void append_work(const BoxTypesLevel& v, uint32_t first, uint32_t n) {
+  __shared__ uint32_t s_w[5];
+  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  const uint32_t incl = wave_incl_scan(n);
+  __syncthreads();  // (s_w of the round before)
+  if (lane == 63) s_w[w] = incl;
+  __syncthreads();
+  const uint32_t total = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+  if (total == 0) return;  // the whole block
+  if (threadIdx.x == 0) s_w[4] = atomicAdd(v.n_work, total);
+  __syncthreads();
+  uint32_t at = s_w[4] + incl - n;
+  for (uint32_t i = 0; i < w; ++i) at += s_w[i];
+  for (uint32_t i = 0; i < n; ++i) v.work[at + i] = first + i;
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(256) void k_types_init(BoxTypes a) {
+  const uint32_t l = blockIdx.y + 2;
+  const BoxTypesLevel& v = a.lv[l];
+  const uint32_t l_crit = a.l_par - 1;
+  const uint64_t t0 = blockIdx.x * 256ull + threadIdx.x, step = gridDim.x * 256ull;
+  if (l < l_crit) {
+    for (uint64_t k = t0; k < v.n_src; k += step) v.types[k] = FMMDS_BOX_DOMESTIC;
+    return;
+  }
+  if (l == l_crit) {
+    const KeyT* __restrict__ sk = (const KeyT*)a.lv[a.l_par].skey;
+    for (uint64_t k = t0; k < v.n_src; k += step) {
+      bool on = false, off = false;
+      for (uint32_t c = v.schild[k]; c < v.schild[k + 1]; ++c) {
+        const bool here = a.owner[(uint64_t)sk[c]] == a.rank;
+        on |= here;
+        off |= !here;
+      }
+      v.types[k] = !on ? FMMDS_BOX_IMPORT : off ? FMMDS_BOX_ROOT : FMMDS_BOX_DOMESTIC;
+    }
+    const KeyT* __restrict__ rk = (const KeyT*)a.lv[a.l_par].rkey;
+    for (uint64_t r0 = blockIdx.x * 256ull; r0 < v.n_recv; r0 += step) {
+      const uint64_t r = r0 + threadIdx.x;
+      bool pick = false;
+      if (r < v.n_recv)
+        for (uint32_t c = v.rchild[r]; c < v.rchild[r + 1]; ++c)
+          pick |= a.owner[(uint64_t)rk[c]] != a.rank;
+      append_work(v, (uint32_t)r, pick ? 1u : 0u);
+    }
+    return;
+  }
+  const uint32_t sh = l - a.l_par;
+  const KeyT* __restrict__ sk = (const KeyT*)v.skey;
+  for (uint64_t k = t0; k < v.n_src; k += step)
+    v.types[k] = a.owner[(uint64_t)sk[k] >> (3 * sh)] == a.rank ? FMMDS_BOX_DOMESTIC
+                                                                 : FMMDS_BOX_OTHER;
+  if (sh == 0) {  // each receiver has its own owner
+    const KeyT* __restrict__ rk = (const KeyT*)v.rkey;
+    for (uint64_t r0 = blockIdx.x * 256ull; r0 < v.n_recv; r0 += step) {
+      const uint64_t r = r0 + threadIdx.x;
+      bool pick = false;
+      if (r < v.n_recv) {
+        const uint64_t kr = (uint64_t)rk[r];
+        pick = region_picked<KeyT>(a, kr >> 3, 0, a.owner[kr]);
+      }
+      append_work(v, (uint32_t)r, pick ? 1u : 0u);
+    }
+    return;
+  }
+  const BoxTypesLevel& u = a.lv[l - 1];
+  const KeyT* __restrict__ pk = (const KeyT*)u.rkey;
+  for (uint64_t p0 = blockIdx.x * 256ull; p0 < u.n_recv; p0 += step) {
+    const uint64_t p = p0 + threadIdx.x;
+    uint32_t first = 0, n = 0;
+    if (p < u.n_recv) {
+      const uint64_t kp = (uint64_t)pk[p];
+      if (region_picked<KeyT>(a, kp, sh, a.owner[kp >> (3 * (sh - 1))])) {
+        first = u.rchild[p];
+        n = u.rchild[p + 1] - first;
+      }
+    }
+    append_work(v, first, n);
+  }
+}
+
+// A listed receiver's E4 entries (at most 189) are read three 64-entry chunks at
+// once, every load before any store (on this GPU a wait for a load also waits
+// for earlier stores).
+template <typename KeyT>
+__global__ __launch_bounds__(256) void k_types_mark(BoxTypes a) {
+  const uint32_t l = blockIdx.y + a.l_par - 1;
+  const BoxTypesLevel& v = a.lv[l];
+  const bool deep = l >= a.l_par;
+  const uint32_t sh = deep ? l - a.l_par : 0;
+  const KeyT* __restrict__ rk = (const KeyT*)v.rkey;
+  const KeyT* __restrict__ sk = (const KeyT*)v.skey;
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t n = *n_work;
+  const uint32_t n = *v.n_work;
   const uint32_t n_waves = gridDim.x * 4;
   for (uint32_t w = blockIdx.x * 4 + (threadIdx.x >> 6); w < n; w += n_waves) {
-    const uint32_t r = work[w];
-    const uint32_t lo = e4_off[r], hi = e4_off[r + 1];
-    const bool r_here = DEEP ? owner[(uint64_t)rkey[r] >> (3 * sh)] == rank : false;
+    const uint32_t r = v.work[w];
+    const uint32_t lo = v.e4_off[r], hi = v.e4_off[r + 1];
+    const bool r_here = deep && a.owner[(uint64_t)rk[r] >> (3 * sh)] == a.rank;
     uint32_t k[3];
-    bool k_here[3];
+    bool set[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       const uint32_t i = lo + 64u * c + lane;
-      k[c] = i < hi ? e4_ent[i] : 0xFFFFFFFFu;
-    }
-    if (DEEP) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        k_here[c] = k[c] != 0xFFFFFFFFu && owner[(uint64_t)skey[k[c]] >> (3 * sh)] == rank;
+      k[c] = i < hi ? v.e4_ent[i] : 0xFFFFFFFFu;
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
+      set[c] = false;
       if (k[c] == 0xFFFFFFFFu) continue;
-      if (!DEEP) {
-        elsewhere[k[c]] = 1;
-      } else {
-        if (k_here[c] && !r_here) elsewhere[k[c]] = 1;
-        if (!k_here[c] && r_here) here[k[c]] = 1;
-      }
+      if (deep) set[c] = (a.owner[(uint64_t)sk[k[c]] >> (3 * sh)] == a.rank) != r_here;
+      else set[c] = v.types[k[c]] == FMMDS_BOX_DOMESTIC;
     }
+    // (a deep box on this rank named by a receiver elsewhere: EXPORT; one
+    // elsewhere named by a receiver here: IMPORT)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (set[c]) v.types[k[c]] = r_here ? FMMDS_BOX_IMPORT : FMMDS_BOX_EXPORT;
   }
-}
-
-// Critical level, sources: children on this rank and elsewhere.
-template <typename KeyT>
-__global__ __launch_bounds__(256) void k_types_crit(uint32_t n_src,
-                                                    const uint32_t* __restrict__ schild,
-                                                    const KeyT* __restrict__ skey_par,
-                                                    const uint32_t* __restrict__ owner,
-                                                    uint32_t rank,
-                                                    const uint8_t* __restrict__ elsewhere,
-                                                    uint8_t* __restrict__ types) {
-  const uint64_t k = blockIdx.x * 256ull + threadIdx.x;
-  if (k >= n_src) return;
-  bool on = false, off = false;
-  for (uint32_t c = schild[k]; c < schild[k + 1]; ++c) {
-    const bool here = owner[(uint64_t)skey_par[c]] == rank;
-    on |= here;
-    off |= !here;
-  }
-  uint8_t t;
-  if (!on) t = FMMDS_BOX_IMPORT;
-  else if (off) t = FMMDS_BOX_ROOT;
-  else t = elsewhere[k] ? FMMDS_BOX_EXPORT : FMMDS_BOX_DOMESTIC;
-  types[k] = t;
-}
-
-template <typename KeyT>
-__global__ __launch_bounds__(256) void k_types_deep(uint32_t n_src, const KeyT* __restrict__ skey,
-                                                    uint32_t level, uint32_t l_par,
-                                                    const uint32_t* __restrict__ owner,
-                                                    uint32_t rank,
-                                                    const uint8_t* __restrict__ elsewhere,
-                                                    const uint8_t* __restrict__ here_mark,
-                                                    uint8_t* __restrict__ types) {
-  const uint64_t k = blockIdx.x * 256ull + threadIdx.x;
-  if (k >= n_src) return;
-  const bool here = owner[(uint64_t)skey[k] >> (3 * (level - l_par))] == rank;
-  types[k] = here ? (elsewhere[k] ? FMMDS_BOX_EXPORT : FMMDS_BOX_DOMESTIC)
-                  : (here_mark[k] ? FMMDS_BOX_IMPORT : FMMDS_BOX_OTHER);
-}
-
-static uint32_t grid_for(uint64_t n) {
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((n + 255) / 256, 1u << 20));
 }
 
 void launch_partition(bool key64, const void* rkey, const uint32_t* rbegin, uint32_t n_boxes,
@@ -232,47 +237,19 @@ void launch_partition(bool key64, const void* rkey, const uint32_t* rbegin, uint
                        rbegin, n_boxes, n_points, n_ranks, n_idx, owner);
 }
 
-void launch_fill_u8(uint8_t* p, uint32_t n, uint8_t v, hipStream_t s) {
-  if (n == 0) return;
-  hipLaunchKernelGGL(k_fill_u8, dim3(std::min<uint32_t>(grid_for(n), 4096)), dim3(256), 0, s, p,
-                     n, v);
-}
-
-template <typename K>
-static void types_crit(const BoxTypeLevel& a, hipStream_t s) {
-  if (a.n_recv) {
-    hipLaunchKernelGGL(k_pick_crit<K>, dim3(grid_for(a.n_recv)), dim3(256), 0, s, a.n_recv,
-                       a.rchild, (const K*)a.rkey_par, a.owner, a.rank, a.work, a.n_work);
-    hipLaunchKernelGGL((k_mark<K, false>), dim3(kMarkBlocks), dim3(256), 0, s, a.work, a.n_work,
-                       (const K*)a.rkey, (const K*)a.skey, 0u, a.owner, a.rank, a.e4_off,
-                       a.e4_ent, a.elsewhere, a.here);
+void launch_box_types(bool key64, const BoxTypes& a, uint32_t depth, hipStream_t s) {
+  uint64_t most = 1;
+  for (uint32_t l = 2; l <= depth; ++l)
+    most = std::max<uint64_t>(most, std::max(a.lv[l].n_src, a.lv[l].n_recv));
+  const dim3 init((uint32_t)std::min<uint64_t>((most + 255) / 256, 8192), depth - 1);
+  const dim3 mark((uint32_t)std::min<uint64_t>((most + 3) / 4, kMarkBlocks), depth - a.l_par + 2);
+  if (key64) {
+    hipLaunchKernelGGL(k_types_init<uint64_t>, init, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_types_mark<uint64_t>, mark, dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(k_types_init<uint32_t>, init, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_types_mark<uint32_t>, mark, dim3(256), 0, s, a);
   }
-  hipLaunchKernelGGL(k_types_crit<K>, dim3(grid_for(a.n_src)), dim3(256), 0, s, a.n_src,
-                     a.schild, (const K*)a.skey_par, a.owner, a.rank, a.elsewhere, a.types);
-}
-
-template <typename K>
-static void types_deep(const BoxTypeLevel& a, hipStream_t s) {
-  if (a.n_recv) {
-    hipLaunchKernelGGL(k_pick_deep<K>, dim3(grid_for(a.n_recv)), dim3(256), 0, s, a.n_recv,
-                       (const K*)a.rkey, a.level, a.l_par, a.owner, a.rank, a.work, a.n_work);
-    hipLaunchKernelGGL((k_mark<K, true>), dim3(kMarkBlocks), dim3(256), 0, s, a.work, a.n_work,
-                       (const K*)a.rkey, (const K*)a.skey, a.level - a.l_par, a.owner, a.rank,
-                       a.e4_off, a.e4_ent, a.elsewhere, a.here);
-  }
-  hipLaunchKernelGGL(k_types_deep<K>, dim3(grid_for(a.n_src)), dim3(256), 0, s, a.n_src,
-                     (const K*)a.skey, a.level, a.l_par, a.owner, a.rank, a.elsewhere, a.here,
-                     a.types);
-}
-
-void launch_types_crit(bool key64, const BoxTypeLevel& a, hipStream_t s) {
-  if (key64) types_crit<uint64_t>(a, s);
-  else types_crit<uint32_t>(a, s);
-}
-
-void launch_types_deep(bool key64, const BoxTypeLevel& a, hipStream_t s) {
-  if (key64) types_deep<uint64_t>(a, s);
-  else types_deep<uint32_t>(a, s);
 }
 
 }  // namespace fmmds

@@ -1862,60 +1862,39 @@ fmmds_status box_types(const fmmds_tree* t, uint32_t l_par, const uint32_t* owne
   if (!t || !t->impl || !owner || !types) return FMMDS_ERR_ARG;
   if (!par_level_ok(t, l_par)) return FMMDS_ERR_LEVEL;
   const TreeImpl* impl = (const TreeImpl*)t->impl;
-  const bool key64 = t->key_bits == 64;
   const uint32_t l_crit = l_par - 1;
-  uint32_t n_max = 1, r_max = 1;
-  for (uint32_t l = l_crit; l <= t->depth; ++l) {
-    n_max = std::max(n_max, t->src[l].n);
-    r_max = std::max(r_max, t->recv[l].n);
-  }
-  // two mark arrays, the work counter and the work list, each 16-byte
-  // aligned and zeroed in whole 16-byte words
-  const size_t marks_b = round_up((size_t)n_max, 16);
-  const size_t clear_b = 2 * marks_b + 16;
-  void* flags = cache_alloc(clear_b + round_up((size_t)r_max * 4, 16), st);
-  if (!flags) return FMMDS_ERR_NOMEM;
-  uint8_t* elsewhere = (uint8_t*)flags;
-  uint8_t* here = elsewhere + marks_b;
-  uint32_t* n_work = (uint32_t*)(here + marks_b);
-  uint32_t* work = n_work + 4;
+  // one counter per level, then the levels' work lists
+  const size_t clear_b = 32 * 4;
+  size_t work = 0;
+  for (uint32_t l = l_crit; l <= t->depth; ++l) work += t->recv[l].n;
+  uint32_t* block = (uint32_t*)cache_alloc(clear_b + std::max<size_t>(work, 1) * 4, st);
+  if (!block) return FMMDS_ERR_NOMEM;
+  launch_zero(block, clear_b, st);
+  BoxTypes a{};
+  a.l_par = l_par;
+  a.rank = rank;
+  a.owner = owner;
+  uint32_t* next = block + clear_b / 4;
   size_t at = 0;
   for (uint32_t l = 2; l <= t->depth; ++l) {
-    const uint32_t ns = t->src[l].n;
-    uint8_t* ty = types + at;
-    at += ns;
-    if (l < l_crit) {
-      launch_fill_u8(ty, ns, FMMDS_BOX_DOMESTIC, st);
-      continue;
-    }
-    launch_zero(flags, clear_b, st);
-    BoxTypeLevel a{};
-    a.level = l;
-    a.l_par = l_par;
-    a.rank = rank;
-    a.n_recv = t->recv[l].n;
-    a.n_src = ns;
-    a.rkey = t->recv[l].key;
-    a.skey = t->src[l].key;
-    a.owner = owner;
-    a.e4_off = impl->lists[l].off[1];
-    a.e4_ent = impl->lists[l].ent[1];
-    a.elsewhere = elsewhere;
-    a.here = here;
-    a.work = work;
-    a.n_work = n_work;
-    a.types = ty;
-    if (l == l_crit) {
-      a.rkey_par = t->recv[l_par].key;
-      a.skey_par = t->src[l_par].key;
-      a.rchild = t->recv[l].child;
-      a.schild = t->src[l].child;
-      launch_types_crit(key64, a, st);
-    } else {
-      launch_types_deep(key64, a, st);
-    }
+    BoxTypesLevel& v = a.lv[l];
+    v.n_recv = t->recv[l].n;
+    v.n_src = t->src[l].n;
+    v.rkey = t->recv[l].key;
+    v.skey = t->src[l].key;
+    v.rchild = t->recv[l].child;
+    v.schild = t->src[l].child;
+    v.e4_off = impl->lists[l].off[1];
+    v.e4_ent = impl->lists[l].ent[1];
+    v.types = types + at;
+    at += v.n_src;
+    if (l < l_crit) continue;
+    v.n_work = block + l;
+    v.work = next;
+    next += v.n_recv;
   }
-  cache_release(flags, st);
+  launch_box_types(t->key_bits == 64, a, t->depth, st);
+  cache_release(block, st);
   return hipGetLastError() == hipSuccess ? FMMDS_OK : FMMDS_ERR_DEVICE;
 }
 
