@@ -54,6 +54,14 @@ void launch_keygen(const float* xyz, uint32_t n, uint32_t L, bool packed, uint64
 void launch_reduce_rows(const uint32_t* rows, uint32_t n_rows, uint32_t* hist, uint32_t n_pass,
                         hipStream_t s);
 void launch_digit_offsets(const uint32_t* hist, uint32_t* goff, uint32_t n_pass, hipStream_t s);
+// Both: keygen's rows to the digit offsets (`hist` zeroed).
+void launch_digits(const uint32_t* rows, uint32_t n_rows, uint32_t* hist, uint32_t* goff,
+                   uint32_t n_pass, hipStream_t s);
+// Keys and the whole sort of at most kSortSmall points (packed elements) by one
+// block: the sorted elements to `out`.
+constexpr uint32_t kSortSmall = 8192;
+void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass, uint64_t* out,
+                       uint32_t* err, hipStream_t s);
 uint32_t sort_tile_elems(int items);
 uint32_t sort_tiles(uint32_t n, int items);
 // Many point sets sorted at once, each within its own range: tile t covers
@@ -94,6 +102,9 @@ struct TabLevels {
   uint32_t* child[kMaxLevel + 1];
   uint4* node[kMaxLevel + 1];  // the list kernels' records (device.h), levels 1..L-1
 };
+// With at most kTabSmallTiles tiles phase 2 scans the counts itself (and
+// writes the box counts): phase 1 does nothing.
+constexpr uint32_t kTabSmallTiles = 64;
 uint32_t tab_tiles(uint32_t n);
 void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* sv,
                    const float* xyz, uint32_t n, uint32_t L, uint32_t* cnt, uint32_t* pre,
@@ -131,14 +142,31 @@ struct ListLevelArgs {
   uint32_t* cnt2_next;
   uint32_t* cnt4_next;
 };
+// The scan of one level's counts into offsets: n boxes, or with n_dev the count
+// there and n its capacity.
+struct ScanArgs {
+  const uint32_t* cnt2;
+  const uint32_t* cnt4;
+  uint32_t n;
+  const uint32_t* n_dev;
+  uint32_t* off2;
+  uint32_t* off4;
+  uint64_t* total2;
+  uint64_t* total4;
+  uint32_t* overflow;
+};
 void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, hipStream_t s);
+// Level 2 of a plain build (at most 8 parents and 64 boxes): counts and offsets.
+void launch_list_first(const ListLevelArgs& a, const ScanArgs& sc, hipStream_t s);
+// Levels of at most kScanSmall boxes: the fill that writes their counts scans
+// them too (the last of its blocks; `done` counts them, zeroed).
+constexpr uint32_t kScanSmall = 4096;
 void launch_list_fill(const ListLevelArgs& a, const uint32_t* off2,
-                      const uint32_t* off4, uint32_t* ent2, uint32_t* ent4, hipStream_t s);
+                      const uint32_t* off4, uint32_t* ent2, uint32_t* ent4, hipStream_t s,
+                      const ScanArgs& next = {}, uint32_t* done = nullptr);
 uint32_t scan_tiles(uint32_t n);
-void launch_scan_counts2(const uint32_t* cnt2, const uint32_t* cnt4, uint32_t n, uint32_t* off2,
-                         uint32_t* off4, uint64_t* total2, uint64_t* total4, uint32_t* overflow,
-                         uint64_t* status2, uint64_t* status4, uint32_t* tile_counter,
-                         hipStream_t s, const uint32_t* n_dev = nullptr);
+void launch_scan_counts2(const ScanArgs& sc, uint64_t* status2, uint64_t* status4,
+                         uint32_t* tile_counter, hipStream_t s);
 
 // ---- rebuild.hip
 void launch_inc_classify(const float* xyz, const float* old_xyz, const uint32_t* old_perm,

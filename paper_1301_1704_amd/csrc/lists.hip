@@ -85,10 +85,9 @@ __device__ __forceinline__ uint32_t octant_field(uint32_t a, uint32_t b, uint32_
   return q < 4 ? (a >> (8 + 6 * q)) & 63u : (b >> (6 * (q - 4))) & 63u;
 }
 
-__global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* __restrict__ cnt2,
-                                                    uint32_t* __restrict__ cnt4) {
-  const uint32_t j = threadIdx.x & 31u, h = threadIdx.x >> 5;
-  const uint64_t p = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * 8 + h;
+__device__ __forceinline__ void count_children(const ListLevelArgs& a, uint64_t p, uint32_t j,
+                                               uint32_t* __restrict__ cnt2,
+                                               uint32_t* __restrict__ cnt4) {
   const uint32_t n_up = a.n_recv_up_dev ? *a.n_recv_up_dev : a.n_recv_up;
   if (p >= n_up) return;  // whole half-wave
   // upbase: batch rank of the set's first box at level - 1 (parent-level E2
@@ -148,6 +147,30 @@ __global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* _
   }
 }
 
+__global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* __restrict__ cnt2,
+                                                    uint32_t* __restrict__ cnt4) {
+  count_children(a, (uint64_t)xcd_block(blockIdx.x, gridDim.x) * 8 + (threadIdx.x >> 5),
+                 threadIdx.x & 31u, cnt2, cnt4);
+}
+
+// A plain build's level 2 (at most 8 parents, 64 boxes): the counts and their
+// offsets in one block, one launch (5 us) less than with the general scan.
+__global__ __launch_bounds__(256) void k_list_first(ListLevelArgs a, ScanArgs sc) {
+  __shared__ uint32_t s_cnt[2][64];
+  const uint32_t n = sc.n_dev ? *sc.n_dev : sc.n, lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  count_children(a, threadIdx.x >> 5, threadIdx.x & 31u, s_cnt[0], s_cnt[1]);
+  __syncthreads();
+  if (w > 1) return;
+  const uint32_t v = lane < n ? s_cnt[w][lane] : 0u;
+  const uint32_t inc = wave_incl_scan(v);
+  uint32_t* off = w ? sc.off4 : sc.off2;
+  if (lane < n) off[lane] = inc - v;
+  if (lane == 63) {  // (64 boxes of at most 64 entries: no overflow)
+    off[n] = inc;
+    *(w ? sc.total4 : sc.total2) = inc;
+  }
+}
+
 // LDS written by other lanes of this wave is read after this point (and the
 // other way round): the LDS serves one wave's accesses in order, so this only
 // keeps the compiler from moving them.
@@ -202,15 +225,18 @@ __device__ __forceinline__ void flush_entries(uint32_t* lds, uint32_t& b, uint32
 // serves them all: with two pairs the sparse levels of a 2M-point level-13
 // build take 1.43 ms in all against 1.60 ms with one (uniform level 8: 1641 us
 // either way; its full level 7, 448 against 423 us).
-template <bool NEXT, bool BATCH, uint32_t PAIRS>
-__global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(ListLevelArgs a,
-                                                      const uint32_t* __restrict__ off2,
-                                                      const uint32_t* __restrict__ off4,
-                                                      uint32_t* __restrict__ ent2,
-                                                      uint32_t* __restrict__ ent4) {
-  // per wave: first U of both parents (8 bytes an entry), with NEXT also the
-  // windows of the receiver children; then the staged E2 and E4 entries
-  __shared__ __align__(16) uint32_t s_all[4][kFillWords];
+//
+// AGENT: the next level's counts are stored past the cache of this XCD, for the
+// block that scans them (k_list_fill_scan).
+template <bool NEXT, bool BATCH, uint32_t PAIRS, bool AGENT>
+__device__ __forceinline__ void fill_wave(const ListLevelArgs& a,
+                                          const uint32_t* __restrict__ off2,
+                                          const uint32_t* __restrict__ off4,
+                                          uint32_t* __restrict__ ent2,
+                                          uint32_t* __restrict__ ent4,
+                                          uint32_t (&s_all)[4][kFillWords]) {
+  // per wave: first U of both parents (8 bytes an entry), with NEXT also
+  // the windows of the receiver children; then the staged E2 and E4 entries
   const uint32_t lane = threadIdx.x & 63u, j = lane & 31u, hf = lane >> 5;
   const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   uint32_t* lds = s_all[w];
@@ -355,8 +381,14 @@ __global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(Li
         const uint4 v = *(const uint4*)(lds + 4 * kUnion + 32 * hh + 4 * q);
         const uint32_t c2 = (uint32_t)__popc(v.x & ex & ey & el) + (uint32_t)__popc(v.y & ex & ey & eh);
         const uint32_t at = rc + (uint32_t)__popc(rm & ((1u << qq) - 1u));
-        a.cnt2_next[at] = nz ? 0u : c2;
-        a.cnt4_next[at] = nz ? 0u : v.z - c2;
+        if (AGENT) {
+          __hip_atomic_store(a.cnt2_next + at, c2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(a.cnt4_next + at, v.z - c2, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          a.cnt2_next[at] = nz ? 0u : c2;
+          a.cnt4_next[at] = nz ? 0u : v.z - c2;
+        }
       }
     }
   }
@@ -439,6 +471,93 @@ __global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(Li
   }
 }
 
+template <bool NEXT, bool BATCH, uint32_t PAIRS>
+__global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(ListLevelArgs a,
+                                                      const uint32_t* __restrict__ off2,
+                                                      const uint32_t* __restrict__ off4,
+                                                      uint32_t* __restrict__ ent2,
+                                                      uint32_t* __restrict__ ent4) {
+  __shared__ __align__(16) uint32_t s_all[4][kFillWords];
+  fill_wave<NEXT, BATCH, PAIRS, false>(a, off2, off4, ent2, ent4, s_all);
+}
+
+// A coarse level of a plain build, whose next level has at most kScanSmall
+// boxes: the block that finishes last (`done` counts them) also turns the next
+// level's counts into offsets. Level 2 of a 4097-point build: fill, gap and scan
+// took 5.7 + 3.8 + 4.6 us, this 8.2. Past kScanSmall one block's scan would be
+// longer than the launch that it saves. Every count is past
+// the caches before its block is counted: its wave waits for its stores
+// (vmcnt 0) ahead of the barrier that the counting lane passes.
+constexpr uint32_t kScanSmallItems = kScanSmall / 256;
+__global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
+                                                           const uint32_t* __restrict__ off2,
+                                                           const uint32_t* __restrict__ off4,
+                                                           uint32_t* __restrict__ ent2,
+                                                           uint32_t* __restrict__ ent4,
+                                                           ScanArgs sc,
+                                                           uint32_t* __restrict__ done) {
+  __shared__ __align__(16) uint32_t s_all[4][kFillWords];
+  __shared__ uint32_t s_done, s_w[2][4];
+  fill_wave<true, false, 1, true>(a, off2, off4, ent2, ent4, s_all);
+  __builtin_amdgcn_s_waitcnt(0);
+  __threadfence_block();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    s_done = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (s_done + 1 != gridDim.x) return;  // whole block
+  const uint32_t n = sc.n_dev ? *sc.n_dev : sc.n;
+  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  const uint32_t base = threadIdx.x * kScanSmallItems;
+  // (the counts from where other XCDs left them, past this one's cache)
+  uint32_t v2[kScanSmallItems], v4[kScanSmallItems], sum2 = 0, sum4 = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < kScanSmallItems; ++i) {
+    const bool ok = base + i < n;
+    v2[i] = v4[i] = 0;
+    if (ok) {
+      v2[i] = __hip_atomic_load(sc.cnt2 + base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      v4[i] = __hip_atomic_load(sc.cnt4 + base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < kScanSmallItems; ++i) {
+    sum2 += v2[i];
+    sum4 += v4[i];
+  }
+  const uint32_t inc2 = wave_incl_scan(sum2), inc4 = wave_incl_scan(sum4);
+  if (lane == 63) {
+    s_w[0][w] = inc2;
+    s_w[1][w] = inc4;
+  }
+  __syncthreads();
+  uint32_t pre2 = inc2 - sum2, pre4 = inc4 - sum4;
+  for (uint32_t i = 0; i < w; ++i) {
+    pre2 += s_w[0][i];
+    pre4 += s_w[1][i];
+  }
+  // (at most kScanSmall * 216 entries: no overflow)
+#pragma unroll
+  for (uint32_t i = 0; i < kScanSmallItems; ++i) {
+    if (base + i < n) {
+      sc.off2[base + i] = pre2;
+      sc.off4[base + i] = pre4;
+      pre2 += v2[i];
+      pre4 += v4[i];
+      if (base + i + 1 == n) {
+        sc.off2[n] = pre2;
+        sc.off4[n] = pre4;
+        *sc.total2 = pre2;
+        *sc.total4 = pre4;
+      }
+    }
+  }
+}
+
+void launch_list_first(const ListLevelArgs& a, const ScanArgs& sc, hipStream_t s) {
+  hipLaunchKernelGGL(k_list_first, dim3(1), dim3(256), 0, s, a, sc);
+}
+
 void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, hipStream_t s) {
   if (a.n_recv_up == 0) return;  // with n_recv_up_dev: the capacity
   hipLaunchKernelGGL(k_list_count, dim3(div_up(a.n_recv_up, 8)), dim3(256), 0, s, a, cnt2, cnt4);
@@ -447,13 +566,19 @@ void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, h
 constexpr uint32_t kFillTwoPairs = 1u << 16;
 
 void launch_list_fill(const ListLevelArgs& a, const uint32_t* off2, const uint32_t* off4,
-                      uint32_t* ent2, uint32_t* ent4, hipStream_t s) {
+                      uint32_t* ent2, uint32_t* ent4, hipStream_t s, const ScanArgs& next,
+                      uint32_t* done) {
   if (a.n_recv_up == 0) return;
   // Two pairs of parents per wave once that still fills the chip's 8192 wave
   // slots twice; below, the level is one round of waves and takes as long as
   // one of them does.
   const bool two = a.n_recv_up >= kFillTwoPairs;
   const dim3 grid(div_up(a.n_recv_up, two ? 16 : 8));
+  if (done) {
+    hipLaunchKernelGGL(k_list_fill_scan, grid, dim3(256), 0, s, a, off2, off4, ent2, ent4, next,
+                       done);
+    return;
+  }
 #define FMMDS_FILL(N, B, P)                                                                      \
   hipLaunchKernelGGL((k_list_fill<N, B, P>), grid, dim3(256), 0, s, a, off2, off4, ent2, ent4)
 #define FMMDS_FILL_P(N, B)                                                                       \
@@ -489,16 +614,17 @@ constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanBlock * kScanItems;  // 16384 boxes
 
 __global__ __launch_bounds__(kScanBlock) void k_scan_counts2(
-    const uint32_t* __restrict__ cnt2, const uint32_t* __restrict__ cnt4, uint32_t n_host,
-    const uint32_t* __restrict__ n_dev, uint32_t* __restrict__ off2, uint32_t* __restrict__ off4,
-    uint64_t* __restrict__ total2, uint64_t* __restrict__ total4, uint32_t* __restrict__ overflow,
-    uint64_t* __restrict__ status2, uint64_t* __restrict__ status4,
+    ScanArgs sc, uint64_t* __restrict__ status2, uint64_t* __restrict__ status4,
     uint32_t* __restrict__ tile_counter) {
+  const uint32_t* __restrict__ cnt2 = sc.cnt2;
+  const uint32_t* __restrict__ cnt4 = sc.cnt4;
+  uint32_t* __restrict__ off2 = sc.off2;
+  uint32_t* __restrict__ off4 = sc.off4;
   __shared__ uint32_t s_w[2][kScanBlock / 64];
   __shared__ uint64_t s_excl[2];
   __shared__ uint32_t s_tile;
   const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const uint32_t n = n_dev ? *n_dev : n_host;
+  const uint32_t n = sc.n_dev ? *sc.n_dev : sc.n;
   if (tid == 0) s_tile = atomicAdd(tile_counter, 1u);
   __syncthreads();
   const uint32_t tile = s_tile;
@@ -568,8 +694,8 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_counts2(
     if (base + kScanItems == n) {
       off2[n] = (uint32_t)pre2;
       off4[n] = (uint32_t)pre4;
-      *total2 = pre2;
-      *total4 = pre4;
+      *sc.total2 = pre2;
+      *sc.total4 = pre4;
     }
   } else {
 #pragma unroll
@@ -582,26 +708,23 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_counts2(
         if (base + i + 1 == n) {
           off2[n] = (uint32_t)pre2;
           off4[n] = (uint32_t)pre4;
-          *total2 = pre2;
-          *total4 = pre4;
+          *sc.total2 = pre2;
+          *sc.total4 = pre4;
         }
       }
     }
   }
   ovf = (pre2 > 0xFFFFFFFFull) || (pre4 > 0xFFFFFFFFull);
-  if (ovf) atomicOr(overflow, 1u);
+  if (ovf) atomicOr(sc.overflow, 1u);
 }
 
 uint32_t scan_tiles(uint32_t n) { return div_up(n, kScanTile); }
 
-void launch_scan_counts2(const uint32_t* cnt2, const uint32_t* cnt4, uint32_t n, uint32_t* off2,
-                         uint32_t* off4, uint64_t* total2, uint64_t* total4, uint32_t* overflow,
-                         uint64_t* status2, uint64_t* status4, uint32_t* tile_counter,
-                         hipStream_t s, const uint32_t* n_dev) {
-  // n is the exact count, or with n_dev the capacity (the count is read there)
-  if (n == 0) return;
-  hipLaunchKernelGGL(k_scan_counts2, dim3(scan_tiles(n)), dim3(kScanBlock), 0, s, cnt2, cnt4, n,
-                     n_dev, off2, off4, total2, total4, overflow, status2, status4, tile_counter);
+void launch_scan_counts2(const ScanArgs& sc, uint64_t* status2, uint64_t* status4,
+                         uint32_t* tile_counter, hipStream_t s) {
+  if (sc.n == 0) return;
+  hipLaunchKernelGGL(k_scan_counts2, dim3(scan_tiles(sc.n)), dim3(kScanBlock), 0, s, sc, status2,
+                     status4, tile_counter);
 }
 
 }  // namespace fmmds

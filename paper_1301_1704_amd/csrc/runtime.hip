@@ -545,7 +545,13 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     const size_t meta_b = round_up(sizeof(DevMeta), 256);
     const size_t hist_b = round_up(2 * kMaxPasses * 256 * 4, 256);
     const size_t tick_b = round_up(tickets * 4, 256);
-    const size_t ws_b = round_up(meta_b + 2 * hist_b + tick_b + words * 8, 256);
+    // the lists' scans: their levels' boxes counted by capacity
+    const uint32_t n_rcv = sets[nsets - 1].n;
+    size_t lwords = 0;
+    for (uint32_t l = 2; l <= L; ++l) lwords += 2 * (size_t)scan_tiles(level_cap(n_rcv, l));
+    const size_t ltick_b = round_up(2 * (kMaxLevel + 1) * 4, 256);
+    const size_t sort_b = meta_b + 2 * hist_b + tick_b + words * 8;
+    const size_t ws_b = round_up(sort_b + ltick_b + lwords * 8, 256);
     char* ws = temps.get<char>(ws_b);
     DevMeta* meta = (DevMeta*)ws;
     uint32_t* hist = (uint32_t*)(ws + meta_b);
@@ -555,6 +561,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     sa.n_tickets = tickets;
     sa.words = (uint64_t*)(ws + meta_b + 2 * hist_b + tick_b);
     sa.n_words = words;
+    StatusArena la;
+    la.tickets = (uint32_t*)(ws + sort_b);
+    la.n_tickets = 2 * (kMaxLevel + 1);
+    la.words = (uint64_t*)(ws + sort_b + ltick_b);
+    la.n_words = lwords;
     P.run(K_ZERO, (double)ws_b, [&] { launch_zero(ws, ws_b, st); });
     const uint32_t n_max = std::max(sets[0].n, sets[nsets - 1].n);
     SortBufs sb{};
@@ -695,10 +706,12 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         q += sets[s].lv[l].cap;
       }
     }
+    const bool plain = !dense && !prev;
+    auto sort_small = [&](int s) { return plain && packed && sets[s].n <= kSortSmall; };
     // keygen's per-block digit-count rows, per set
     uint32_t* krows[2] = {nullptr, nullptr};
     for (int s = 0; s < nsets; ++s)
-      krows[s] = temps.get<uint32_t>((size_t)keygen_blocks(sets[s].n) * n_pass * 256);
+      if (!sort_small(s)) krows[s] = temps.get<uint32_t>((size_t)keygen_blocks(sets[s].n) * n_pass * 256);
     // every level's tables in one pass (not the dense variant): per set the
     // per-tile box-start counts of every level and their scan
     uint32_t* tabbuf[2] = {nullptr, nullptr};
@@ -727,7 +740,6 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
 
     // Plain builds: both chains' key generation is enqueued first, so that
     // the receivers' chain starts while the host enqueues the rest.
-    const bool plain = !dense && !prev;
     for (int s = 0; plain && s < nsets; ++s) {
       const hipStream_t st = s == 1 ? st1 : impl->A.stream;
       P.s = st;
@@ -735,13 +747,18 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       const uint32_t n = sets[s].n;
       uint32_t* h = hist + s * kMaxPasses * 256;
       uint32_t* g = goff + s * kMaxPasses * 256;
+      if (sort_small(s)) {  // keys and the whole sort at once
+        P.run(K_SORT, (double)n * (12 + 8), [&] {
+          launch_sort_small(sets[s].xyz, n, L, n_pass, sb.k[0], &meta->err_range, st);
+        });
+        continue;
+      }
       P.run(K_KEYGEN, (double)n * (packed ? 12 + 8 : 12 + 8 + 4), [&] {
         launch_keygen(sets[s].xyz, n, L, packed, sb.k[0], sb.v[0], n_pass, krows[s],
                       &meta->err_range, st);
       });
       P.run(K_DIGITS, (double)keygen_blocks(n) * n_pass * 1024, [&] {
-        launch_reduce_rows(krows[s], keygen_blocks(n), h, n_pass, st);
-        launch_digit_offsets(h, g, n_pass, st);
+        launch_digits(krows[s], keygen_blocks(n), h, g, n_pass, st);
       });
     }
 
@@ -832,11 +849,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
                           &meta->err_range, st);
           });
           P.run(K_DIGITS, (double)keygen_blocks(n) * n_pass * 1024, [&] {
-            launch_reduce_rows(krows[s], keygen_blocks(n), h, n_pass, st);
-            launch_digit_offsets(h, g, n_pass, st);
+            launch_digits(krows[s], keygen_blocks(n), h, g, n_pass, st);
           });
         }
-        for (uint32_t p = 0; p < n_pass; ++p) {
+        const uint32_t n_left = sort_small(s) ? 0 : n_pass;
+        for (uint32_t p = 0; p < n_left; ++p) {
           const int a = p & 1, b = a ^ 1;
           const uint32_t shift = (packed ? 32 : 0) + 8 * p;
           uint64_t* stw =
@@ -847,7 +864,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
                              stw, tk, st, packed ? kSortWide : kSortItemsDefault);
           });
         }
-        const int fin = n_pass & 1;
+        const int fin = n_left & 1;
         fin_k = sb.k[fin];
         fin_v = sb.v[fin];
       }
@@ -955,8 +972,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
                       st);
       });
       P.run(K_DIGITS, 0.0, [&] {
-        launch_reduce_rows(krows[s], keygen_blocks(n), h, n_pass, st);
-        launch_digit_offsets(h, g, n_pass, st);
+        launch_digits(krows[s], keygen_blocks(n), h, g, n_pass, st);
       });
       for (uint32_t p = 0; p < n_pass; ++p) {
         const int a = p & 1, b = a ^ 1;
@@ -977,20 +993,8 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     }
 
     // ---- lists, levels 2..D
-    size_t lwords = 0, lmax = 0;
-    for (uint32_t l = 2; l <= D; ++l) {
-      lwords += 2 * (size_t)scan_tiles(lcap[rs][l]);
-      lmax = std::max<size_t>(lmax, lcap[rs][l]);
-    }
-    const size_t ltick_b = round_up(2 * (kMaxLevel + 1) * 4, 256);
-    const size_t lws_b = round_up(ltick_b + lwords * 8, 256);
-    char* lws = temps.get<char>(lws_b);
-    StatusArena la;
-    la.tickets = (uint32_t*)lws;
-    la.n_tickets = 2 * (kMaxLevel + 1);
-    la.words = (uint64_t*)(lws + ltick_b);
-    la.n_words = lwords;
-    P.run(K_ZERO, (double)lws_b, [&] { launch_zero(lws, lws_b, st); });
+    size_t lmax = 0;
+    for (uint32_t l = 2; l <= D; ++l) lmax = std::max<size_t>(lmax, lcap[rs][l]);
     // E2 counts, then E4 counts from a 16-byte aligned start (vector loads)
     uint32_t* cnt = temps.get<uint32_t>(2 * round_up(std::max<size_t>(lmax, 1), 4));
     // Levels with at most a quarter of the finest level's receiver boxes get
@@ -1019,6 +1023,14 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       uint32_t* q = (uint32_t*)lblock;
       lblock += round_up(count * 4, 256);
       return q;
+    };
+    for (uint32_t l = 2; l <= D; ++l)
+      for (int k = 0; k < 2; ++k) impl->lists[l].off[k] = carve((size_t)lcap[rs][l] + 1);
+    auto scan_args = [&](uint32_t l) {
+      const uint32_t nr = lcap[rs][l];
+      return ScanArgs{cnt, cnt + round_up(nr, 4), nr, early ? &meta->n_boxes[rs][l] : nullptr,
+                      impl->lists[l].off[0], impl->lists[l].off[1], &meta->list_total[0][l],
+                      &meta->list_total[1][l], &meta->overflow};
     };
     for (uint32_t l = 2; l <= D; ++l) {
       const uint32_t nr = lcap[rs][l];
@@ -1049,19 +1061,13 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
                              nullptr, nullptr, nullptr, st);
         });
       else if (l == 2)
-        P.run(K_COUNT, 0.0, [&] { launch_list_count(a, cnt, cnt + round_up(nr, 4), st); },
-              kListSet, (int)l);
-      LB.off[0] = carve((size_t)nr + 1);
-      LB.off[1] = carve((size_t)nr + 1);
-      {
+        P.run(K_COUNT, 0.0, [&] { launch_list_first(a, scan_args(l), st); }, kListSet, (int)l);
+      if (dense || (l > 2 && nr > kScanSmall)) {
         uint64_t* st2 = la.take_words(scan_tiles(nr));
         uint64_t* st4 = la.take_words(scan_tiles(nr));
         uint32_t* tk = la.take_ticket();
-        P.run(K_SCAN, 0.0, [&] {
-          launch_scan_counts2(cnt, cnt + round_up(nr, 4), nr, LB.off[0], LB.off[1], &meta->list_total[0][l],
-                              &meta->list_total[1][l], &meta->overflow, st2, st4, tk, st,
-                              early ? &meta->n_boxes[rs][l] : nullptr);
-        }, kListSet, (int)l);
+        P.run(K_SCAN, 0.0, [&] { launch_scan_counts2(scan_args(l), st2, st4, tk, st); }, kListSet,
+              (int)l);
       }
       if (small_level(l)) {
         for (int k = 0; k < 2; ++k) LB.ent[k] = carve((size_t)nr * (k == 0 ? 27 : 189));
@@ -1084,14 +1090,18 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         });
         continue;
       }
-      if (l < D) {  // the next level's counts
+      ScanArgs next{};
+      uint32_t* done = nullptr;
+      if (l < D) {  // the next level's counts, and where they are few their scan
+        next = scan_args(l + 1);
         a.recv_node_cur = sets[rs].lv[l].node;
         a.cnt2_next = cnt;
         a.cnt4_next = cnt + round_up(lcap[rs][l + 1], 4);
+        if (lcap[rs][l + 1] <= kScanSmall) done = la.take_ticket();
       }
-      P.run(K_FILL, 0.0,
-            [&] { launch_list_fill(a, LB.off[0], LB.off[1], LB.ent[0], LB.ent[1], st); },
-            kListSet, (int)l);
+      P.run(K_FILL, 0.0, [&] {
+        launch_list_fill(a, LB.off[0], LB.off[1], LB.ent[0], LB.ent[1], st, next, done);
+      }, kListSet, (int)l);
     }
     for (uint32_t l = 2; l <= D; ++l) impl->n_recv_boxes[l] = nb[rs][l];
 
@@ -1382,9 +1392,9 @@ void batch_enqueue(BatchImpl& B, const float* xyz, Prof& P) {
       uint64_t* st4 = sa.take_words(scan_tiles(B.cap[l]));
       uint32_t* tk = sa.take_ticket();
       P.run(K_SCAN, 0.0, [&] {
-        launch_scan_counts2(c2, c4, B.cap[l], B.goff[l][0], B.goff[l][1], &meta->list_total[0][l],
-                            &meta->list_total[1][l], &meta->overflow, st2, st4, tk, st,
-                            &meta->n_boxes[0][l]);
+        launch_scan_counts2({c2, c4, B.cap[l], &meta->n_boxes[0][l], B.goff[l][0], B.goff[l][1],
+                             &meta->list_total[0][l], &meta->list_total[1][l], &meta->overflow},
+                            st2, st4, tk, st);
       });
     }
     if (l < L) {  // the next level's counts (batch ranks; sets ending at l get zeros)

@@ -152,6 +152,37 @@ void launch_digit_offsets(const uint32_t* hist, uint32_t* goff, uint32_t n_pass,
   hipLaunchKernelGGL(k_digit_offsets, dim3(n_pass), dim3(256), 0, s, hist, goff);
 }
 
+// The same from keygen's rows where there are few of them: block p adds pass p's
+// rows and scans the sums (one launch less; 2048 points a row, so up to 131072).
+__global__ __launch_bounds__(256) void k_digit_offsets_rows(const uint32_t* __restrict__ rows,
+                                                            uint32_t n_rows, uint32_t n_pass,
+                                                            uint32_t* __restrict__ goff) {
+  __shared__ uint32_t s_w[4];
+  const uint32_t p = blockIdx.x, d = threadIdx.x, lane = d & 63, w = d >> 6;
+  uint32_t c = 0;
+#pragma unroll 8
+  for (uint32_t r = 0; r < n_rows; ++r) c += rows[((uint64_t)r * n_pass + p) * 256 + d];
+  const uint32_t inc = wave_incl_scan(c);
+  if (lane == 63) s_w[w] = inc;
+  __syncthreads();
+  uint32_t base = 0;
+  for (uint32_t i = 0; i < w; ++i) base += s_w[i];
+  goff[p * 256 + d] = base + inc - c;
+}
+
+constexpr uint32_t kDigitRows = 64;
+
+void launch_digits(const uint32_t* rows, uint32_t n_rows, uint32_t* hist, uint32_t* goff,
+                   uint32_t n_pass, hipStream_t s) {
+  if (n_rows <= kDigitRows) {
+    hipLaunchKernelGGL(k_digit_offsets_rows, dim3(n_pass), dim3(256), 0, s, rows, n_rows, n_pass,
+                       goff);
+  } else {
+    launch_reduce_rows(rows, n_rows, hist, n_pass, s);
+    launch_digit_offsets(hist, goff, n_pass, s);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // K2: one stable LSD pass on the 8-bit digit at `shift`.
 //
@@ -175,6 +206,37 @@ template <bool PACKED>
 __device__ __forceinline__ uint32_t sort_digit(uint64_t k, uint32_t shift) {
   return PACKED ? __builtin_amdgcn_ubfe((uint32_t)(k >> 32), shift - 32u, 8u)
                 : (uint32_t)(k >> shift) & 0xFFu;
+}
+
+// Ranks of a wave's items (64 of each i, in order) by the digit at `shift` within
+// the wave's own items: item i of this lane is valid while 64 i + lane < lim;
+// `hist` (256 words, zeroed) ends with the wave's digit counts.
+template <bool PACKED, int ITEMS>
+__device__ __forceinline__ void sort_rank(const uint64_t (&k)[ITEMS], uint32_t shift, uint32_t lim,
+                                          uint32_t lane, uint32_t* hist, uint32_t (&r)[ITEMS]) {
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const bool valid = 64u * i + lane < lim;
+    const uint32_t d = sort_digit<PACKED>(k[i], shift);
+    // peers: the valid lanes whose digit equals this lane's. Per bit b, m is
+    // all ones where this lane's bit is 0, so that (ballot ^ m) keeps the
+    // lanes that agree with it on bit b (one three-input bit op per half).
+    const uint64_t vb = __ballot(valid);
+    uint32_t plo = (uint32_t)vb, phi = (uint32_t)(vb >> 32);
+    const uint32_t nd = ~d;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)nd, b, 1);
+      const uint64_t bal = __ballot(m == 0u);
+      plo &= (uint32_t)bal ^ m;
+      phi &= (uint32_t)(bal >> 32) ^ m;
+    }
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+    uint32_t prev = 0;
+    if (valid) prev = hist[d];
+    r[i] = prev + below;
+    if (valid && below == 0) hist[d] = prev + (uint32_t)(__popc(plo) + __popc(phi));
+  }
 }
 
 // With SEG, tiles come from a set-aligned table (SegSort): each tile lies in
@@ -249,29 +311,7 @@ __global__ __launch_bounds__(BLOCK) void k_sort_pass(
     const uint64_t agg = s_cnt[tid];
     st_status(status + (uint64_t)tile * 256 + tid, (first ? kStInc : kStAgg) | agg);
   }
-#pragma unroll
-  for (int i = 0; i < ITEMS; ++i) {
-    const bool valid = 64u * i + lane < lim;
-    const uint32_t d = sort_digit<PACKED>(k[i], shift);
-    // peers: the valid lanes whose digit equals this lane's. Per bit b, m is
-    // all ones where this lane's bit is 0, so that (ballot ^ m) keeps the
-    // lanes that agree with it on bit b (one three-input bit op per half).
-    const uint64_t vb = __ballot(valid);
-    uint32_t plo = (uint32_t)vb, phi = (uint32_t)(vb >> 32);
-    const uint32_t nd = ~d;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)nd, b, 1);
-      const uint64_t bal = __ballot(m == 0u);
-      plo &= (uint32_t)bal ^ m;
-      phi &= (uint32_t)(bal >> 32) ^ m;
-    }
-    const uint32_t below = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
-    uint32_t prev = 0;
-    if (valid) prev = s_hist[w][d];
-    r[i] = prev + below;
-    if (valid && below == 0) s_hist[w][d] = prev + (uint32_t)(__popc(plo) + __popc(phi));
-  }
+  sort_rank<PACKED, ITEMS>(k, shift, lim, lane, s_hist[w], r);
   __syncthreads();
 
   // Thread d < 256 owns digit d: wave-exclusive prefixes, tile count, local
@@ -319,6 +359,96 @@ __global__ __launch_bounds__(BLOCK) void k_sort_pass(
     kout[g] = kk;
     if (!PACKED) vout[g] = s_val[j];
   }
+}
+
+// ---------------------------------------------------------------------------
+// Small sets: keys and every pass in one block, which keeps its elements in
+// registers and turns them over in LDS between the passes. Key generation, the
+// digit counts (two launches) and each pass are launches of their own otherwise,
+// a few us apiece whatever their size: 4097 points at level 3 (two passes) took
+// 28 us of kernels and four gaps of about 4 us, and take 15 us here. What bounds
+// it is the serial chain of each wave's ranks, so that the time grows with the
+// items a wave holds; larger sets spread over blocks.
+// ---------------------------------------------------------------------------
+template <int BLOCK, int ITEMS>
+__global__ __launch_bounds__(BLOCK) void k_sort_small(const P3* __restrict__ xyz, uint32_t n,
+                                                    uint32_t L, uint32_t n_pass,
+                                                    uint64_t* __restrict__ out,
+                                                    uint32_t* __restrict__ err) {
+  constexpr int W = BLOCK / 64;
+  constexpr uint32_t WSEG = 64 * ITEMS;
+  __shared__ uint64_t s_key[BLOCK * ITEMS];
+  __shared__ uint32_t s_hist[W][256];
+  __shared__ uint32_t s_lstart[256];
+  __shared__ uint32_t s_scan[4];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint32_t wbase = w * WSEG;
+  const uint32_t lim = n > wbase ? min(WSEG, n - wbase) : 0u;
+  uint64_t k[ITEMS];
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const uint32_t j = 64u * i + lane;
+    k[i] = 0;
+    if (j < lim) {
+      const P3 p = xyz[wbase + j];
+      bool ok;
+      k[i] = point_key(p.x, p.y, p.z, L, ok) << 32 | (wbase + j);
+      bad |= !ok;
+    }
+  }
+  if (bad) atomicOr(err, 1u);
+  for (uint32_t p = 0; p < n_pass; ++p) {
+    const uint32_t shift = 32 + 8 * p;
+    for (uint32_t i = tid; i < W * 256; i += BLOCK) (&s_hist[0][0])[i] = 0;
+    __syncthreads();
+    uint32_t r[ITEMS];
+    sort_rank<true, ITEMS>(k, shift, lim, lane, s_hist[w], r);
+    __syncthreads();
+    uint32_t cnt = 0, inc = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int ww = 0; ww < W; ++ww) {
+        const uint32_t c = s_hist[ww][tid];
+        s_hist[ww][tid] = cnt;
+        cnt += c;
+      }
+      inc = wave_incl_scan(cnt);
+      if (lane == 63) s_scan[w] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t wpre = 0;
+      for (uint32_t ww = 0; ww < w; ++ww) wpre += s_scan[ww];
+      s_lstart[tid] = wpre + inc - cnt;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (64u * i + lane < lim) {
+        const uint32_t d = sort_digit<true>(k[i], shift);
+        s_key[s_lstart[d] + s_hist[w][d] + r[i]] = k[i];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i)
+      if (64u * i + lane < lim) k[i] = s_key[wbase + 64u * i + lane];
+    // (the next pass writes s_key after two more barriers)
+  }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i)
+    if (64u * i + lane < lim) out[wbase + 64u * i + lane] = k[i];
+}
+
+void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass, uint64_t* out,
+                       uint32_t* err, hipStream_t s) {
+#define FMMDS_SMALL(B, I)                                                                        \
+  hipLaunchKernelGGL((k_sort_small<B, I>), dim3(1), dim3(B), 0, s, (const P3*)xyz, n, L, n_pass, \
+                     out, err)
+  if (n <= 2048) FMMDS_SMALL(512, 4);
+  else if (n <= 4096) FMMDS_SMALL(1024, 4);
+  else FMMDS_SMALL(1024, 8);
+#undef FMMDS_SMALL
 }
 
 uint32_t sort_tile_elems(int items) { return items == kSortWide ? 8192u : 256u * (uint32_t)items; }

@@ -207,7 +207,8 @@ __global__ __launch_bounds__(kTabScanBlock) void k_tab_scan(const uint32_t* __re
 template <bool PACKED, typename KeyT>
 __global__ __launch_bounds__(kCompBlock) void k_tab_write(
     const uint64_t* __restrict__ sk, const uint32_t* __restrict__ sv, const P3* __restrict__ xyz,
-    uint32_t n, uint32_t L, uint32_t tiles, const uint32_t* __restrict__ pre, TabLevels T,
+    uint32_t n, uint32_t L, uint32_t tiles, const uint32_t* __restrict__ cnt,
+    const uint32_t* __restrict__ pre, uint32_t* __restrict__ n_boxes, TabLevels T,
     uint32_t* __restrict__ perm, P3* __restrict__ sorted_xyz,
     const uint64_t* __restrict__ set_off, uint32_t set_shift) {
   constexpr int NSLOT = kCompItems * kCompWaves;
@@ -248,7 +249,15 @@ __global__ __launch_bounds__(kCompBlock) void k_tab_write(
   for (uint32_t l = w; l <= L; l += kCompWaves) {
     const uint32_t v = lane < NSLOT ? s_c[l][lane] : 0u;
     const uint32_t inc = wave_incl_scan(v);
-    if (lane < NSLOT) s_c[l][lane] = pre[(uint64_t)l * tiles + tile] + inc - v;
+    uint32_t before;
+    if (pre) {
+      before = pre[(uint64_t)l * tiles + tile];
+    } else {  // at most 64 tiles: the scan of their counts is one load a lane
+      const uint32_t c = lane < tile ? cnt[l * tiles + lane] : 0u;
+      before = (uint32_t)__shfl((int)wave_incl_scan(c), 63, 64);
+      if (tile + 1 == tiles && lane == 63) n_boxes[l] = before + inc;
+    }
+    if (lane < NSLOT) s_c[l][lane] = before + inc - v;
   }
   __syncthreads();
 #pragma unroll
@@ -344,12 +353,13 @@ void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* 
     else
       hipLaunchKernelGGL(k_tab_count<false>, dim3(tiles), dim3(kCompBlock), 0, s, sk, n, L, tiles, cnt);
   } else if (phase == 1) {
-    hipLaunchKernelGGL(k_tab_scan, dim3(L + 1), dim3(kTabScanBlock), 0, s, cnt, tiles, pre, n_boxes);
+    if (tiles > kTabSmallTiles)
+      hipLaunchKernelGGL(k_tab_scan, dim3(L + 1), dim3(kTabScanBlock), 0, s, cnt, tiles, pre, n_boxes);
   } else if (phase == 2) {
 #define FMMDS_TABW(P, K)                                                                         \
   hipLaunchKernelGGL((k_tab_write<P, K>), dim3(tiles), dim3(kCompBlock), 0, s, sk, sv,            \
-                     (const P3*)xyz, n, L, tiles, pre, T, perm, (P3*)sorted_xyz, set_off,  \
-                     set_shift)
+                     (const P3*)xyz, n, L, tiles, cnt, tiles > kTabSmallTiles ? pre : nullptr,  \
+                     n_boxes, T, perm, (P3*)sorted_xyz, set_off, set_shift)
     if (packed && key64) FMMDS_TABW(true, uint64_t);
     else if (packed) FMMDS_TABW(true, uint32_t);
     else if (key64) FMMDS_TABW(false, uint64_t);
