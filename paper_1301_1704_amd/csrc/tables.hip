@@ -125,8 +125,29 @@ __device__ __forceinline__ uint32_t new_box_level(uint64_t k, uint64_t kp, uint3
 }
 
 template <bool PACKED>
-__device__ __forceinline__ uint64_t elem_key(const uint64_t* __restrict__ sk, uint64_t e) {
-  return PACKED ? (sk[e] >> 32) : sk[e];
+__device__ __forceinline__ uint64_t elem_key(uint64_t el) {
+  return PACKED ? (el >> 32) : el;
+}
+
+// A thread's elements of a tile and the ones before them, all loaded at once:
+// without a branch around any (points past the end repeat the last one), since
+// a branch waits for its loads.
+template <bool PACKED, int ITEMS>
+__device__ __forceinline__ void load_keys(const uint64_t* __restrict__ sk, uint32_t n,
+                                          uint64_t first, uint64_t (&el)[ITEMS],
+                                          uint64_t (&prev)[ITEMS]) {
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const uint64_t e = min(first + (uint64_t)i * (kCompTile / ITEMS), (uint64_t)n - 1);
+    el[i] = sk[e];
+    prev[i] = sk[e - (e ? 1u : 0u)];
+  }
+}
+// d(e), with no new box past the end.
+__device__ __forceinline__ uint32_t first_level(uint64_t e, uint32_t n, uint64_t k, uint64_t kp,
+                                                uint32_t L) {
+  const uint32_t d = e == 0 ? 0u : new_box_level(k, kp, L);
+  return e < n ? d : L + 1;
 }
 
 template <bool PACKED>
@@ -136,13 +157,13 @@ __global__ __launch_bounds__(kCompBlock) void k_tab_count(const uint64_t* __rest
   __shared__ uint32_t s_c[kMaxLevel + 1][kCompWaves];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
   const uint64_t tbase = (uint64_t)blockIdx.x * kCompTile;
+  uint64_t key[kCompItems], kp[kCompItems];
+  load_keys<PACKED, kCompItems>(sk, n, tbase + tid, key, kp);
   uint32_t d[kCompItems];
 #pragma unroll
-  for (int i = 0; i < kCompItems; ++i) {
-    const uint64_t e = tbase + (uint64_t)i * kCompBlock + tid;
-    d[i] = L + 1;
-    if (e < n) d[i] = e == 0 ? 0u : new_box_level(elem_key<PACKED>(sk, e), elem_key<PACKED>(sk, e - 1), L);
-  }
+  for (int i = 0; i < kCompItems; ++i)
+    d[i] = first_level(tbase + (uint64_t)i * kCompBlock + tid, n, elem_key<PACKED>(key[i]),
+                       elem_key<PACKED>(kp[i]), L);
   for (uint32_t l = 0; l <= L; ++l) {
     uint32_t c = 0;
 #pragma unroll
@@ -204,14 +225,28 @@ __global__ __launch_bounds__(kTabScanBlock) void k_tab_scan(const uint32_t* __re
 // `set_shift` up and the permutation is written relative to the set's first
 // point; a set boundary differs in those bits, so it starts a box at every
 // level.
-template <bool PACKED, typename KeyT>
-__global__ __launch_bounds__(kCompBlock) void k_tab_write(
+//
+// GATHER: the coordinates follow (else they are already in place).
+//
+// A tile of 2048 points is 2 items a thread of 1024, or 4 of 512. Few tiles (one
+// round of blocks on the chip's 256 CUs, two a CU): what bounds the kernel is
+// one wave's serial chain over its items and levels, so the fewer items the
+// better. 4097 points at level 3: 12.4 us with 8 items a thread, 9.2 with 4, 7.7
+// with 2; 65536 at level 5: 16.3, 11.3, 9.3; two sets of 1M and 0.7M: 53, 48, 43
+// together. Many tiles: the gather of the coordinates (12 random bytes a point,
+// a whole line fetched each) bounds it, and blocks that start and end together
+// hinder each other: a batch of 512 sets 1063 us with 8 items, 1021 with 4, 1057
+// with 2; two sets of 2^24 914, 902, 896; where nothing is gathered 280, 276,
+// 316.
+constexpr uint32_t kTabWideTiles = 512;
+template <bool PACKED, typename KeyT, bool GATHER, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_tab_write(
     const uint64_t* __restrict__ sk, const uint32_t* __restrict__ sv, const P3* __restrict__ xyz,
     uint32_t n, uint32_t L, uint32_t tiles, const uint32_t* __restrict__ cnt,
     const uint32_t* __restrict__ pre, uint32_t* __restrict__ n_boxes, TabLevels T,
     uint32_t* __restrict__ perm, P3* __restrict__ sorted_xyz,
     const uint64_t* __restrict__ set_off, uint32_t set_shift) {
-  constexpr int NSLOT = kCompItems * kCompWaves;
+  constexpr int ITEMS = kCompTile / BLOCK, WAVES = BLOCK / 64, NSLOT = ITEMS * WAVES;
   __shared__ uint32_t s_c[kMaxLevel + 1][NSLOT];
   const uint32_t tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
   // Consecutive tiles on one XCD: with a batch each set's coordinate gather
@@ -219,34 +254,41 @@ __global__ __launch_bounds__(kCompBlock) void k_tab_write(
   // 512 sets); a single set's gather is random over all of it either way.
   const uint32_t tile = xcd_block(blockIdx.x, gridDim.x);
   const uint64_t tbase = (uint64_t)tile * kCompTile;
-  uint64_t key[kCompItems];
-  uint32_t d[kCompItems];
+  uint64_t key[ITEMS], kp[ITEMS];
+  uint32_t d[ITEMS], idx[ITEMS];
+  float x[ITEMS], y[ITEMS], z[ITEMS];
+  load_keys<PACKED, ITEMS>(sk, n, tbase + tid, key, kp);
 #pragma unroll
-  for (int i = 0; i < kCompItems; ++i) {
-    const uint64_t e = tbase + (uint64_t)i * kCompBlock + tid;
-    d[i] = L + 1;
-    key[i] = 0;
-    if (e < n) {
-      const uint64_t el = sk[e];
-      key[i] = PACKED ? (el >> 32) : el;
-      d[i] = e == 0 ? 0u : new_box_level(key[i], elem_key<PACKED>(sk, e - 1), L);
-      const uint32_t idx = PACKED ? (uint32_t)el : sv[e];
-      perm[e] = set_off ? idx - (uint32_t)set_off[key[i] >> set_shift] : idx;
-      if (xyz) sorted_xyz[e] = xyz[idx];  // null: the coordinates are already in place
+  for (int i = 0; i < ITEMS; ++i) {
+    const uint64_t e = tbase + (uint64_t)i * BLOCK + tid;
+    idx[i] = PACKED ? (uint32_t)key[i] : sv[min(e, (uint64_t)n - 1)];
+    key[i] = elem_key<PACKED>(key[i]);
+    d[i] = first_level(e, n, key[i], elem_key<PACKED>(kp[i]), L);
+  }
+  // (all in flight while the box starts are counted)
+  if (GATHER) {
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const P3 p = xyz[idx[i]];
+      x[i] = p.x, y[i] = p.y, z[i] = p.z;
     }
+  }
+  if (set_off) {
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) idx[i] -= (uint32_t)set_off[key[i] >> set_shift];
   }
   // per level and (item, wave) slot: the number of box starts
   for (uint32_t l = 0; l <= L; ++l) {
 #pragma unroll
-    for (int i = 0; i < kCompItems; ++i) {
+    for (int i = 0; i < ITEMS; ++i) {
       const uint64_t b = __ballot(d[i] <= l);
-      if (lane == 0) s_c[l][i * kCompWaves + w] = (uint32_t)__popcll(b);
+      if (lane == 0) s_c[l][i * WAVES + w] = (uint32_t)__popcll(b);
     }
   }
   __syncthreads();
   // slots in point order (item, then wave): exclusive prefixes plus the tile's
   // prefix from the scan, one level per wave at a time
-  for (uint32_t l = w; l <= L; l += kCompWaves) {
+  for (uint32_t l = w; l <= L; l += WAVES) {
     const uint32_t v = lane < NSLOT ? s_c[l][lane] : 0u;
     const uint32_t inc = wave_incl_scan(v);
     uint32_t before;
@@ -259,11 +301,19 @@ __global__ __launch_bounds__(kCompBlock) void k_tab_write(
     }
     if (lane < NSLOT) s_c[l][lane] = before + inc - v;
   }
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) {
+    const uint64_t e = tbase + (uint64_t)i * BLOCK + tid;
+    if (e < n) {
+      perm[e] = idx[i];
+      if (GATHER) sorted_xyz[e] = P3{x[i], y[i], z[i]};
+    }
+  }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < kCompItems; ++i) {
-    const uint64_t e = tbase + (uint64_t)i * kCompBlock + tid;
-    const uint32_t slot = i * kCompWaves + w;
+  for (int i = 0; i < ITEMS; ++i) {
+    const uint64_t e = tbase + (uint64_t)i * BLOCK + tid;
+    const uint32_t slot = i * WAVES + w;
     // inclusive count of box starts up to this point: at level l - 1 (prev),
     // l (cur) and l + 1 (next)
     auto incl = [&](uint32_t l) {
@@ -356,15 +406,22 @@ void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* 
     if (tiles > kTabSmallTiles)
       hipLaunchKernelGGL(k_tab_scan, dim3(L + 1), dim3(kTabScanBlock), 0, s, cnt, tiles, pre, n_boxes);
   } else if (phase == 2) {
+#define FMMDS_TABWB(P, K, B)                                                                     \
+  hipLaunchKernelGGL((xyz ? k_tab_write<P, K, true, B> : k_tab_write<P, K, false, B>),           \
+                     dim3(tiles), dim3(B), 0, s, sk, sv, (const P3*)xyz, n, L, tiles, cnt,       \
+                     tiles > kTabSmallTiles ? pre : nullptr, n_boxes, T, perm, (P3*)sorted_xyz,  \
+                     set_off, set_shift)
 #define FMMDS_TABW(P, K)                                                                         \
-  hipLaunchKernelGGL((k_tab_write<P, K>), dim3(tiles), dim3(kCompBlock), 0, s, sk, sv,            \
-                     (const P3*)xyz, n, L, tiles, cnt, tiles > kTabSmallTiles ? pre : nullptr,  \
-                     n_boxes, T, perm, (P3*)sorted_xyz, set_off, set_shift)
+  do {                                                                                           \
+    if (tiles <= kTabWideTiles) FMMDS_TABWB(P, K, 1024);                                         \
+    else FMMDS_TABWB(P, K, 512);                                                                 \
+  } while (0)
     if (packed && key64) FMMDS_TABW(true, uint64_t);
     else if (packed) FMMDS_TABW(true, uint32_t);
     else if (key64) FMMDS_TABW(false, uint64_t);
     else FMMDS_TABW(false, uint32_t);
 #undef FMMDS_TABW
+#undef FMMDS_TABWB
   } else if (L >= 2) {
     const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(div_up(node_cap, 32), 2048)), L - 1);
     if (key64) hipLaunchKernelGGL(k_tab_nodes<uint64_t>, grid, dim3(256), 0, s, T, n_boxes);
