@@ -34,6 +34,15 @@ struct DevMeta {
   uint64_t list_total[2][kMaxLevel + 1];  // [0] = E2, [1] = E4
   uint32_t inc_counts[2][2];              // incremental rebuild: stayers, movers per set
   uint32_t dense_big[2];                  // dense variant: finest boxes ordered by blocks
+  uint32_t published;                     // host copy only: the level whose scan wrote it
+};
+// Where a scan leaves the metadata block for the host, which waits for
+// `published` to be the scan's level (to: pinned memory, null: nowhere). The
+// totals of that level are the scan's own.
+struct Publish {
+  DevMeta* to;
+  const DevMeta* meta;
+  uint32_t level;
 };
 
 // Sort elements: with `packed`, one uint64 holding (key << 32 | index) for keys
@@ -154,6 +163,7 @@ struct ScanArgs {
   uint64_t* total2;
   uint64_t* total4;
   uint32_t* overflow;
+  Publish pub;
 };
 void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, hipStream_t s);
 // Level 2 of a plain build (at most 8 parents and 64 boxes): counts and offsets.

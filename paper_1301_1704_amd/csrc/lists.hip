@@ -18,6 +18,8 @@
 //   d = 0: always;  d = +1: child bit 0 and r bit 1;  d = -1: child bit 1 and
 //   r bit 0;
 // giving an 8-bit mask over the child octants.
+#include <cstddef>
+
 #include "device.h"
 #include "internal.h"
 
@@ -153,22 +155,52 @@ __global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* _
                  threadIdx.x & 31u, cnt2, cnt4);
 }
 
+// One wave copies the metadata block to the host's pinned memory and then sets
+// `published`: the host, which polls it, reads the totals some 20 us earlier
+// than after a copy command and a stream synchronization. Every word is stored
+// past the caches and waited for (vmcnt 0) before the flag is.
+__device__ __forceinline__ void publish_meta(const Publish& pub, uint64_t total2, uint64_t total4,
+                                             uint32_t lane) {
+  auto put = [](uint32_t* at, uint32_t v) {
+    __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
+  const uint32_t* from = (const uint32_t*)pub.meta;
+  uint32_t* to = (uint32_t*)pub.to;
+  for (uint32_t i = lane; i < offsetof(DevMeta, published) / 4; i += 64) put(to + i, from[i]);
+  __builtin_amdgcn_s_waitcnt(0);
+  if (lane < 2) {
+    const uint64_t t = lane ? total4 : total2;
+    uint32_t* at = (uint32_t*)&pub.to->list_total[lane][pub.level];
+    put(at, (uint32_t)t);
+    put(at + 1, (uint32_t)(t >> 32));
+  } else if (lane == 2 && (total2 > 0xFFFFFFFFull || total4 > 0xFFFFFFFFull)) {
+    put(&pub.to->overflow, 1u);
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) put(&pub.to->published, pub.level);
+}
+
 // A plain build's level 2 (at most 8 parents, 64 boxes): the counts and their
 // offsets in one block, one launch (5 us) less than with the general scan.
 __global__ __launch_bounds__(256) void k_list_first(ListLevelArgs a, ScanArgs sc) {
-  __shared__ uint32_t s_cnt[2][64];
+  __shared__ uint32_t s_cnt[2][64], s_tot[2];
   const uint32_t n = sc.n_dev ? *sc.n_dev : sc.n, lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
   count_children(a, threadIdx.x >> 5, threadIdx.x & 31u, s_cnt[0], s_cnt[1]);
   __syncthreads();
-  if (w > 1) return;
-  const uint32_t v = lane < n ? s_cnt[w][lane] : 0u;
-  const uint32_t inc = wave_incl_scan(v);
-  uint32_t* off = w ? sc.off4 : sc.off2;
-  if (lane < n) off[lane] = inc - v;
-  if (lane == 63) {  // (64 boxes of at most 64 entries: no overflow)
-    off[n] = inc;
-    *(w ? sc.total4 : sc.total2) = inc;
+  if (w < 2) {
+    const uint32_t v = lane < n ? s_cnt[w][lane] : 0u;
+    const uint32_t inc = wave_incl_scan(v);
+    uint32_t* off = w ? sc.off4 : sc.off2;
+    if (lane < n) off[lane] = inc - v;
+    if (lane == 63) {  // (64 boxes of at most 64 entries: no overflow)
+      off[n] = inc;
+      *(w ? sc.total4 : sc.total2) = inc;
+      s_tot[w] = inc;
+    }
   }
+  __syncthreads();
+  if (sc.pub.to && w == 0) publish_meta(sc.pub, s_tot[0], s_tot[1], lane);
 }
 
 // LDS written by other lanes of this wave is read after this point (and the
@@ -497,7 +529,7 @@ __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
                                                            ScanArgs sc,
                                                            uint32_t* __restrict__ done) {
   __shared__ __align__(16) uint32_t s_all[4][kFillWords];
-  __shared__ uint32_t s_done, s_w[2][4];
+  __shared__ uint32_t s_done, s_w[2][4], s_tot[2];
   fill_wave<true, false, 1, true>(a, off2, off4, ent2, ent4, s_all);
   __builtin_amdgcn_s_waitcnt(0);
   __threadfence_block();
@@ -547,11 +579,13 @@ __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
       if (base + i + 1 == n) {
         sc.off2[n] = pre2;
         sc.off4[n] = pre4;
-        *sc.total2 = pre2;
-        *sc.total4 = pre4;
+        *sc.total2 = s_tot[0] = pre2;
+        *sc.total4 = s_tot[1] = pre4;
       }
     }
   }
+  __syncthreads();
+  if (sc.pub.to && w == 0) publish_meta(sc.pub, s_tot[0], s_tot[1], lane);
 }
 
 void launch_list_first(const ListLevelArgs& a, const ScanArgs& sc, hipStream_t s) {
@@ -621,7 +655,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_counts2(
   uint32_t* __restrict__ off2 = sc.off2;
   uint32_t* __restrict__ off4 = sc.off4;
   __shared__ uint32_t s_w[2][kScanBlock / 64];
-  __shared__ uint64_t s_excl[2];
+  __shared__ uint64_t s_excl[2], s_tot[2];
   __shared__ uint32_t s_tile;
   const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const uint32_t n = sc.n_dev ? *sc.n_dev : sc.n;
@@ -694,8 +728,8 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_counts2(
     if (base + kScanItems == n) {
       off2[n] = (uint32_t)pre2;
       off4[n] = (uint32_t)pre4;
-      *sc.total2 = pre2;
-      *sc.total4 = pre4;
+      *sc.total2 = s_tot[0] = pre2;
+      *sc.total4 = s_tot[1] = pre4;
     }
   } else {
 #pragma unroll
@@ -708,14 +742,18 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_counts2(
         if (base + i + 1 == n) {
           off2[n] = (uint32_t)pre2;
           off4[n] = (uint32_t)pre4;
-          *sc.total2 = pre2;
-          *sc.total4 = pre4;
+          *sc.total2 = s_tot[0] = pre2;
+          *sc.total4 = s_tot[1] = pre4;
         }
       }
     }
   }
   ovf = (pre2 > 0xFFFFFFFFull) || (pre4 > 0xFFFFFFFFull);
   if (ovf) atomicOr(sc.overflow, 1u);
+  if (sc.pub.to && (uint64_t)(tile + 1) * kScanTile >= n) {  // the last tile
+    __syncthreads();
+    if (w == 0) publish_meta(sc.pub, s_tot[0], s_tot[1], lane);
+  }
 }
 
 uint32_t scan_tiles(uint32_t n) { return div_up(n, kScanTile); }

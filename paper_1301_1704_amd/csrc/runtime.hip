@@ -332,6 +332,25 @@ void fetch_meta(const DevMeta* d, DevMeta* h, hipStream_t s) {
   ck(hipStreamSynchronize(s));
 }
 
+// Waits for the scan of `level` (enqueued on s) to have published into h. The
+// stream is asked now and then (ever less often: asking costs the stream a
+// marker), so that a device error ends the wait too.
+void await_meta(const DevMeta* h, uint32_t level, hipStream_t s) {
+  auto there = [&] { return __atomic_load_n(&h->published, __ATOMIC_ACQUIRE) == level; };
+  for (uint64_t i = 1, ask = 1u << 13; !there(); ++i) {
+    __builtin_ia32_pause();
+    if (i < ask) continue;
+    ask = i + std::min<uint64_t>(i, 1u << 18);
+    const hipError_t q = hipStreamQuery(s);
+    if (q == hipErrorNotReady) {
+      (void)hipGetLastError();
+      continue;
+    }
+    ck(q);
+    if (!there()) throw Fail{FMMDS_ERR_DEVICE};
+  }
+}
+
 
 // ---------------------------------------------------------------------------
 // Per-kernel event timing (fmmds_profile_*).
@@ -1024,13 +1043,15 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       lblock += round_up(count * 4, 256);
       return q;
     };
+    hm->published = 0;  // (nothing enqueued writes it yet)
     for (uint32_t l = 2; l <= D; ++l)
       for (int k = 0; k < 2; ++k) impl->lists[l].off[k] = carve((size_t)lcap[rs][l] + 1);
     auto scan_args = [&](uint32_t l) {
       const uint32_t nr = lcap[rs][l];
       return ScanArgs{cnt, cnt + round_up(nr, 4), nr, early ? &meta->n_boxes[rs][l] : nullptr,
                       impl->lists[l].off[0], impl->lists[l].off[1], &meta->list_total[0][l],
-                      &meta->list_total[1][l], &meta->overflow};
+                      &meta->list_total[1][l], &meta->overflow,
+                      Publish{small_level(l) ? nullptr : hm, meta, l}};
     };
     for (uint32_t l = 2; l <= D; ++l) {
       const uint32_t nr = lcap[rs][l];
@@ -1072,7 +1093,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       if (small_level(l)) {
         for (int k = 0; k < 2; ++k) LB.ent[k] = carve((size_t)nr * (k == 0 ? 27 : 189));
       } else {
-        fetch_meta(meta, hm, st);  // sync point: this level's list totals
+        await_meta(hm, l, st);  // sync point: this level's list totals
         if (early) {
           if (hm->err_range) throw Fail{FMMDS_ERR_RANGE};
           read_counts();
