@@ -12,10 +12,7 @@ constexpr int kMaxLevel = 21;
 constexpr int kMaxPasses = 8;  // 63 key bits / 8-bit digits
 
 // Tile shapes of the single-pass kernels.
-constexpr int kSortBlock = 256;
-// Sort tile sizes, in units of 256 elements: 8, 12 and 16 are tiles of
-// 256 threads with that many elements each; kSortWide is a tile of 8192
-// elements (512 threads x 16), for packed elements only.
+// Sort tile sizes, in units of 256 elements.
 constexpr int kSortItemsDefault = 16;
 constexpr int kSortWide = 32;
 constexpr int kCompBlock = 256;
@@ -73,6 +70,9 @@ void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass
                        uint32_t* err, hipStream_t s);
 uint32_t sort_tile_elems(int items);
 uint32_t sort_tiles(uint32_t n, int items);
+// The tile size for one set of n, and the most tiles of any set of up to n.
+int sort_items(uint32_t n);
+uint32_t sort_tiles_max(uint32_t n);
 // Many point sets sorted at once, each within its own range: tile t covers
 // elements [start[t], start[t + 1]) of set set[t] & 0x7FFFFFFF, never more
 // than one set (the top bit marks a set's first tile); goff holds, per set

@@ -553,8 +553,10 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       const uint32_t n = sets[s].n;
       const uint32_t np = inc[s] ? inc_pass[s] : n_pass;
       // status words of each sort pass, for the tile size that pass runs with
-      const int items = (packed && !dense && !inc[s]) ? kSortWide : kSortItemsDefault;
-      words += (size_t)np * sort_tiles(n, items) * 256 + 2 * div_up(n, kCompTile);
+      const uint32_t tiles = dense    ? sort_tiles(n, kSortItemsDefault)
+                             : inc[s] ? sort_tiles_max(n)  // (the movers: any number of them)
+                                      : sort_tiles(n, sort_items(n));
+      words += (size_t)np * tiles * 256 + 2 * div_up(n, kCompTile);
       tickets += np + 2 + L;
       if (dense) {
         for (uint32_t l = 0; l <= L; ++l) words += dense_scan_tiles(1u << (3 * l));
@@ -838,11 +840,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         P.run(K_DIGITS, (double)np * 2048, [&] { launch_digit_offsets(h, g, np, st); });
         for (uint32_t p = 0; p < np && nm > 0; ++p) {
           const int a = p & 1, b = a ^ 1;
-          uint64_t* stw = sa.take_words((size_t)sort_tiles(n, kSortItemsDefault) * 256);
+          uint64_t* stw = sa.take_words((size_t)sort_tiles(nm, sort_items(nm)) * 256);
           uint32_t* tk = sa.take_ticket();
           P.run(K_SORT, (double)nm * 24, [&] {
             launch_sort_pass(false, mk[a], mk[b], mv[a], mv[b], nm, 8 * p, g + p * 256, stw, tk,
-                             st, kSortItemsDefault);
+                             st, sort_items(nm));
           });
         }
         const int mf = nm > 0 ? (int)(np & 1) : 0;
@@ -875,12 +877,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         for (uint32_t p = 0; p < n_left; ++p) {
           const int a = p & 1, b = a ^ 1;
           const uint32_t shift = (packed ? 32 : 0) + 8 * p;
-          uint64_t* stw =
-              sa.take_words((size_t)sort_tiles(n, packed ? kSortWide : kSortItemsDefault) * 256);
+          uint64_t* stw = sa.take_words((size_t)sort_tiles(n, sort_items(n)) * 256);
           uint32_t* tk = sa.take_ticket();
           P.run(K_SORT, (double)n * (packed ? 16 : 24), [&] {
             launch_sort_pass(packed, sb.k[a], sb.k[b], sb.v[a], sb.v[b], n, shift, g + p * 256,
-                             stw, tk, st, packed ? kSortWide : kSortItemsDefault);
+                             stw, tk, st, sort_items(n));
           });
         }
         const int fin = n_left & 1;
@@ -1462,7 +1463,6 @@ int batch_autotune(BatchImpl& B, const float* xyz) {
   int best = kSortItemsDefault;
   float best_ms = 1e30f;
   for (int items : {8, 12, 16, kSortWide}) {
-    if (items == kSortWide && !B.packed) continue;
     float total = 0;
     for (int rep = 0; rep < 2; ++rep) {
       StatusArena sa;

@@ -451,7 +451,24 @@ void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass
 #undef FMMDS_SMALL
 }
 
-uint32_t sort_tile_elems(int items) { return items == kSortWide ? 8192u : 256u * (uint32_t)items; }
+uint32_t sort_tile_elems(int items) { return 256u * (uint32_t)items; }
+
+// Fewer, larger tiles shorten the look-back chain and write longer runs; more
+// tiles spread a small set over more CUs (there are 256). us per pass, packed
+// elements (tiles of 2048 / 4096 / 8192): 65536 elements 10.1 / 11.2 / 14.7,
+// 200000 12.1 / 12.5 / 15.6, 500000 15.8 / 14.9 / 17.5, 10^6 23.2 / 19.0 / 19.8,
+// 2 * 10^6 34.2 / 26.0 / 24.0; key and index apart: 65536 10.6 / 11.7 / 14.9,
+// 500000 17.0 / 16.2 / 18.2, 10^6 24.5 / 20.3 / 21.0, 4 * 10^6 59 / 43 / 41.
+constexpr uint32_t kSortSmallTiles = 1u << 18, kSortMidTiles = 1u << 20;
+int sort_items(uint32_t n) {
+  return n <= kSortSmallTiles ? 8 : n <= kSortMidTiles ? kSortItemsDefault : kSortWide;
+}
+uint32_t sort_tiles_max(uint32_t n) {
+  uint32_t t = sort_tiles(n, sort_items(n));
+  if (n > kSortSmallTiles) t = std::max(t, sort_tiles(kSortSmallTiles, 8));
+  if (n > kSortMidTiles) t = std::max(t, sort_tiles(kSortMidTiles, kSortItemsDefault));
+  return t;
+}
 
 uint32_t sort_tiles(uint32_t n, int items) { return div_up(n, sort_tile_elems(items)); }
 
@@ -463,17 +480,24 @@ void sort_pass_dispatch(bool packed, const uint64_t* kin, uint64_t* kout, const 
 #define FMMDS_SORT(P, B, I)                                                                     \
   hipLaunchKernelGGL((k_sort_pass<P, B, I, SEG>), dim3(grid), dim3(B), 0, s, kin, kout, vin,   \
                      vout, n, shift, goff, status, tile_counter, n_dev, sg)
+#define FMMDS_SORT2(B, I)                                                                       \
+  do {                                                                                           \
+    if (packed) FMMDS_SORT(true, B, I);                                                          \
+    else FMMDS_SORT(false, B, I);                                                                \
+  } while (0)
+  // 1024 threads a tile: a wave ranks its items one after the other, so fewer
+  // items a thread are a shorter tile (us per pass with 256 threads: tiles of
+  // 2048 14.7 -> 10.1 at 65536 elements, 55.5 -> 54.3 at 4 * 10^6; of 4096 41.1
+  // -> 39.2). Large tiles of packed elements stay at 512 threads, whose LDS
+  // leaves room for two tiles a CU (2^24 elements: 91 us a pass, 116 with 1024);
+  // with the index apart (153 us a pass in tiles of 4096 by 256) there is room
+  // for one either way, 137 us.
   if (items == kSortWide && packed) FMMDS_SORT(true, 512, 16);
-  else if (items == 8) {
-    if (packed) FMMDS_SORT(true, 256, 8);
-    else FMMDS_SORT(false, 256, 8);
-  } else if (items == 12) {
-    if (packed) FMMDS_SORT(true, 256, 12);
-    else FMMDS_SORT(false, 256, 12);
-  } else {
-    if (packed) FMMDS_SORT(true, 256, 16);
-    else FMMDS_SORT(false, 256, 16);
-  }
+  else if (items == kSortWide) FMMDS_SORT(false, 1024, 8);
+  else if (items == 8) FMMDS_SORT2(1024, 2);
+  else if (items == 12) FMMDS_SORT2(1024, 3);
+  else FMMDS_SORT2(1024, 4);
+#undef FMMDS_SORT2
 #undef FMMDS_SORT
 }
 

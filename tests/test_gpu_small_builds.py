@@ -2,7 +2,8 @@
 to 8192 points, packed keys) at the edges of its three block shapes and past
 it, digit offsets straight from key generation's rows and table counts scanned
 in place (up to 64 blocks, 131072 points), the table blocks of 1024 and of 512
-threads (up to and past 1048576 points), level 2 in one block and the coarse
+threads (up to and past 1048576 points), the sort tiles of 2048, 4096 and 8192
+elements (up to 2^18, 2^20 and past it, packed and not), level 2 in one block and the coarse
 levels' scans inside the fill. Bit for bit against the CPU oracle."""
 import os
 import sys
@@ -35,7 +36,8 @@ CASES = [(1, 0, 2, 32, 0), (1, 1, 5, 64, 0), (2, 63, 3, 32, 0), (2048, 0, 3, 32,
          (8192, 0, 10, 32, 0), (8193, 8191, 4, 32, 0), (8192, 8193, 9, 64, 4),
          (5000, 0, 12, 64, 0), (131072, 0, 4, 32, 0), (131073, 131072, 6, 32, 0),
          (131073, 5, 6, 64, 16), (30000, 30000, 10, 32, 40),
-         (1048576, 1048577, 7, 64, 0)]
+         (1048576, 1048577, 7, 64, 0), (262144, 262145, 5, 32, 0),
+         (262145, 262144, 11, 64, 64), (1048577, 1048576, 11, 64, 256)]
 
 
 @pytest.mark.parametrize("n,m,L,kb,s", CASES)
