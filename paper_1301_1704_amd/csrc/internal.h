@@ -68,6 +68,14 @@ void launch_digits(const uint32_t* rows, uint32_t n_rows, uint32_t* hist, uint32
 constexpr uint32_t kSortSmall = 8192;
 void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass, uint64_t* out,
                        uint32_t* err, hipStream_t s);
+// The passes over the points themselves (packed elements): the first (rin null)
+// reads xyz, the last (kout) writes the sorted coordinates and elements.
+bool sort_by_records(uint32_t n, uint32_t n_pass);
+uint32_t record_tiles(uint32_t n);
+void launch_sort_records(const float* xyz, const uint4* rin, uint4* rout, float* sorted_xyz,
+                         uint64_t* kout, uint32_t n, uint32_t L, uint32_t shift,
+                         const uint32_t* goff, uint64_t* status, uint32_t* tile_counter,
+                         hipStream_t s);
 uint32_t sort_tile_elems(int items);
 uint32_t sort_tiles(uint32_t n, int items);
 // The tile size for one set of n, and the most tiles of any set of up to n.

@@ -548,12 +548,18 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     }
 
     // ---- workspace: metadata, histograms, digit offsets, status words
+    const bool plain = !dense && !prev;
+    auto sort_small = [&](int s) { return plain && packed && sets[s].n <= kSortSmall; };
+    auto sort_records = [&](int s) {
+      return plain && packed && sort_by_records(sets[s].n, n_pass);
+    };
     size_t words = 0, tickets = 0;
     for (int s = 0; s < nsets; ++s) {
       const uint32_t n = sets[s].n;
       const uint32_t np = inc[s] ? inc_pass[s] : n_pass;
       // status words of each sort pass, for the tile size that pass runs with
       const uint32_t tiles = dense    ? sort_tiles(n, kSortItemsDefault)
+                             : sort_records(s) ? record_tiles(n)
                              : inc[s] ? sort_tiles_max(n)  // (the movers: any number of them)
                                       : sort_tiles(n, sort_items(n));
       words += (size_t)np * tiles * 256 + 2 * div_up(n, kCompTile);
@@ -591,8 +597,10 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     const uint32_t n_max = std::max(sets[0].n, sets[nsets - 1].n);
     SortBufs sb{};
     SortBufs& sb0 = sb;
-    sb.k[0] = temps.get<uint64_t>(2 * (size_t)round_up(n_max, 2));
-    sb.k[1] = sb.k[0] + round_up(n_max, 2);
+    // two buffers of elements, or of records (twice the size)
+    const size_t k_n = round_up(n_max, 2) * (sort_records(0) || sort_records(nsets - 1) ? 2 : 1);
+    sb.k[0] = temps.get<uint64_t>(2 * k_n);
+    sb.k[1] = sb.k[0] + k_n;
     if (!packed || prev) {
       sb.v[0] = temps.get<uint32_t>(n_max);
       sb.v[1] = temps.get<uint32_t>(n_max);
@@ -667,8 +675,8 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     uint32_t* inc_fvs[2] = {inc_fv, inc_fv};
     float* full_x[2] = {nullptr, nullptr};    // incremental fallback: original order
     if (two) {
-      sb1.k[0] = temps.get<uint64_t>(2 * (size_t)round_up(n_max, 2));
-      sb1.k[1] = sb1.k[0] + round_up(n_max, 2);
+      sb1.k[0] = temps.get<uint64_t>(2 * k_n);
+      sb1.k[1] = sb1.k[0] + k_n;
       if (!packed || prev) {
         sb1.v[0] = temps.get<uint32_t>(n_max);
         sb1.v[1] = temps.get<uint32_t>(n_max);
@@ -727,8 +735,6 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         q += sets[s].lv[l].cap;
       }
     }
-    const bool plain = !dense && !prev;
-    auto sort_small = [&](int s) { return plain && packed && sets[s].n <= kSortSmall; };
     // keygen's per-block digit-count rows, per set
     uint32_t* krows[2] = {nullptr, nullptr};
     for (int s = 0; s < nsets; ++s)
@@ -774,9 +780,9 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         });
         continue;
       }
-      P.run(K_KEYGEN, (double)n * (packed ? 12 + 8 : 12 + 8 + 4), [&] {
-        launch_keygen(sets[s].xyz, n, L, packed, sb.k[0], sb.v[0], n_pass, krows[s],
-                      &meta->err_range, st);
+      P.run(K_KEYGEN, (double)n * (sort_records(s) ? 12 : packed ? 12 + 8 : 12 + 8 + 4), [&] {
+        launch_keygen(sets[s].xyz, n, L, packed, sort_records(s) ? nullptr : sb.k[0], sb.v[0],
+                      n_pass, krows[s], &meta->err_range, st);
       });
       P.run(K_DIGITS, (double)keygen_blocks(n) * n_pass * 1024, [&] {
         launch_digits(krows[s], keygen_blocks(n), h, g, n_pass, st);
@@ -873,7 +879,19 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
             launch_digits(krows[s], keygen_blocks(n), h, g, n_pass, st);
           });
         }
-        const uint32_t n_left = sort_small(s) ? 0 : n_pass;
+        for (uint32_t p = 0; sort_records(s) && p < n_pass; ++p) {
+          const bool last = p + 1 == n_pass;
+          uint4* b[2] = {(uint4*)sb.k[0], (uint4*)sb.k[1]};
+          uint64_t* stw = sa.take_words((size_t)record_tiles(n) * 256);
+          uint32_t* tk = sa.take_ticket();
+          P.run(K_SORT, (double)n * ((p == 0 ? 12 : 16) + (last ? 20 : 16)), [&] {
+            launch_sort_records(S.xyz, p == 0 ? nullptr : b[(p & 1) ^ 1], b[p & 1], S.sorted_xyz,
+                                last ? sb.k[p & 1] : nullptr, n, L, 32 + 8 * p,
+                                g + p * 256, stw, tk, st);
+          });
+        }
+        if (sort_records(s)) leaf_xyz = nullptr;  // (in place already)
+        const uint32_t n_left = sort_small(s) || sort_records(s) ? 0 : n_pass;
         for (uint32_t p = 0; p < n_left; ++p) {
           const int a = p & 1, b = a ^ 1;
           const uint32_t shift = (packed ? 32 : 0) + 8 * p;
@@ -884,7 +902,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
                              stw, tk, st, sort_items(n));
           });
         }
-        const int fin = n_left & 1;
+        const int fin = sort_records(s) ? (int)((n_pass - 1) & 1) : (int)(n_left & 1);
         fin_k = sb.k[fin];
         fin_v = sb.v[fin];
       }

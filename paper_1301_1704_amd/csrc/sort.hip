@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_keygen(const P3* __restrict__ xyz, uint
       const uint64_t key = point_key(p[j].x, p[j].y, p[j].z, L, ok);
       bad |= !ok;
       if (PACKED) {
-        keys[i] = (key << 32) | (uint32_t)i;
+        if (keys) keys[i] = (key << 32) | (uint32_t)i;
       } else {
         keys[i] = key;
         vals[i] = (uint32_t)i;
@@ -211,9 +211,9 @@ __device__ __forceinline__ uint32_t sort_digit(uint64_t k, uint32_t shift) {
 // Ranks of a wave's items (64 of each i, in order) by the digit at `shift` within
 // the wave's own items: item i of this lane is valid while 64 i + lane < lim;
 // `hist` (256 words, zeroed) ends with the wave's digit counts.
-template <bool PACKED, int ITEMS>
+template <bool PACKED, int ITEMS, typename H>
 __device__ __forceinline__ void sort_rank(const uint64_t (&k)[ITEMS], uint32_t shift, uint32_t lim,
-                                          uint32_t lane, uint32_t* hist, uint32_t (&r)[ITEMS]) {
+                                          uint32_t lane, H* hist, uint32_t (&r)[ITEMS]) {
 #pragma unroll
   for (int i = 0; i < ITEMS; ++i) {
     const bool valid = 64u * i + lane < lim;
@@ -235,7 +235,7 @@ __device__ __forceinline__ void sort_rank(const uint64_t (&k)[ITEMS], uint32_t s
     uint32_t prev = 0;
     if (valid) prev = hist[d];
     r[i] = prev + below;
-    if (valid && below == 0) hist[d] = prev + (uint32_t)(__popc(plo) + __popc(phi));
+    if (valid && below == 0) hist[d] = (H)(prev + (uint32_t)(__popc(plo) + __popc(phi)));
   }
 }
 
@@ -449,6 +449,145 @@ void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass
   else if (n <= 4096) FMMDS_SMALL(1024, 4);
   else FMMDS_SMALL(1024, 8);
 #undef FMMDS_SMALL
+}
+
+// ---------------------------------------------------------------------------
+// Large sets: the passes move the points themselves (coordinates and index, 16
+// bytes; the key is computed anew), so that the last one leaves coordinates and
+// sorted elements in order. Moving (key, index) alone is half the bytes, but the
+// coordinates then have to be gathered by index at the end: 12 random bytes a
+// point, a whole line fetched for each (2^24 points at level 8: keys 86 us, three
+// passes of 91, tables with the gather 451; here keys 69, passes of 161 on
+// average, tables 127). FIRST reads the points as they are given, LAST writes the
+// results instead of records. What bounds it is memory: two chains of passes
+// together move 3.4 (FIRST) to 3.9 TB/s (a plain copy 4.8). Tiles of 8192 leave
+// runs of 512 bytes per digit, one tile a CU; with tiles of 4096 and two tiles a
+// CU the build of 2 x 2^24 points took 3835 us, with these 3790 (by elements
+// 4005).
+// ---------------------------------------------------------------------------
+// Builds (us, by records / by elements): one set at level 6 of 2^20 points 249 /
+// 244, 2^21 288 / 297, 2^24 831 / 921; at level 8 2^20 604 / 597, 2^21 977 / 993,
+// 2^24 3103 / 3180. Four passes (levels 9 and 10) move so much more that it pays
+// later: 3 * 2^20 points 2941 / 2924, 2^24 8506 / 8504, two sets of 2^24
+// clustered points at level 10 3357 / 3450.
+constexpr uint32_t kRecMin = 1u << 20, kRecMin4 = 1u << 22;
+bool sort_by_records(uint32_t n, uint32_t n_pass) {
+  return n_pass >= 2 && n > (n_pass <= 3 ? kRecMin : kRecMin4);
+}
+
+constexpr int kRecBlock = 1024, kRecItems = 8, kRecTile = kRecBlock * kRecItems;
+
+__device__ __forceinline__ uint64_t record_key(uint4 q, uint32_t L) {
+  bool ok;
+  return point_key(__uint_as_float(q.x), __uint_as_float(q.y), __uint_as_float(q.z), L, ok) << 32;
+}
+
+template <bool FIRST, bool LAST>
+__global__ __launch_bounds__(kRecBlock) void k_sort_records(
+    const uint32_t* __restrict__ xyz, const uint4* __restrict__ rin, uint4* __restrict__ rout,
+    uint32_t* __restrict__ sorted_xyz, uint64_t* __restrict__ kout, uint32_t n, uint32_t L,
+    uint32_t shift, const uint32_t* __restrict__ goff,
+    uint64_t* __restrict__ status, uint32_t* __restrict__ tile_counter) {
+  constexpr int W = kRecBlock / 64;
+  constexpr uint32_t WSEG = 64 * kRecItems;
+  __shared__ uint4 s_rec[kRecTile];
+  __shared__ uint16_t s_hist[W][256];
+  __shared__ uint32_t s_cnt[256], s_lstart[256], s_base[256];
+  __shared__ uint32_t s_scan[4];
+  __shared__ uint32_t s_tile;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (tid == 0) s_tile = atomicAdd(tile_counter, 1u);
+  for (uint32_t i = tid; i < W * 128; i += kRecBlock) ((uint32_t*)s_hist)[i] = 0;
+  if (tid < 256) s_cnt[tid] = 0;
+  __syncthreads();
+  const uint32_t tile = __builtin_amdgcn_readfirstlane(s_tile);
+  const uint32_t tbase = tile * kRecTile;
+  const uint32_t tcount = min((uint32_t)kRecTile, n - tbase);
+  const uint32_t wbase = w * WSEG;
+  const uint32_t lim = tcount > wbase ? min(WSEG, tcount - wbase) : 0u;
+
+  uint4 q[kRecItems];
+  uint64_t k[kRecItems];
+  uint32_t r[kRecItems];
+#pragma unroll
+  for (int i = 0; i < kRecItems; ++i) {
+    const uint32_t e = tbase + min(wbase + 64u * i + lane, tcount - 1);  // (past the end: the last)
+    if (FIRST) {
+      const uint32_t* p = xyz + 3ull * e;
+      q[i] = make_uint4(p[0], p[1], p[2], e);
+    } else {
+      q[i] = rin[e];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kRecItems; ++i) {
+    k[i] = record_key(q[i], L);
+    if (64u * i + lane < lim) atomicAdd(&s_cnt[sort_digit<true>(k[i], shift)], 1u);
+  }
+  __syncthreads();
+  if (tid < 256)
+    st_status(status + (uint64_t)tile * 256 + tid,
+              (tile == 0 ? kStInc : kStAgg) | (uint64_t)s_cnt[tid]);
+  sort_rank<true, kRecItems>(k, shift, lim, lane, s_hist[w], r);
+  __syncthreads();
+  uint32_t cnt = 0, inc = 0;
+  if (tid < 256) {
+#pragma unroll
+    for (int ww = 0; ww < W; ++ww) {
+      const uint32_t c = s_hist[ww][tid];
+      s_hist[ww][tid] = (uint16_t)cnt;
+      cnt += c;
+    }
+    inc = wave_incl_scan(cnt);
+    if (lane == 63) s_scan[w] = inc;
+  }
+  __syncthreads();
+  if (tid < 256) {
+    uint32_t wpre = 0;
+    for (uint32_t ww = 0; ww < w; ++ww) wpre += s_scan[ww];
+    const uint32_t lstart = wpre + inc - cnt;
+    s_lstart[tid] = lstart;
+    const uint64_t excl = tile == 0 ? 0 : lookback_window<4>(status + tid, 256, tile, cnt);
+    s_base[tid] = goff[tid] + (uint32_t)excl - lstart;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kRecItems; ++i) {
+    if (64u * i + lane < lim) {
+      const uint32_t d = sort_digit<true>(k[i], shift);
+      s_rec[s_lstart[d] + s_hist[w][d] + r[i]] = q[i];
+    }
+  }
+  __syncthreads();
+#pragma unroll 2
+  for (uint32_t j = tid; j < tcount; j += kRecBlock) {
+    const uint4 v = s_rec[j];
+    const uint64_t key = record_key(v, L);
+    const uint32_t g = s_base[sort_digit<true>(key, shift)] + j;
+    if (LAST) {
+      uint32_t* o = sorted_xyz + 3ull * g;
+      o[0] = v.x, o[1] = v.y, o[2] = v.z;
+      kout[g] = key | v.w;
+    } else {
+      rout[g] = v;
+    }
+  }
+}
+
+uint32_t record_tiles(uint32_t n) { return div_up(n, kRecTile); }
+
+void launch_sort_records(const float* xyz, const uint4* rin, uint4* rout, float* sorted_xyz,
+                         uint64_t* kout, uint32_t n, uint32_t L, uint32_t shift,
+                         const uint32_t* goff, uint64_t* status, uint32_t* tile_counter,
+                         hipStream_t s) {
+#define FMMDS_REC(A, B)                                                                         \
+  hipLaunchKernelGGL((k_sort_records<A, B>), dim3(record_tiles(n)), dim3(kRecBlock), 0, s,      \
+                     (const uint32_t*)xyz, rin, rout, (uint32_t*)sorted_xyz, kout, n, L,  \
+                     shift, goff, status, tile_counter)
+  if (!rin) FMMDS_REC(true, false);
+  else if (kout) FMMDS_REC(false, true);
+  else FMMDS_REC(false, false);
+#undef FMMDS_REC
 }
 
 uint32_t sort_tile_elems(int items) { return 256u * (uint32_t)items; }

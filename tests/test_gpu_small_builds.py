@@ -3,7 +3,8 @@ to 8192 points, packed keys) at the edges of its three block shapes and past
 it, digit offsets straight from key generation's rows and table counts scanned
 in place (up to 64 blocks, 131072 points), the table blocks of 1024 and of 512
 threads (up to and past 1048576 points), the sort tiles of 2048, 4096 and 8192
-elements (up to 2^18, 2^20 and past it, packed and not), level 2 in one block and the coarse
+elements (up to 2^18, 2^20 and past it, packed and not), the passes over whole
+points (past 2^20 points: two and three passes), level 2 in one block and the coarse
 levels' scans inside the fill. Bit for bit against the CPU oracle."""
 import os
 import sys
@@ -37,7 +38,8 @@ CASES = [(1, 0, 2, 32, 0), (1, 1, 5, 64, 0), (2, 63, 3, 32, 0), (2048, 0, 3, 32,
          (5000, 0, 12, 64, 0), (131072, 0, 4, 32, 0), (131073, 131072, 6, 32, 0),
          (131073, 5, 6, 64, 16), (30000, 30000, 10, 32, 40),
          (1048576, 1048577, 7, 64, 0), (262144, 262145, 5, 32, 0),
-         (262145, 262144, 11, 64, 64), (1048577, 1048576, 11, 64, 256)]
+         (262145, 262144, 11, 64, 64), (1048577, 1048576, 11, 64, 256),
+         (1048577, 1048576, 5, 32, 0), (2000003, 1500001, 8, 64, 0)]
 
 
 @pytest.mark.parametrize("n,m,L,kb,s", CASES)
@@ -59,9 +61,10 @@ def test_small_build_matches_oracle(F, oracle_lib, n, m, L, kb, s):
     o.close()
 
 
-def test_small_sort_refuses_points_out_of_range(F):
-    for at in (0, 4099, 8191):
-        p = I.uniform_points(303, 8192)
+@pytest.mark.parametrize("n", [8192, 1048577])
+def test_points_out_of_range_are_refused(F, n):
+    for at in (0, n // 2 + 3, n - 1):
+        p = I.uniform_points(303, n)
         p[at, 1] = 1.0
         with pytest.raises(F.FmmdsError):
             F.build(parity.to_gpu(p), None, max_level=4, key_bits=32)
