@@ -128,8 +128,12 @@ void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* 
                    const TabLevels& T, uint32_t* perm, float* sorted_xyz, uint32_t* n_boxes,
                    uint32_t node_cap, hipStream_t s, int phase,
                    const uint64_t* set_off = nullptr, uint32_t set_shift = 0);
-void launch_max_occupancy(const uint32_t* begin, const uint32_t* n_in, uint32_t cap,
-                          uint32_t* out, hipStream_t s);
+struct OccLevels {
+  const uint32_t* begin[kMaxLevel + 1];
+};
+// max_occ[l] (zeroed) of levels 2..L; cap: most boxes of any of them.
+void launch_max_occupancy(const OccLevels& lv, uint32_t L, uint32_t cap, const uint32_t* n_boxes,
+                          uint32_t* max_occ, hipStream_t s);
 
 // ---- lists.hip
 struct ListLevelArgs {
@@ -173,6 +177,8 @@ struct ScanArgs {
   uint32_t* overflow;
   Publish pub;
 };
+// One wave writes the metadata block to pub.to (no list totals).
+void launch_publish(const Publish& pub, hipStream_t s);
 void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, hipStream_t s);
 // Level 2 of a plain build (at most 8 parents and 64 boxes): counts and offsets.
 void launch_list_first(const ListLevelArgs& a, const ScanArgs& sc, hipStream_t s);

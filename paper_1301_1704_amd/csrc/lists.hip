@@ -588,6 +588,14 @@ __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
   if (sc.pub.to && w == 0) publish_meta(sc.pub, s_tot[0], s_tot[1], lane);
 }
 
+__global__ __launch_bounds__(64) void k_publish(Publish pub) {
+  publish_meta(pub, 0, 0, threadIdx.x);
+}
+
+void launch_publish(const Publish& pub, hipStream_t s) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, pub);
+}
+
 void launch_list_first(const ListLevelArgs& a, const ScanArgs& sc, hipStream_t s) {
   hipLaunchKernelGGL(k_list_first, dim3(1), dim3(256), 0, s, a, sc);
 }

@@ -318,18 +318,13 @@ DevMeta* host_meta() {
   thread_local DevMeta* h = nullptr;
   if (!h) {
     void* p = nullptr;
-    if (hipHostMalloc(&p, sizeof(DevMeta), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&p, sizeof(DevMeta), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
       (void)hipGetLastError();
       throw Fail{FMMDS_ERR_NOMEM};
     }
     h = (DevMeta*)p;
   }
   return h;
-}
-
-void fetch_meta(const DevMeta* d, DevMeta* h, hipStream_t s) {
-  ck(hipMemcpyAsync(h, d, sizeof(DevMeta), hipMemcpyDeviceToHost, s));
-  ck(hipStreamSynchronize(s));
 }
 
 // Waits for the scan of `level` (enqueued on s) to have published into h. The
@@ -349,6 +344,13 @@ void await_meta(const DevMeta* h, uint32_t level, hipStream_t s) {
     ck(q);
     if (!there()) throw Fail{FMMDS_ERR_DEVICE};
   }
+}
+
+// The metadata block as the stream leaves it.
+void fetch_meta(const DevMeta* d, DevMeta* h, hipStream_t s) {
+  h->published = 0;
+  launch_publish({h, d, 1}, s);
+  await_meta(h, 1, s);
 }
 
 
@@ -936,12 +938,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         P.run(K_LEVEL, 0.0, [&] { tab(3); }, s, -1);
       }
       if (opt->cluster_s > 0) {
-        for (uint32_t l = 2; l <= L; ++l) {
-          P.run(K_MAXOCC, 0.0, [&] {
-            launch_max_occupancy(S.lv[l].begin, &meta->n_boxes[s][l], S.lv[l].cap,
-                                 &meta->max_occ[s][l], st);
-          }, s, (int)l);
-        }
+        OccLevels lv{};
+        for (uint32_t l = 2; l <= L; ++l) lv.begin[l] = S.lv[l].begin;
+        P.run(K_MAXOCC, 0.0, [&] {
+          launch_max_occupancy(lv, L, S.lv[L].cap, meta->n_boxes[s], meta->max_occ[s], st);
+        }, s);
       }
     }
 
@@ -1183,7 +1184,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       }
       if (r.cls == K_LEVEL)
         return (double)c[r.level + 1] * (ksz + 4 + 4) + (double)c[r.level] * (ksz + 4 + 4 + 1);
-      if (r.cls == K_MAXOCC) return (double)(c[r.level] + 1) * 4;
+      if (r.cls == K_MAXOCC) {
+        double b = 0;
+        for (uint32_t l = 2; l <= L; ++l) b += (double)(c[l] + 1) * 4;
+        return b;
+      }
       return 0.0;
     });
 
