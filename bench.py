@@ -70,10 +70,12 @@ def counter_traffic(workload_name: str, kernel_class: str):
 
 
 KERNEL_CLASS = [  # rocprofv3 kernel name (namespace and arguments stripped) -> class
-    ("k_list_fill", "list_fill"), ("k_list_count", "list_count"), ("k_list_first", "list_count"),
+    ("k_list_fill", "list_fill"), ("k_list_fill_scan", "list_fill"),
+    ("k_list_count", "list_count"), ("k_list_first", "list_count"),
     ("k_scan_counts2", "scan_counts"), ("k_sort_pass", "sort_pass"),
     ("k_sort_small", "sort_pass"), ("k_sort_records", "sort_pass"), ("k_keygen", "keygen"),
-    ("k_digit_offsets", "digit_offsets"), ("k_zero", "zero"), ("k_leaf", "leaf"),
+    ("k_digit_offsets", "digit_offsets"), ("k_digit_offsets_rows", "digit_offsets"),
+    ("k_zero", "zero"), ("k_leaf", "leaf"),
     ("k_level", "level"), ("k_max_occupancy", "max_occupancy"), ("k_tab_count", "tab_count"),
     ("k_tab_scan", "tab_scan"), ("k_tab_write", "leaf"), ("k_tab_nodes", "level"),
     ("k_pack_sources", "near_pack"), ("k_near_field", "near_field")]

@@ -1619,14 +1619,6 @@ void batch_layout(BatchImpl& B, Carve& M) {
     B.sb.v[0] = M.get<uint32_t>(P);
     B.sb.v[1] = M.get<uint32_t>(P);
   }
-  // (the list kernels' records go where the sorted elements were, if they fit)
-  size_t nodes = 0;
-  for (uint32_t l = 1; l < L; ++l) nodes += B.cap[l];
-  uint4* node = nodes <= P ? (uint4*)B.sb.k[0] : M.get<uint4>(nodes);
-  for (uint32_t l = 1; l < L; ++l) {
-    B.node[l] = node;
-    if (node) node += B.cap[l];
-  }
   B.perm = M.get<uint32_t>(P);
   B.sxyz = M.get<float>(3 * (size_t)P);
   B.tabbuf = M.get<uint32_t>((size_t)2 * (L + 1) * tab_tiles(P));
@@ -1650,9 +1642,42 @@ void batch_layout(BatchImpl& B, Carve& M) {
     if (l >= 2) {
       for (int k = 0; k < 2; ++k) {
         B.goff[l][k] = M.get<uint32_t>(c + 1);
-        B.loff[l][k] = M.get<uint32_t>(c + n_sets);
         B.ent[l][k] = M.get<uint32_t>((size_t)(k == 0 ? 27 : 189) * B.rcap[l]);
       }
+    }
+  }
+  // every level's set-relative offsets, written last of all, in one block
+  size_t lo_n = 0;
+  for (uint32_t l = 2; l <= L; ++l) lo_n += 2 * round_up((size_t)B.cap[l] + n_sets, 64);
+  uint32_t* lo = M.get<uint32_t>(std::max<size_t>(lo_n, 1));
+  size_t lo_at = 0;
+  for (uint32_t l = 2; l <= L; ++l)
+    for (int k = 0; k < 2; ++k) {
+      B.loff[l][k] = lo ? lo + lo_at : nullptr;
+      lo_at += round_up((size_t)B.cap[l] + n_sets, 64);
+    }
+  // The list kernels' records (16 bytes a box) take no memory of their own where
+  // they fit elsewhere: in the space of the sorted elements, done with by then, of
+  // the set-relative offsets, or of the E4 entries of a level whose fill comes
+  // after the last read of them (level l's are read by the fills of levels l and
+  // l + 1).
+  size_t room[kMaxLevel + 2] = {}, used[kMaxLevel + 2] = {};
+  // (slot 0: the sorted elements; 1: the offsets; m: level m's E4 entries)
+  room[0] = P;
+  room[1] = lo_n / 4;
+  for (uint32_t m = 2; m <= L; ++m) room[m] = (size_t)189 * B.rcap[m] / 4;
+  for (uint32_t l = L - 1; l >= 1 && l < L; --l) {
+    uint32_t at = kMaxLevel + 1;  // (none)
+    for (uint32_t m = L; m >= l + 2 && at > L; --m)
+      if (used[m] + B.cap[l] <= room[m]) at = m;
+    if (at > L && used[1] + B.cap[l] <= room[1]) at = 1;
+    if (used[0] + B.cap[l] <= room[0]) at = 0;
+    if (at > L) {
+      B.node[l] = M.get<uint4>(B.cap[l]);
+    } else {
+      uint4* q = (uint4*)(at == 0 ? (void*)B.sb.k[0] : at == 1 ? (void*)lo : (void*)B.ent[at][1]);
+      B.node[l] = q ? q + used[at] : nullptr;
+      used[at] += B.cap[l];
     }
   }
   B.cnt = M.get<uint32_t>(2 * round_up(std::max<uint32_t>(cmax, 1), 4));

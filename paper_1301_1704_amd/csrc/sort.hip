@@ -196,7 +196,7 @@ void launch_digits(const uint32_t* rows, uint32_t n_rows, uint32_t* hist, uint32
 // consecutive addresses of one digit's run. The look-back chain is what sets
 // the pass's length (without it a 4096-element pass over 2^24 elements takes
 // ~75 us instead of ~125 us), so each tile publishes its digit counts (LDS
-// atomics) before it ranks, tiles of 8192 packed elements (512 threads)
+// atomics) before it ranks, large sets take tiles of 8192 elements, which
 // halve the chain of 4096-element tiles, and each digit's walk loads four
 // predecessors' words at a time.
 // ---------------------------------------------------------------------------

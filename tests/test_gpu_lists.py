@@ -81,3 +81,32 @@ def test_batch_lists_of_large_levels(F, oracle_lib):
             parity.compare_lists(t, o)
         torch.cuda.synchronize()
     b.free()
+
+
+@pytest.mark.parametrize("sizes,levels", [
+    ((3000, 9000, 40), (9, 3, 9)),        # records in the sorted elements' space and E4 lists
+    ((20000, 20000, 2), (8, 4, 12)),      # few deep boxes: also in the set-relative offsets
+    ((9, 5, 7), (12, 11, 20)),            # key and index apart
+    ((1, 1), (2, 3)),
+])
+def test_batch_records_in_borrowed_space(F, oracle_lib, sizes, levels):
+    """Batches of more boxes than points: the list kernels' records use space
+    of buffers written later. Replays with other points each time."""
+    import torch
+    off = np.zeros(len(sizes) + 1, np.uint64)
+    off[1:] = np.cumsum(sizes)
+    b = F.Batch(off, np.asarray(levels, np.uint8))
+    x = torch.empty((int(off[-1]), 3), dtype=torch.float32, device="cuda")
+    for k, capture in enumerate((False, True, True)):
+        sets = [I.uniform_points(400 + 10 * k + i, n) for i, n in enumerate(sizes)]
+        x.copy_(torch.from_numpy(np.concatenate(sets)))
+        torch.cuda.synchronize()
+        b.launch(x, capture=capture)
+        b.wait()
+        for i, (pts, L) in enumerate(zip(sets, levels)):
+            o = oracle_lib.OracleTree(pts, None, key_bits=64, max_level=L)
+            t = b.tree(i)
+            parity.compare_tables(t, o, 64)
+            parity.compare_lists(t, o)
+        torch.cuda.synchronize()
+    b.free()
