@@ -221,7 +221,7 @@ def cpu_model() -> str:
 
 
 def host_cores() -> int:
-    """Cores this process may use (the GPU machine gives one GPU 16 of them)."""
+    """Cores this process may use (a container may give fewer than the machine has)."""
     try:
         n = len(os.sched_getaffinity(0))
     except AttributeError:
