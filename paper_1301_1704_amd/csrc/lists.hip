@@ -540,22 +540,34 @@ __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
   if (s_done + 1 != gridDim.x) return;  // whole block
   const uint32_t n = sc.n_dev ? *sc.n_dev : sc.n;
   const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-  const uint32_t base = threadIdx.x * kScanSmallItems;
-  // (the counts from where other XCDs left them, past this one's cache)
-  uint32_t v2[kScanSmallItems], v4[kScanSmallItems], sum2 = 0, sum4 = 0;
+  // The counts from where other XCDs left them, past this one's cache, read 256
+  // consecutive ones at a time into LDS (E4 in the high half; at most 216), from
+  // which each thread takes kScanSmallItems consecutive ones (65536 points, level
+  // 3 to 4, fill and scan: 16.8 us with each thread reading its own, now 14.0).
+  static_assert(kScanSmall <= 4 * kFillWords, "the counts fit the staging space");
+  uint32_t* st = &s_all[0][0];
+  {
+    uint32_t c2[kScanSmallItems], c4[kScanSmallItems];
 #pragma unroll
-  for (uint32_t i = 0; i < kScanSmallItems; ++i) {
-    const bool ok = base + i < n;
-    v2[i] = v4[i] = 0;
-    if (ok) {
-      v2[i] = __hip_atomic_load(sc.cnt2 + base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      v4[i] = __hip_atomic_load(sc.cnt4 + base + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (uint32_t i = 0; i < kScanSmallItems; ++i) {
+      const uint32_t k = min(256u * i + threadIdx.x, max(n, 1u) - 1u);
+      c2[i] = __hip_atomic_load(sc.cnt2 + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      c4[i] = __hip_atomic_load(sc.cnt4 + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kScanSmallItems; ++i) {
+      const uint32_t k = 256u * i + threadIdx.x;
+      st[k] = k < n ? c4[i] << 16 | c2[i] : 0u;
     }
   }
+  __syncthreads();
+  const uint32_t base = threadIdx.x * kScanSmallItems;
+  uint32_t v[kScanSmallItems], sum2 = 0, sum4 = 0;
 #pragma unroll
   for (uint32_t i = 0; i < kScanSmallItems; ++i) {
-    sum2 += v2[i];
-    sum4 += v4[i];
+    v[i] = st[base + i];
+    sum2 += v[i] & 0xFFFFu;
+    sum4 += v[i] >> 16;
   }
   const uint32_t inc2 = wave_incl_scan(sum2), inc4 = wave_incl_scan(sum4);
   if (lane == 63) {
@@ -569,21 +581,25 @@ __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
     pre4 += s_w[1][i];
   }
   // (at most kScanSmall * 216 entries: no overflow)
-#pragma unroll
-  for (uint32_t i = 0; i < kScanSmallItems; ++i) {
-    if (base + i < n) {
-      sc.off2[base + i] = pre2;
-      sc.off4[base + i] = pre4;
-      pre2 += v2[i];
-      pre4 += v4[i];
-      if (base + i + 1 == n) {
-        sc.off2[n] = pre2;
-        sc.off4[n] = pre4;
-        *sc.total2 = s_tot[0] = pre2;
-        *sc.total4 = s_tot[1] = pre4;
-      }
-    }
+  if (threadIdx.x == 255) {
+    sc.off2[n] = s_tot[0] = pre2 + sum2;
+    sc.off4[n] = s_tot[1] = pre4 + sum4;
+    *sc.total2 = pre2 + sum2;
+    *sc.total4 = pre4 + sum4;
   }
+  // the offsets out through LDS the same way
+  auto put = [&](uint32_t pre, uint32_t shift, uint32_t* off) {
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kScanSmallItems; ++i) {
+      st[base + i] = pre;
+      pre += (v[i] >> shift) & 0xFFFFu;
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < n; k += 256) off[k] = st[k];
+  };
+  put(pre2, 0, sc.off2);
+  put(pre4, 16, sc.off4);
   __syncthreads();
   if (sc.pub.to && w == 0) publish_meta(sc.pub, s_tot[0], s_tot[1], lane);
 }
