@@ -157,28 +157,29 @@ __global__ __launch_bounds__(256) void k_list_count(ListLevelArgs a, uint32_t* _
 
 // One wave copies the metadata block to the host's pinned memory and then sets
 // `published`: the host, which polls it, reads the totals some 20 us earlier
-// than after a copy command and a stream synchronization. Every word is stored
-// past the caches and waited for (vmcnt 0) before the flag is.
+// than after a copy command and a stream synchronization. It sizes arrays by
+// them, so every lane's words are released to the system before the flag is
+// stored, and each word is stored once: the totals of pub.level and the
+// overflow flag, the scan's own, in place of the block's.
 __device__ __forceinline__ void publish_meta(const Publish& pub, uint64_t total2, uint64_t total4,
                                              uint32_t lane) {
-  auto put = [](uint32_t* at, uint32_t v) {
-    __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  };
   const uint32_t* from = (const uint32_t*)pub.meta;
   uint32_t* to = (uint32_t*)pub.to;
-  for (uint32_t i = lane; i < offsetof(DevMeta, published) / 4; i += 64) put(to + i, from[i]);
-  __builtin_amdgcn_s_waitcnt(0);
-  if (lane < 2) {
-    const uint64_t t = lane ? total4 : total2;
-    uint32_t* at = (uint32_t*)&pub.to->list_total[lane][pub.level];
-    put(at, (uint32_t)t);
-    put(at + 1, (uint32_t)(t >> 32));
-  } else if (lane == 2 && (total2 > 0xFFFFFFFFull || total4 > 0xFFFFFFFFull)) {
-    put(&pub.to->overflow, 1u);
+  const uint32_t at2 = offsetof(DevMeta, list_total) / 4 + 2u * pub.level;
+  const uint32_t at4 = at2 + 2u * (kMaxLevel + 1);
+  const bool over = total2 > 0xFFFFFFFFull || total4 > 0xFFFFFFFFull;
+  for (uint32_t i = lane; i < offsetof(DevMeta, published) / 4; i += 64) {
+    uint32_t v = from[i];
+    if (i - at2 < 2u) v = (uint32_t)(total2 >> (32u * (i - at2)));
+    if (i - at4 < 2u) v = (uint32_t)(total4 >> (32u * (i - at4)));
+    if (i == offsetof(DevMeta, overflow) / 4 && over) v = 1u;
+    __hip_atomic_store(to + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
-  __builtin_amdgcn_s_waitcnt(0);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
   __builtin_amdgcn_wave_barrier();
-  if (lane == 0) put(&pub.to->published, pub.level);
+  if (lane == 0)
+    __hip_atomic_store(&pub.to->published, pub.level, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // A plain build's level 2 (at most 8 parents, 64 boxes): the counts and their

@@ -313,12 +313,14 @@ hipStream_t side_stream() {
   return streams[dev];
 }
 
-// Host copy of the metadata block, through a pinned buffer of this thread.
+// Host copy of the metadata block, through a pinned buffer of this thread: of
+// coherent memory, since the host polls it while the kernel that writes it runs.
 DevMeta* host_meta() {
   thread_local DevMeta* h = nullptr;
   if (!h) {
     void* p = nullptr;
-    if (hipHostMalloc(&p, sizeof(DevMeta), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    if (hipHostMalloc(&p, sizeof(DevMeta), hipHostMallocPortable | hipHostMallocMapped |
+                                               hipHostMallocCoherent) != hipSuccess) {
       (void)hipGetLastError();
       throw Fail{FMMDS_ERR_NOMEM};
     }
