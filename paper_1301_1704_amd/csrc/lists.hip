@@ -258,10 +258,7 @@ __device__ __forceinline__ void flush_entries(uint32_t* lds, uint32_t& b, uint32
 // serves them all: with two pairs the sparse levels of a 2M-point level-13
 // build take 1.43 ms in all against 1.60 ms with one (uniform level 8: 1641 us
 // either way; its full level 7, 448 against 423 us).
-//
-// AGENT: the next level's counts are stored past the cache of this XCD, for the
-// block that scans them (k_list_fill_scan).
-template <bool NEXT, bool BATCH, uint32_t PAIRS, bool AGENT>
+template <bool NEXT, bool BATCH, uint32_t PAIRS>
 __device__ __forceinline__ void fill_wave(const ListLevelArgs& a,
                                           const uint32_t* __restrict__ off2,
                                           const uint32_t* __restrict__ off4,
@@ -414,14 +411,8 @@ __device__ __forceinline__ void fill_wave(const ListLevelArgs& a,
         const uint4 v = *(const uint4*)(lds + 4 * kUnion + 32 * hh + 4 * q);
         const uint32_t c2 = (uint32_t)__popc(v.x & ex & ey & el) + (uint32_t)__popc(v.y & ex & ey & eh);
         const uint32_t at = rc + (uint32_t)__popc(rm & ((1u << qq) - 1u));
-        if (AGENT) {
-          __hip_atomic_store(a.cnt2_next + at, c2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(a.cnt4_next + at, v.z - c2, __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-          a.cnt2_next[at] = nz ? 0u : c2;
-          a.cnt4_next[at] = nz ? 0u : v.z - c2;
-        }
+        a.cnt2_next[at] = nz ? 0u : c2;
+        a.cnt4_next[at] = nz ? 0u : v.z - c2;
       }
     }
   }
@@ -511,16 +502,15 @@ __global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(Li
                                                       uint32_t* __restrict__ ent2,
                                                       uint32_t* __restrict__ ent4) {
   __shared__ __align__(16) uint32_t s_all[4][kFillWords];
-  fill_wave<NEXT, BATCH, PAIRS, false>(a, off2, off4, ent2, ent4, s_all);
+  fill_wave<NEXT, BATCH, PAIRS>(a, off2, off4, ent2, ent4, s_all);
 }
 
 // A coarse level of a plain build, whose next level has at most kScanSmall
 // boxes: the block that finishes last (`done` counts them) also turns the next
 // level's counts into offsets. Level 2 of a 4097-point build: fill, gap and scan
 // took 5.7 + 3.8 + 4.6 us, this 8.2. Past kScanSmall one block's scan would be
-// longer than the launch that it saves. Every count is past
-// the caches before its block is counted: its wave waits for its stores
-// (vmcnt 0) ahead of the barrier that the counting lane passes.
+// longer than the launch that it saves. The counter releases each block's counts
+// and acquires the others' for the block that scans them.
 constexpr uint32_t kScanSmallItems = kScanSmall / 256;
 __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
                                                            const uint32_t* __restrict__ off2,
@@ -531,20 +521,18 @@ __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
                                                            uint32_t* __restrict__ done) {
   __shared__ __align__(16) uint32_t s_all[4][kFillWords];
   __shared__ uint32_t s_done, s_w[2][4], s_tot[2];
-  fill_wave<true, false, 1, true>(a, off2, off4, ent2, ent4, s_all);
-  __builtin_amdgcn_s_waitcnt(0);
-  __threadfence_block();
+  fill_wave<true, false, 1>(a, off2, off4, ent2, ent4, s_all);
   __syncthreads();
   if (threadIdx.x == 0)
-    s_done = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_done = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (s_done + 1 != gridDim.x) return;  // whole block
   const uint32_t n = sc.n_dev ? *sc.n_dev : sc.n;
   const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
-  // The counts from where other XCDs left them, past this one's cache, read 256
-  // consecutive ones at a time into LDS (E4 in the high half; at most 216), from
-  // which each thread takes kScanSmallItems consecutive ones (65536 points, level
-  // 3 to 4, fill and scan: 16.8 us with each thread reading its own, now 14.0).
+  // The counts, read 256 consecutive ones at a time into LDS (E4 in the high
+  // half; at most 216), from which each thread takes kScanSmallItems consecutive
+  // ones (65536 points, level 3 to 4, fill and scan: 16.8 us with each thread
+  // reading its own, now 14.0).
   static_assert(kScanSmall <= 4 * kFillWords, "the counts fit the staging space");
   uint32_t* st = &s_all[0][0];
   {
@@ -552,8 +540,8 @@ __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
 #pragma unroll
     for (uint32_t i = 0; i < kScanSmallItems; ++i) {
       const uint32_t k = min(256u * i + threadIdx.x, max(n, 1u) - 1u);
-      c2[i] = __hip_atomic_load(sc.cnt2 + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      c4[i] = __hip_atomic_load(sc.cnt4 + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      c2[i] = sc.cnt2[k];
+      c4[i] = sc.cnt4[k];
     }
 #pragma unroll
     for (uint32_t i = 0; i < kScanSmallItems; ++i) {

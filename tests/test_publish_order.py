@@ -38,3 +38,18 @@ def test_flag_is_stored_after_a_release_to_the_system(asm, name):
     between = ops[stores[0] + 1:stores[1]]
     assert between and between[0] == "buffer_wbl2 sc0 sc1", ops
     assert "s_waitcnt" in between[1], ops
+
+
+def test_last_block_acquires_what_the_others_released(asm):
+    """The block that counts itself last scans the counts that the others wrote:
+    the counter is an acquire and a release across the chip."""
+    ops = [x for x in _kernel(asm, "k_list_fill_scan")
+           if re.match(r"s_barrier|buffer_wbl2 sc1$|buffer_inv sc1$|global_atomic_add|"
+                       r"s_waitcnt .*vmcnt\(0\)", x)]
+    at = [i for i, x in enumerate(ops) if x.startswith("global_atomic_add")]
+    assert len(at) == 1, ops
+    before, after = ops[:at[0]], ops[at[0] + 1:]
+    while before[-1].startswith("s_waitcnt"):
+        before.pop()
+    assert before[-1] == "buffer_wbl2 sc1" and before[-2] == "s_barrier", ops
+    assert after[0].startswith("s_waitcnt") and after[1] == "buffer_inv sc1", ops
