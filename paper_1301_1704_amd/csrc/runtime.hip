@@ -18,6 +18,7 @@
 #include <map>
 #include <memory>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "../../include/fmmds.h"
@@ -331,11 +332,14 @@ DevMeta* host_meta() {
 
 // Waits for the scan of `level` (enqueued on s) to have published into h. The
 // stream is asked now and then (ever less often: asking costs the stream a
-// marker), so that a device error ends the wait too.
+// marker), so that a device error ends the wait too. The core is offered to
+// other threads every few microseconds: with more building threads than cores
+// the waiting ones would otherwise hold the cores that the others enqueue from.
 void await_meta(const DevMeta* h, uint32_t level, hipStream_t s) {
   auto there = [&] { return __atomic_load_n(&h->published, __ATOMIC_ACQUIRE) == level; };
   for (uint64_t i = 1, ask = 1u << 13; !there(); ++i) {
-    __builtin_ia32_pause();
+    if (i % 256 == 0) std::this_thread::yield();
+    else __builtin_ia32_pause();
     if (i < ask) continue;
     ask = i + std::min<uint64_t>(i, 1u << 18);
     const hipError_t q = hipStreamQuery(s);
