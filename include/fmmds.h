@@ -130,7 +130,8 @@ typedef struct fmmds_tree {
  * caller's stream, so results are unaffected. The call waits on the host for
  * the finest level's list sizes (with cluster_s > 0 also for the box counts
  * and occupancies after the tables, which set the depth), so it cannot be
- * captured into a graph (the batched form can).
+ * captured into a graph (the batched form can): on a stream under capture it
+ * returns FMMDS_ERR_DEVICE and records nothing.
  */
 fmmds_status fmmds_build(const float* src_xyz, uint32_t n_src, const float* recv_xyz,
                          uint32_t n_recv, const fmmds_options* opt, fmmds_tree** out);

@@ -503,6 +503,16 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     return FMMDS_ERR_ARG;
 
   if (dense && opt->max_level > kDenseMaxLevel) return FMMDS_ERR_ARG;
+  // The build waits for what it enqueues, which a stream under capture never
+  // runs: refused before anything is recorded, so that the capture stays whole
+  // (the null stream cannot be captured).
+  if (opt->stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)opt->stream, &cap) != hipSuccess)
+      (void)hipGetLastError();
+    else if (cap != hipStreamCaptureStatusNone)
+      return FMMDS_ERR_DEVICE;
+  }
   const uint32_t L = opt->max_level;
   const bool key64 = opt->key_bits == 64;
   const bool packed = 3 * L <= 32;

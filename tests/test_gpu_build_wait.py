@@ -59,3 +59,42 @@ def test_waiting_build_leaves_the_core_to_others(F):
     t.free()
     assert wall > 0.05, wall  # it did wait
     assert cpu < 0.25 * wall, (cpu, wall)
+
+
+@pytest.mark.parametrize("entry", ["build", "build_shared", "build_dense", "rebuild"])
+def test_build_on_a_capturing_stream_is_refused(F, entry):
+    """A stream under capture runs nothing, so a build could only wait for ever:
+    the call returns an error before it records anything, the capture goes on and
+    its graph replays, and the next build is whole."""
+    import torch
+    x, y = parity.to_gpu(I.uniform_points(602, 30000)), parity.to_gpu(I.uniform_points(603, 20000))
+    prev = F.build(x, y, max_level=5)
+    torch.cuda.synchronize()
+    call = {"build": lambda s: F.build(x, y, max_level=5, stream=s),
+            "build_shared": lambda s: F.build(x, None, max_level=5, stream=s),
+            "build_dense": lambda s: F.build_dense(x, y, max_level=5, stream=s),
+            "rebuild": lambda s: F.rebuild(prev, x, y, in_prev_order=True, stream=s)}[entry]
+    v = torch.zeros(1000, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        g.capture_begin()
+        v.add_(1.0)
+        with pytest.raises(F.FmmdsError) as e:
+            call(s)
+        v.add_(1.0)
+        g.capture_end()
+    assert e.value.status == F.ERR_DEVICE
+    for k in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.all(v == 2.0 * (k + 1))
+        t = F.build(x, y, max_level=5)
+        torch.cuda.synchronize()
+        for l in range(2, 6):
+            for kind in (2, 4):
+                for a, b in zip(t.host_list(kind, l), prev.host_list(kind, l)):
+                    assert a.tobytes() == b.tobytes()
+        t.free()
+    prev.free()
