@@ -31,19 +31,22 @@
 
 namespace fmmds {
 
-// One term of the sum, q / |x - y|, zero for coincident points, added to acc.
+// One term of the sum, q / |x - y|, added to acc; a coincident pair adds nothing
+// whatever its charge (infinite or NaN): its charge is replaced by zero and its
+// distance by one whose reciprocal is finite.
 // Coordinates come scaled by kNearScale (exactly), so that the square of the
 // smallest distance whose square FP32 can hold is a normal number, as the
 // reciprocal square root instruction needs; the sums are scaled back at the
-// end. A term takes 10 instructions; with the library's rsqrtf, which scales
+// end. A term takes 11 instructions; with the library's rsqrtf, which scales
 // its argument each time, it took 16 (3.6M uniform points at 110 per box, bound
 // by these: 4406 -> 3252 us).
 constexpr float kNearScale = 4096.0f;
+constexpr float kNearMin = 1.17549435e-38f;  // the smallest normal number
 __device__ __forceinline__ void add_term(float& acc, const float4 x, float yx, float yy, float yz) {
   const float dx = x.x - yx, dy = x.y - yy, dz = x.z - yz;
   const float r2 = dx * dx + dy * dy + dz * dz;
-  const float inv = __builtin_amdgcn_rsqf(r2);
-  acc += x.w * (r2 >= 1.17549435e-38f ? inv : 0.0f);
+  const float q = r2 >= kNearMin ? x.w : 0.0f;
+  acc += q * __builtin_amdgcn_rsqf(fmaxf(r2, kNearMin));
 }
 
 // The sources as records, and the box of every W-th receiver (the first of
