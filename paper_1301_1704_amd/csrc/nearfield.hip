@@ -36,8 +36,9 @@ namespace fmmds {
 // distance by one whose reciprocal is finite.
 // Coordinates come scaled by kNearScale (exactly), so that the square of the
 // smallest distance whose square FP32 can hold is a normal number, as the
-// reciprocal square root instruction needs; the sums are scaled back at the
-// end. A term takes 11 instructions; with the library's rsqrtf, which scales
+// reciprocal square root instruction needs; the reciprocal is scaled back before
+// the charge meets it, so that a term is subnormal or infinite only where q / r
+// itself is. A term takes 12 instructions; with the library's rsqrtf, which scales
 // its argument each time, it took 16 (3.6M uniform points at 110 per box, bound
 // by these: 4406 -> 3252 us).
 constexpr float kNearScale = 4096.0f;
@@ -46,7 +47,7 @@ __device__ __forceinline__ void add_term(float& acc, const float4 x, float yx, f
   const float dx = x.x - yx, dy = x.y - yy, dz = x.z - yz;
   const float r2 = dx * dx + dy * dy + dz * dz;
   const float q = r2 >= kNearMin ? x.w : 0.0f;
-  acc += q * __builtin_amdgcn_rsqf(fmaxf(r2, kNearMin));
+  acc += q * (kNearScale * __builtin_amdgcn_rsqf(fmaxf(r2, kNearMin)));
 }
 
 // The sources as records, and the box of every W-th receiver (the first of
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(256, 5) void k_near_field(
   float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 #pragma unroll
   for (uint32_t o = W; o < 64u; o <<= 1) sum += __shfl_xor(sum, (int)o, 64);
-  if (mine && part == 0u) phi[perm] = kNearScale * (sum + whole);
+  if (mine && part == 0u) phi[perm] = sum + whole;
   if (n_pairs) {
     const uint64_t all = wave_sum_u64(pts);
     if (lane == 0 && all) atomicAdd(n_pairs, (unsigned long long)all);

@@ -1,6 +1,8 @@
-"""The near-field sum with infinite and NaN charges, against sums in 64 bits over
-the pairs themselves. Points lie in the middle of the cube, where the 2 x 2 x 2
-boxes of level 2 are all neighbors, so every source counts for every receiver."""
+"""The near-field sum with charges at the ends of their range: infinite and NaN
+ones, and ones so small or so large that scaled terms would leave FP32's normal
+range. Against sums in 64 bits over the pairs themselves. Points lie in the
+middle of the cube, where the 2 x 2 x 2 boxes of level 2 are all neighbors, so
+every source counts for every receiver."""
 import os
 
 import numpy as np
@@ -77,3 +79,19 @@ def test_charge_that_is_not_finite_spoils_other_pairs_only(F, n, m, value, no_al
             ref, mag = _sums(src, src, q)
         assert np.isfinite(got).sum() == 1
         assert abs(got[at] - ref[at]) <= (n + 8) * 2.0 ** -24 * mag[at]
+
+
+@pytest.mark.parametrize("no_alloc", [False, True])
+@pytest.mark.parametrize("scale", [4e-38, 1e-36, 1e-30, 1.0, 1e30, 3e35, 1e37])
+@pytest.mark.parametrize("n,m", SHAPES)
+def test_charges_of_any_size_keep_their_bits(F, n, m, scale, no_alloc):
+    """Every term and sum is a normal number, so the bound is the plain one. (A
+    term scaled by 4096 would be subnormal at the small end, a charge so scaled
+    infinite at the large one.)"""
+    src, recv = _points(n, 4), _points(m, 5)
+    # the largest sums stay in range: terms of 2 to 100 times the charge here
+    top = scale if scale < 1e30 else scale / n
+    q = (top * np.random.RandomState(6).uniform(1, 1.5, n)).astype(np.float32)
+    ref, mag = _sums(src, recv, q)
+    got = _run(F, src, recv, q, no_alloc).astype(np.float64)
+    assert np.all(np.abs(got - ref) <= (n + 8) * 2.0 ** -24 * mag)
