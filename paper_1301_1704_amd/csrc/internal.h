@@ -313,13 +313,13 @@ void launch_partition(bool key64, const void* rkey, const uint32_t* rbegin, uint
 void launch_box_types(bool key64, const BoxTypes& a, uint32_t depth, hipStream_t s);
 
 // ---- nearfield.hip
-uint64_t near_field_waves(uint32_t n_recv);  // entries of wave_box
+uint64_t near_field_table(uint32_t n_recv);  // entries of wave_box
 // Bytes of the fixed scratch array of the near-field entry point that
 // allocates nothing, and its device address on the current device (looked up
 // once per device). The status is an fmmds_status.
 constexpr size_t kNearStaticBytes = FMMDS_NEAR_FIELD_STATIC_BYTES;
 fmmds_status near_field_static_scratch(void** out);
-// src: n_src records of scratch, wave_box: near_field_waves(n_recv) words of it.
+// src: n_src records of scratch, wave_box: near_field_table(n_recv) words of it.
 void launch_near_field(const float* sxyz, const uint32_t* sperm, const float* charges,
                        uint32_t n_src, float4* src, uint32_t n_rbox, uint32_t n_recv,
                        const uint32_t* rbegin, const float* rxyz, const uint32_t* rperm,

@@ -50,22 +50,26 @@ __device__ __forceinline__ void add_term(float& acc, const float4 x, float yx, f
   acc += q * (kNearScale * __builtin_amdgcn_rsqf(fmaxf(r2, kNearMin)));
 }
 
-// The sources as records, and the box of every W-th receiver (the first of
-// each wave of the sum; w_log2 = log2 W).
+// The sources as records, and the box of every T-th receiver (t_log2 = log2 T).
+// T is the receivers per wave W, so that each wave finds its first box there, but
+// at least 8, so that the table fits the scratch that the header promises (8 bytes
+// per 9 receivers): waves of 4 go on from the box starts between, which they load
+// anyway.
+constexpr uint32_t kNearTable = 8;
 __global__ __launch_bounds__(256) void k_pack_sources(
     const float* __restrict__ sxyz, const uint32_t* __restrict__ sperm,
     const float* __restrict__ charges, uint32_t n, float4* __restrict__ out,
-    const uint32_t* __restrict__ rbegin, uint32_t n_rbox, uint32_t w_log2,
+    const uint32_t* __restrict__ rbegin, uint32_t n_rbox, uint32_t t_log2,
     uint32_t* __restrict__ wave_box) {
   for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < n; i += gridDim.x * 256ull) {
     const float q = charges ? charges[sperm[i]] : 1.0f;
     out[i] = make_float4(kNearScale * sxyz[3 * i], kNearScale * sxyz[3 * i + 1],
                          kNearScale * sxyz[3 * i + 2], q);
   }
-  const uint32_t W = 1u << w_log2;
+  const uint32_t T = 1u << t_log2;
   for (uint64_t b = blockIdx.x * 256ull + threadIdx.x; b < n_rbox; b += gridDim.x * 256ull) {
     const uint32_t k0 = rbegin[b], k1 = rbegin[b + 1];
-    for (uint64_t t = ((uint64_t)k0 + W - 1u) >> w_log2; t << w_log2 < k1; ++t)
+    for (uint64_t t = ((uint64_t)k0 + T - 1u) >> t_log2; t << t_log2 < k1; ++t)
       wave_box[t] = (uint32_t)b;
   }
 }
@@ -176,13 +180,14 @@ __global__ __launch_bounds__(256, 5) void k_near_field(
   const uint64_t k0 = W * t;
   if (k0 >= n_recv) return;  // whole wave
   // Box of each receiver: the wave's first one plus the box starts up to it.
-  const uint32_t b0 = wave_box[t];
+  constexpr uint32_t T = W < kNearTable ? kNearTable : W;
+  const uint32_t bt = wave_box[k0 / T];
   S.start[lane] = 0;
   wave_fence();
-  if (lane < W && b0 + 1 + (uint64_t)lane < n_rbox) {
-    const uint32_t st = rbegin[b0 + 1 + lane];
-    if (st < k0 + W) S.start[st - (uint32_t)k0] = 1;
-  }
+  uint32_t st = 0;  // box starts past the table's receiver (none: 0, never past k0)
+  if (lane < T && bt + 1 + (uint64_t)lane < n_rbox) st = rbegin[bt + 1 + lane];
+  const uint32_t b0 = bt + (T > W ? (uint32_t)__popcll(__ballot(st != 0 && st <= k0)) : 0u);
+  if (st > k0 && st < k0 + W) S.start[st - (uint32_t)k0] = 1;
   wave_fence();
   const uint64_t starts = __ballot(lane < W && S.start[lane] != 0);
   const uint32_t jb = (uint32_t)__popcll(starts & ((2ull << rec) - 1ull));
@@ -365,9 +370,9 @@ uint32_t near_field_w_log2(uint32_t n_recv) {
   return l;
 }
 
-uint64_t near_field_waves(uint32_t n_recv) {
-  const uint32_t l = near_field_w_log2(n_recv);
-  return ((uint64_t)n_recv + (1u << l) - 1u) >> l;
+uint64_t near_field_table(uint32_t n_recv) {
+  const uint32_t T = std::max(1u << near_field_w_log2(n_recv), kNearTable);
+  return ((uint64_t)n_recv + T - 1u) / T;
 }
 
 void launch_near_field(const float* sxyz, const uint32_t* sperm, const float* charges,
@@ -380,8 +385,9 @@ void launch_near_field(const float* sxyz, const uint32_t* sperm, const float* ch
   const uint32_t pack = std::max<uint32_t>(
       1, std::min<uint32_t>(div_up(std::max(n_src, n_rbox), 256), 8192));
   hipLaunchKernelGGL(k_pack_sources, dim3(pack), dim3(256), 0, s, sxyz, sperm, charges, n_src, src,
-                     rbegin, n_rbox, l, wave_box);
-  const dim3 grid(div_up(near_field_waves(n_recv), 4));
+                     rbegin, n_rbox, std::max(l, 3u), wave_box);
+  static_assert(kNearTable == 1u << 3, "the table's step");
+  const dim3 grid(div_up(n_recv, 4ull << l));
 #define FMMDS_NEAR(W)                                                                           \
   hipLaunchKernelGGL(k_near_field<W>, grid, dim3(256), 0, s, n_recv, rbegin, n_rbox, rxyz,      \
                      rperm, e2_off, e2_ent, sbegin, src, phi, n_pairs, wave_box)

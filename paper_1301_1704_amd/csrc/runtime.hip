@@ -1993,15 +1993,14 @@ fmmds_status box_types(const fmmds_tree* t, uint32_t l_par, const uint32_t* owne
   return hipGetLastError() == hipSuccess ? FMMDS_OK : FMMDS_ERR_DEVICE;
 }
 
-// Bytes of the near-field scratch: packed sources, then the first box of each
-// wave of receivers, for which 8 bytes per 9 receivers and 512 are set aside
-// (the header's bound on what the fixed scratch takes).
+// Bytes of the near-field scratch: packed sources, then the boxes that the waves
+// of receivers start from (at most a word per 8 receivers), for which 8 bytes per
+// 9 receivers and 256 are set aside, as the header promises.
 struct NearScratch {
   size_t src_b, total;
   explicit NearScratch(const fmmds_tree* t)
       : src_b(round_up((size_t)t->n_src * 16, 256)),
-        total(src_b + std::max<size_t>(round_up(near_field_waves(t->n_recv) * 4, 256),
-                                       round_up(((size_t)t->n_recv / 9 + 1) * 8, 256) + 256)) {}
+        total(src_b + round_up(((size_t)t->n_recv / 9 + 1) * 8, 256) + 256) {}
 };
 
 void near_field_launch(const fmmds_tree* t, const NearScratch& ns, char* scratch,
