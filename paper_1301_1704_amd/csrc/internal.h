@@ -128,6 +128,11 @@ void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* 
                    const TabLevels& T, uint32_t* perm, float* sorted_xyz, uint32_t* n_boxes,
                    uint32_t node_cap, hipStream_t s, int phase,
                    const uint64_t* set_off = nullptr, uint32_t set_shift = 0);
+// Phase 3 alone, for the boxes of `levels` levels from `first` on: the records of
+// levels first + 1 .. first + levels, and the second halves of those of level
+// first, as far as T has space for them.
+void launch_nodes(bool key64, const TabLevels& T, uint32_t first, uint32_t levels,
+                  const uint32_t* n_boxes, uint32_t node_cap, hipStream_t s);
 struct OccLevels {
   const uint32_t* begin[kMaxLevel + 1];
 };

@@ -489,9 +489,16 @@ uint32_t index_bits(uint32_t n) { return n <= 2 ? 1u : 32u - (uint32_t)__builtin
 
 // prev: with a previous tree, the order is rebuilt incrementally from it
 // (the coordinates are given in prev's sorted order).
-fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, uint32_t n_recv,
-                   const fmmds_options* opt, fmmds_tree** out,
-                   const fmmds_tree* prev = nullptr, bool dense = false) {
+//
+// lean: the temporaries in the least memory. The elements are sorted, never the
+// points, in tiles of which a set has few; the list kernels' records are written
+// level by level, each over the last, into the sorted elements' space, and every
+// level counts its own lists (counting the next one's while filling takes the
+// records of two levels). Otherwise `roomy` tells whether this build takes more
+// than that.
+fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_xyz,
+                        uint32_t n_recv, const fmmds_options* opt, fmmds_tree** out,
+                        const fmmds_tree* prev, bool dense, bool lean, bool* roomy) {
   const bool shared = recv_xyz == nullptr;
   if (shared) n_recv = n_src;
   if (!src_xyz || !opt || n_src == 0 || n_recv == 0 || n_src >= 0xFFFFFFFFu ||
@@ -569,17 +576,25 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     const bool plain = !dense && !prev;
     auto sort_small = [&](int s) { return plain && packed && sets[s].n <= kSortSmall; };
     auto sort_records = [&](int s) {
-      return plain && packed && sort_by_records(sets[s].n, n_pass);
+      return plain && packed && !lean && sort_by_records(sets[s].n, n_pass);
+    };
+    auto tile_items = [&](uint32_t n, bool movers) {
+      return !lean ? sort_items(n) : packed && !movers ? kSortWide : kSortItemsDefault;
     };
     size_t words = 0, tickets = 0;
     for (int s = 0; s < nsets; ++s) {
       const uint32_t n = sets[s].n;
       const uint32_t np = inc[s] ? inc_pass[s] : n_pass;
       // status words of each sort pass, for the tile size that pass runs with
-      const uint32_t tiles = dense    ? sort_tiles(n, kSortItemsDefault)
+      const uint32_t tiles = dense             ? sort_tiles(n, kSortItemsDefault)
+                             : sort_small(s)   ? 0
                              : sort_records(s) ? record_tiles(n)
-                             : inc[s] ? sort_tiles_max(n)  // (the movers: any number of them)
-                                      : sort_tiles(n, sort_items(n));
+                             : !inc[s]         ? sort_tiles(n, tile_items(n, false))
+                             : lean            ? sort_tiles(n, kSortItemsDefault)
+                                               : sort_tiles_max(n);  // (any number of movers)
+      if (sort_records(s) ||
+          tiles > sort_tiles(n, packed && !dense && !inc[s] ? kSortWide : kSortItemsDefault))
+        *roomy = true;
       words += (size_t)np * tiles * 256 + 2 * div_up(n, kCompTile);
       tickets += np + 2 + L;
       if (dense) {
@@ -744,13 +759,21 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
     }
     // The list kernels' records are written after the last read of the sorted
     // elements: in their space where they fit (two 8-byte buffers a point).
+    bool by_level = false;  // every level's records over the last one's
     for (int s = 0; !dense && s < nsets; ++s) {
       size_t nodes = 0;
       for (uint32_t l = 1; l < L; ++l) nodes += sets[s].lv[l].cap;
-      uint4* q = nodes <= n_max ? (uint4*)(s == 1 ? sb1 : sb).k[0] : temps.get<uint4>(nodes);
+      if (nodes > n_max) *roomy = true;
+      by_level |= lean && nodes > n_max;
+    }
+    for (int s = 0; !dense && s < nsets; ++s) {
+      size_t nodes = 0;
+      for (uint32_t l = 1; l < L; ++l) nodes += sets[s].lv[l].cap;
+      uint4* q = by_level || nodes <= n_max ? (uint4*)(s == 1 ? sb1 : sb).k[0]
+                                            : temps.get<uint4>(nodes);
       for (uint32_t l = 1; l < L; ++l) {
         sets[s].lv[l].node = q;
-        q += sets[s].lv[l].cap;
+        if (!by_level) q += sets[s].lv[l].cap;
       }
     }
     // keygen's per-block digit-count rows, per set
@@ -773,6 +796,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       Dn.key = temps.get<uint32_t>(sets[s].n);
       Dn.rank = temps.get<uint32_t>(sets[s].n);
     }
+    TabLevels tabs[2] = {};
     hipStream_t st1 = st;
     // (profiling with on == 2 keeps both chains on the build stream, so that
     // every kernel's event-measured duration is its own)
@@ -864,11 +888,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         P.run(K_DIGITS, (double)np * 2048, [&] { launch_digit_offsets(h, g, np, st); });
         for (uint32_t p = 0; p < np && nm > 0; ++p) {
           const int a = p & 1, b = a ^ 1;
-          uint64_t* stw = sa.take_words((size_t)sort_tiles(nm, sort_items(nm)) * 256);
+          uint64_t* stw = sa.take_words((size_t)sort_tiles(nm, tile_items(nm, true)) * 256);
           uint32_t* tk = sa.take_ticket();
           P.run(K_SORT, (double)nm * 24, [&] {
             launch_sort_pass(false, mk[a], mk[b], mv[a], mv[b], nm, 8 * p, g + p * 256, stw, tk,
-                             st, sort_items(nm));
+                             st, tile_items(nm, true));
           });
         }
         const int mf = nm > 0 ? (int)(np & 1) : 0;
@@ -913,11 +937,11 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         for (uint32_t p = 0; p < n_left; ++p) {
           const int a = p & 1, b = a ^ 1;
           const uint32_t shift = (packed ? 32 : 0) + 8 * p;
-          uint64_t* stw = sa.take_words((size_t)sort_tiles(n, sort_items(n)) * 256);
+          uint64_t* stw = sa.take_words((size_t)sort_tiles(n, tile_items(n, false)) * 256);
           uint32_t* tk = sa.take_ticket();
           P.run(K_SORT, (double)n * (packed ? 16 : 24), [&] {
             launch_sort_pass(packed, sb.k[a], sb.k[b], sb.v[a], sb.v[b], n, shift, g + p * 256,
-                             stw, tk, st, sort_items(n));
+                             stw, tk, st, tile_items(n, false));
           });
         }
         const int fin = sort_records(s) ? (int)((n_pass - 1) & 1) : (int)(n_left & 1);
@@ -927,7 +951,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
 
       // ---- every level's tables from the sorted points
       {
-        TabLevels T{};
+        TabLevels& T = tabs[s];
         for (uint32_t l = 0; l <= L; ++l) {
           T.key[l] = S.lv[l].key;
           T.begin[l] = S.lv[l].begin;
@@ -951,7 +975,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         P.run(K_TSCAN, 2 * cnt_b, [&] { tab(1); });
         P.run(K_LEAF, (double)n * (elem_b + 4 + (leaf_xyz ? 12 + 12 : 0)) + cnt_b,
               [&] { tab(2); }, s, (int)L);
-        P.run(K_LEVEL, 0.0, [&] { tab(3); }, s, -1);
+        if (!by_level) P.run(K_LEVEL, 0.0, [&] { tab(3); }, s, -1);
       }
       if (opt->cluster_s > 0) {
         OccLevels lv{};
@@ -1109,7 +1133,16 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       ListBufs& LB = impl->lists[l];
       // (the bytes of the count, scan and fill launches follow from the box
       // counts and list sizes, added once known: see P.finish below)
-      // level 2 only: the fill of each level writes the next level's counts
+      // level 2 only (without by_level): the fill of each level writes the next
+      // level's counts
+      for (int s = 0; by_level && s < nsets; ++s) {
+        TabLevels T = tabs[s];
+        for (uint32_t m = 0; m <= L; ++m)
+          if (m != l - 1) T.node[m] = nullptr;
+        P.run(K_LEVEL, 0.0, [&] {
+          launch_nodes(key64, T, l - 2, 1, meta->n_boxes[s], lcap[s][l - 2], st);
+        }, s, (int)l - 1);
+      }
       if (dense)
         P.run(K_DLIST, 0.0, [&] {
           launch_dense_lists(key64, false, l, nb[rs][l - 1], sets[rs].lv[l - 1].key,
@@ -1119,7 +1152,10 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
         });
       else if (l == 2)
         P.run(K_COUNT, 0.0, [&] { launch_list_first(a, scan_args(l), st); }, kListSet, (int)l);
-      if (dense || (l > 2 && nr > kScanSmall)) {
+      else if (by_level)
+        P.run(K_COUNT, 0.0, [&] { launch_list_count(a, cnt, cnt + round_up(nr, 4), st); },
+              kListSet, (int)l);
+      if (dense || (l > 2 && (nr > kScanSmall || by_level))) {
         uint64_t* st2 = la.take_words(scan_tiles(nr));
         uint64_t* st4 = la.take_words(scan_tiles(nr));
         uint32_t* tk = la.take_ticket();
@@ -1149,7 +1185,7 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
       }
       ScanArgs next{};
       uint32_t* done = nullptr;
-      if (l < D) {  // the next level's counts, and where they are few their scan
+      if (l < D && !by_level) {  // the next level's counts, and where they are few their scan
         next = scan_args(l + 1);
         a.recv_node_cur = sets[rs].lv[l].node;
         a.cnt2_next = cnt;
@@ -1198,8 +1234,9 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
           b += (double)c[l] * (4 + (l >= 1 ? 16 : 0)) + 4 + (double)c[l + 1] * ksz;
         return b;
       }
-      if (r.cls == K_LEVEL)
-        return (double)c[r.level + 1] * (ksz + 4 + 4) + (double)c[r.level] * (ksz + 4 + 4 + 1);
+      if (r.cls == K_LEVEL)  // one level's alone, their first 8 bytes
+        return (double)c[r.level - 1] * 4 + (double)c[r.level] * (4 + ksz + 8) +
+               (double)c[r.level + 1] * ksz;
       if (r.cls == K_MAXOCC) {
         double b = 0;
         for (uint32_t l = 2; l <= L; ++l) b += (double)(c[l] + 1) * 4;
@@ -1256,6 +1293,15 @@ fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, 
   return FMMDS_OK;
 }
 
+fmmds_status build(const float* src_xyz, uint32_t n_src, const float* recv_xyz, uint32_t n_recv,
+                   const fmmds_options* opt, fmmds_tree** out, const fmmds_tree* prev = nullptr,
+                   bool dense = false) {
+  bool roomy = false;
+  const fmmds_status s =
+      build_plan(src_xyz, n_src, recv_xyz, n_recv, opt, out, prev, dense, false, &roomy);
+  if (s != FMMDS_ERR_NOMEM || !roomy) return s;
+  return build_plan(src_xyz, n_src, recv_xyz, n_recv, opt, out, prev, dense, true, &roomy);
+}
 
 // ---------------------------------------------------------------------------
 // Batched form (fmmds_batch_*).

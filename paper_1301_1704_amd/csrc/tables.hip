@@ -370,7 +370,7 @@ __device__ __forceinline__ void tab_nodes(const TabLevels& T, uint32_t l, uint32
       *(uint2*)&node1[c] = make_uint2(g0, m | (k & 63u) << 8);
       grid |= node_grid(k & 7u, m);
     }
-    if (l == 0) continue;  // (level 0 has no record)
+    if (!node) continue;
     uint32_t lo = (uint32_t)grid, hi = (uint32_t)(grid >> 32);
 #pragma unroll
     for (int o = 1; o < (int)G; o <<= 1) {
@@ -382,11 +382,19 @@ __device__ __forceinline__ void tab_nodes(const TabLevels& T, uint32_t l, uint32
 }
 
 template <typename KeyT>
-__global__ __launch_bounds__(256) void k_tab_nodes(TabLevels T, const uint32_t* __restrict__ n_boxes) {
-  const uint32_t l = blockIdx.y;
+__global__ __launch_bounds__(256) void k_tab_nodes(TabLevels T, uint32_t first,
+                                                   const uint32_t* __restrict__ n_boxes) {
+  const uint32_t l = first + blockIdx.y;
   const uint32_t nl = n_boxes[l];
   if (n_boxes[l + 1] < 3ull * nl) tab_nodes<KeyT, 1>(T, l, nl);
   else tab_nodes<KeyT, 8>(T, l, nl);
+}
+
+void launch_nodes(bool key64, const TabLevels& T, uint32_t first, uint32_t levels,
+                  const uint32_t* n_boxes, uint32_t node_cap, hipStream_t s) {
+  const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(div_up(node_cap, 32), 2048)), levels);
+  if (key64) hipLaunchKernelGGL(k_tab_nodes<uint64_t>, grid, dim3(256), 0, s, T, first, n_boxes);
+  else hipLaunchKernelGGL(k_tab_nodes<uint32_t>, grid, dim3(256), 0, s, T, first, n_boxes);
 }
 
 uint32_t tab_tiles(uint32_t n) { return div_up(n, kCompTile); }
@@ -423,9 +431,7 @@ void launch_tables(bool packed, bool key64, const uint64_t* sk, const uint32_t* 
 #undef FMMDS_TABW
 #undef FMMDS_TABWB
   } else if (L >= 2) {
-    const dim3 grid(std::max<uint32_t>(1, std::min<uint32_t>(div_up(node_cap, 32), 2048)), L - 1);
-    if (key64) hipLaunchKernelGGL(k_tab_nodes<uint64_t>, grid, dim3(256), 0, s, T, n_boxes);
-    else hipLaunchKernelGGL(k_tab_nodes<uint32_t>, grid, dim3(256), 0, s, T, n_boxes);
+    launch_nodes(key64, T, 0, L - 1, n_boxes, node_cap, s);
   }
 }
 
