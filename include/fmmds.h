@@ -253,11 +253,10 @@ fmmds_status fmmds_batch_footprint(const uint64_t* set_offsets, const uint8_t* l
                                    uint32_t n_sets, uint64_t* bytes);
 /* Device bytes the batch holds. */
 uint64_t fmmds_batch_bytes(const fmmds_batch* b);
-/* Sort tile size the batch uses, in units of 256 elements: 8, 12 or 16
- * or 32 (tiles of 2048, 3072, 4096 or 8192 elements). A graph capture times the four and keeps the fastest; the
- * environment variable FMMDS_BATCH_SORT_ITEMS, read by fmmds_batch_create,
- * fixes it instead (8, 12, 16, or 32 when max(1, ceil(log2 n_sets)) plus 3
- * times the deepest level is at most 32; other values are ignored). */
+/* Sort tile size the batch uses, in units of 256 elements: 8, 12, 16 or 32
+ * (tiles of 2048, 3072, 4096 or 8192 elements). A graph capture times the four
+ * and keeps the fastest; the environment variable FMMDS_BATCH_SORT_ITEMS, read by
+ * fmmds_batch_create, fixes one of them instead (other values are ignored). */
 uint32_t fmmds_batch_sort_items(const fmmds_batch* b);
 void fmmds_batch_free(fmmds_batch* b);
 

@@ -1547,7 +1547,7 @@ int batch_autotune(BatchImpl& B, const float* xyz) {
   ck(hipEventCreate(&e1));
   int best = kSortItemsDefault;
   float best_ms = 1e30f;
-  for (int items : {8, 12, 16, kSortWide}) {
+  for (int items : kTileItems) {
     float total = 0;
     for (int rep = 0; rep < 2; ++rep) {
       StatusArena sa;
@@ -1779,7 +1779,7 @@ fmmds_status batch_create(const uint64_t* set_offsets, const uint8_t* levels, ui
     B->lev.assign(levels, levels + n_sets);
     if (const char* e = std::getenv("FMMDS_BATCH_SORT_ITEMS")) {
       const int v = std::atoi(e);
-      if (v == 8 || v == 12 || v == 16 || (v == kSortWide && B->packed)) {
+      if (std::find(std::begin(kTileItems), std::end(kTileItems), v) != std::end(kTileItems)) {
         B->items = v;
         B->items_fixed = true;
       }
