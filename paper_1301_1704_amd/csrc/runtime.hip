@@ -1198,27 +1198,28 @@ fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_
     }
     for (uint32_t l = 2; l <= D; ++l) impl->n_recv_boxes[l] = nb[rs][l];
 
-    // Box-count-dependent bytes: leaf keys + bookmarks; a coarser level reads
-    // the finer keys and bookmarks and writes keys, bookmarks, first children,
-    // masks and the finer level's parents; the occupancy pass reads bookmarks.
+    // Box-count-dependent bytes: every array that a launch needs, once in and once
+    // out. List kernels read the parent level's records: a receiver's first 8
+    // bytes, a source's 16 where the next level is counted too, else 8.
     P.finish([&](const Prof::Rec& r) -> double {
       if (r.set == kListSet) {
         const uint32_t l = (uint32_t)r.level;
-        const double nr = nb[rs][l];
-        if (r.cls == K_SCAN) return nr * 16 + 8;  // two counts in, two offsets out
-        // receiver key + parent in, two counts out; the parent lists and the
-        // parent-level source keys, masks and first children read once
-        const double side = (double)nb[rs][l - 1] * (ksz + 1 + 4 + 8) +
-                            (double)nb[0][l - 1] * (ksz + 1 + 4);
-        if (r.cls == K_COUNT) return side + nr * 8;
-        // a fill: also its entries and the parent level's E2 list read, and
-        // below D the next level's counts (masks and first children in, two
-        // counts out)
+        const double nr = nb[rs][l], scan = 16 * nr + 8;  // two counts in, two offsets out
+        if (r.cls == K_SCAN) return scan;
+        const bool next = r.cls == K_FILL && l < D && !by_level;
+        double side = 8.0 * nb[rs][l - 1] + (next ? 16.0 : 8.0) * nb[0][l - 1];
+        if (l >= 3) side += 4.0 * nb[rs][l - 1] + 4 + 4.0 * (double)impl->lists[l - 1].total[0];
+        if (r.cls == K_COUNT) return side + (l == 2 ? 8 * nr + 8 : 8 * nr);  // offsets / counts
+        // a fill: where its parents' lists start, and the entries; below D the
+        // receivers' own records and the next level's counts, scanned where few
         const ListBufs& LB = impl->lists[l];
-        const double e2up = l - 1 >= 2 ? (double)impl->lists[l - 1].total[0] : 0.0;
-        const double next_b =
-            l < D ? nr * 5 + (double)nb[0][l] + (double)nb[rs][l + 1] * 8 : 0.0;
-        return side + nr * 8 + next_b + 4.0 * (double)(LB.total[0] + LB.total[1]) + 4.0 * e2up;
+        side += 8.0 * nb[rs][l - 1] + 4.0 * (double)(LB.total[0] + LB.total[1]);
+        if (next) {
+          const double nn = nb[rs][l + 1];
+          side += 8 * nr + 8 * nn;
+          if (lcap[rs][l + 1] <= kScanSmall) side += 16 * nn + 8;
+        }
+        return side;
       }
       if (r.set < 0) return 0.0;
       const uint32_t* c = nb[r.set == 0 ? 0 : rs];
@@ -1228,10 +1229,10 @@ fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_
           b += (double)c[l] * (ksz + 4 + (l >= 1 ? 4 : 0) + (l < L ? 4 : 0)) + 4 + (l < L ? 4 : 0);
         return b;
       }
-      if (r.cls == K_LEVEL && r.level < 0) {  // nodes: first children and keys in, 16 bytes out
+      if (r.cls == K_LEVEL && r.level < 0) {  // records: first children and keys in, 16 bytes out
         double b = 0;
         for (uint32_t l = 0; l < L; ++l)
-          b += (double)c[l] * (4 + (l >= 1 ? 16 : 0)) + 4 + (double)c[l + 1] * ksz;
+          b += (double)c[l] * (4 + (l == 0 ? 0 : l + 1 < L ? 16 : 8)) + 4 + (double)c[l + 1] * ksz;
         return b;
       }
       if (r.cls == K_LEVEL)  // one level's alone, their first 8 bytes
