@@ -133,8 +133,9 @@ typedef struct fmmds_tree {
  * captured into a graph (the batched form can): on a stream under capture it
  * returns FMMDS_ERR_DEVICE and records nothing.
  * Temporary device memory, returned before the call returns: per set 32 bytes a
- * point where the points themselves are sorted (max_level <= 10, more than 2^20
- * points), else 16 (24 with max_level > 10); 16 bytes a box of levels 1 ..
+ * point where the points themselves are sorted (more than 2^20 points and
+ * max_level <= 8, or two sets of more than 2^22 and max_level <= 10), else 16 (24
+ * with max_level > 10); 16 bytes a box of levels 1 ..
  * max_level - 1, at most the points each, where they exceed the points; and a few
  * bytes a point of counts. When an allocation fails the build is made again with
  * 16 (24) bytes a point and no records beside them, more slowly on deep levels;

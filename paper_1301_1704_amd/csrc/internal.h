@@ -70,7 +70,7 @@ void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass
                        uint32_t* err, hipStream_t s);
 // The passes over the points themselves (packed elements): the first (rin null)
 // reads xyz, the last (kout) writes the sorted coordinates and elements.
-bool sort_by_records(uint32_t n, uint32_t n_pass);
+bool sort_by_records(uint32_t n, uint32_t n_pass, bool two_sets);
 uint32_t record_tiles(uint32_t n);
 void launch_sort_records(const float* xyz, const uint4* rin, uint4* rout, float* sorted_xyz,
                          uint64_t* kout, uint32_t n, uint32_t L, uint32_t shift,

@@ -576,7 +576,7 @@ fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_
     const bool plain = !dense && !prev;
     auto sort_small = [&](int s) { return plain && packed && sets[s].n <= kSortSmall; };
     auto sort_records = [&](int s) {
-      return plain && packed && !lean && sort_by_records(sets[s].n, n_pass);
+      return plain && packed && !lean && sort_by_records(sets[s].n, n_pass, nsets == 2);
     };
     auto tile_items = [&](uint32_t n, bool movers) {
       return !lean ? sort_items(n) : packed && !movers ? kSortWide : kSortItemsDefault;

@@ -465,14 +465,18 @@ void launch_sort_small(const float* xyz, uint32_t n, uint32_t L, uint32_t n_pass
 // CU the build of 2 x 2^24 points took 3835 us, with these 3790 (by elements
 // 4005).
 // ---------------------------------------------------------------------------
-// Builds (us, by records / by elements): one set at level 6 of 2^20 points 249 /
-// 244, 2^21 288 / 297, 2^24 831 / 921; at level 8 2^20 604 / 597, 2^21 977 / 993,
-// 2^24 3103 / 3180. Four passes (levels 9 and 10) move so much more that it pays
-// later: 3 * 2^20 points 2941 / 2924, 2^24 8506 / 8504, two sets of 2^24
-// clustered points at level 10 3357 / 3450.
+// Builds (us, by records / by elements). Three passes, one set at level 6 of 2^20
+// points 249 / 244, 2^21 288 / 297, 2^24 831 / 921; at level 8 2^20 604 / 597, 2^21
+// 977 / 993, 2^24 3103 / 3180. Four passes (levels 9 and 10) move so much more that
+// one set gains nothing for twice the memory: at level 10 uniform 3 * 2^20 points
+// 2871 / 2864, 2^23 6193 / 6218, 2^24 11896 / 11914, clustered 2^23 1741 / 1761, 2^24
+// 2571 / 2589. Two sets, whose chains of passes share the chip, gain a little:
+// clustered at level 10 2 x 2^22 and a quarter more 1655 / 1647, 2 x 2^23 2183 /
+// 2199, 2 x 3 * 2^22 2801 / 2856, 2 x 2^24 3359 / 3450.
 constexpr uint32_t kRecMin = 1u << 20, kRecMin4 = 1u << 22;
-bool sort_by_records(uint32_t n, uint32_t n_pass) {
-  return n_pass >= 2 && n > (n_pass <= 3 ? kRecMin : kRecMin4);
+bool sort_by_records(uint32_t n, uint32_t n_pass, bool two_sets) {
+  if (n_pass < 2) return false;
+  return n_pass <= 3 ? n > kRecMin : two_sets && n > kRecMin4;
 }
 
 constexpr int kRecBlock = 1024, kRecItems = 8, kRecTile = kRecBlock * kRecItems;

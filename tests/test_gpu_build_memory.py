@@ -172,3 +172,19 @@ def test_depth_rule_in_less_memory(F, n, m, L, cluster):
                 assert a.tobytes() == b.tobytes(), (kind, l)
     got.free()
     want.free()
+
+
+def test_one_set_of_four_passes_sorts_elements(F):
+    """Nothing is gained there by moving whole points: 16 bytes a point, not 32."""
+    import torch
+    n, L = 5000000, 9
+    b = Bounded(F)
+    st, t = b.build(F, parity.to_gpu(I.uniform_points(807, n)), None, L, 32)
+    torch.cuda.synchronize()
+    assert st == F.OK
+    records = sum(min(n, 8 ** l) for l in range(1, L))
+    assert records > n  # (a block of their own, 16 bytes each, in place of masks)
+    masks = sum(_r(min(n, 8 ** l)) for l in range(L))
+    scans = 256 + sum(16 * -(-min(n, 8 ** l) // 16384) for l in range(2, L + 1))
+    assert b.peak - b.live <= _least([n], L, n, False) - masks + _r(16 * records) + _r(scans)
+    t.free()
