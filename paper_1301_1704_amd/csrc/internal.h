@@ -187,9 +187,11 @@ void launch_publish(const Publish& pub, hipStream_t s);
 void launch_list_count(const ListLevelArgs& a, uint32_t* cnt2, uint32_t* cnt4, hipStream_t s);
 // Level 2 of a plain build (at most 8 parents and 64 boxes): counts and offsets.
 void launch_list_first(const ListLevelArgs& a, const ScanArgs& sc, hipStream_t s);
-// Levels of at most kScanSmall boxes: the fill that writes their counts scans
-// them too (the last of its blocks; `done` counts them, zeroed).
-constexpr uint32_t kScanSmall = 4096;
+// Levels of at most kScanSmall boxes, with at most kScanParents two levels above
+// (the parents of the level that the fill before them builds): the fill that
+// writes their counts scans them too (the last of its blocks; `done` counts them,
+// zeroed).
+constexpr uint32_t kScanSmall = 4096, kScanParents = 1024;
 void launch_list_fill(const ListLevelArgs& a, const uint32_t* off2,
                       const uint32_t* off4, uint32_t* ent2, uint32_t* ent4, hipStream_t s,
                       const ScanArgs& next = {}, uint32_t* done = nullptr);

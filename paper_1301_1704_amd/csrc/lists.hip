@@ -508,9 +508,13 @@ __global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(Li
 // A coarse level of a plain build, whose next level has at most kScanSmall
 // boxes: the block that finishes last (`done` counts them) also turns the next
 // level's counts into offsets. Level 2 of a 4097-point build: fill, gap and scan
-// took 5.7 + 3.8 + 4.6 us, this 8.2. Past kScanSmall one block's scan would be
-// longer than the launch that it saves. The counter releases each block's counts
-// and acquires the others' for the block that scans them.
+// took 5.7 + 3.8 + 4.6 us, this 8.2. Whole builds with it and without, us: 600
+// points at level 5 88 / 93, 3000 90 / 94, 4096 at level 4 74.6 / 77.5, 65536 at
+// level 5 112 / 114. kScanSmall is what one block's registers hold. The counter
+// releases each block's counts and acquires the others' for the block that scans
+// them, which a grid of many blocks pays for many times: with kScanParents of 512 /
+// 1024 / no limit, 600 points at level 8 took 144 / 138 / 142, 3000 150 / 146 / 167
+// and 4096 153 / 149 / 180.
 constexpr uint32_t kScanSmallItems = kScanSmall / 256;
 __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
                                                            const uint32_t* __restrict__ off2,

@@ -1103,6 +1103,11 @@ fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_
       lblock += round_up(count * 4, 256);
       return q;
     };
+    // whether level l's counts are scanned by the fill that writes them
+    auto filled_scan = [&](uint32_t l) {
+      return !dense && !by_level && l > 2 && lcap[rs][l] <= kScanSmall &&
+             lcap[rs][l - 2] <= kScanParents;
+    };
     hm->published = 0;  // (nothing enqueued writes it yet)
     for (uint32_t l = 2; l <= D; ++l)
       for (int k = 0; k < 2; ++k) impl->lists[l].off[k] = carve((size_t)lcap[rs][l] + 1);
@@ -1155,7 +1160,7 @@ fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_
       else if (by_level)
         P.run(K_COUNT, 0.0, [&] { launch_list_count(a, cnt, cnt + round_up(nr, 4), st); },
               kListSet, (int)l);
-      if (dense || (l > 2 && (nr > kScanSmall || by_level))) {
+      if (dense || (l > 2 && !filled_scan(l))) {
         uint64_t* st2 = la.take_words(scan_tiles(nr));
         uint64_t* st4 = la.take_words(scan_tiles(nr));
         uint32_t* tk = la.take_ticket();
@@ -1190,7 +1195,7 @@ fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_
         a.recv_node_cur = sets[rs].lv[l].node;
         a.cnt2_next = cnt;
         a.cnt4_next = cnt + round_up(lcap[rs][l + 1], 4);
-        if (lcap[rs][l + 1] <= kScanSmall) done = la.take_ticket();
+        if (filled_scan(l + 1)) done = la.take_ticket();
       }
       P.run(K_FILL, 0.0, [&] {
         launch_list_fill(a, LB.off[0], LB.off[1], LB.ent[0], LB.ent[1], st, next, done);
@@ -1217,7 +1222,7 @@ fmmds_status build_plan(const float* src_xyz, uint32_t n_src, const float* recv_
         if (next) {
           const double nn = nb[rs][l + 1];
           side += 8 * nr + 8 * nn;
-          if (lcap[rs][l + 1] <= kScanSmall) side += 16 * nn + 8;
+          if (filled_scan(l + 1)) side += 16 * nn + 8;
         }
         return side;
       }

@@ -10,7 +10,7 @@ from paper_1301_1704_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-SCAN_SMALL = 4096  # levels of at most so many boxes are scanned by the fill above
+SCAN_SMALL, SCAN_PARENTS = 4096, 1024  # such levels are scanned by the fill above
 
 
 @pytest.fixture(scope="module")
@@ -43,7 +43,7 @@ def _expected(t, n, m, L, kb):
         if l < L:
             b += 8 * rcv[l] + 8 * rcv[l + 1]  # the receivers' records, the next counts
             scan = 16 * rcv[l + 1] + 8
-            if cap[l + 1] <= SCAN_SMALL:
+            if cap[l + 1] <= SCAN_SMALL and cap[l - 1] <= SCAN_PARENTS:
                 b += scan
             else:
                 out["scan_counts"] += scan
@@ -55,7 +55,7 @@ def _expected(t, n, m, L, kb):
 
 
 @pytest.mark.parametrize("n,m,L,kb", [(30000, 0, 5, 32), (3000, 5000, 3, 64), (200000, 90000, 8, 64),
-                                      (20000, 0, 2, 32)])
+                                      (20000, 0, 2, 32), (1024, 0, 7, 32), (1025, 4000, 8, 64)])
 def test_list_bytes(F, n, m, L, kb):
     import torch
     s = parity.to_gpu(I.sphere_cluster_points(861, 862, n))
