@@ -18,8 +18,8 @@
 //   - short lists: 64 / W lanes per receiver, each walking a part of its box's
 //     runs; lanes of one box read the same points, and those of neighboring
 //     boxes mostly the same lines;
-//   - long lists, and boxes with more than half of the wave's receivers
-//     (clustered input puts hundreds of points in one box): the wave stages
+//   - long lists, and boxes that hold the whole wave of receivers (clustered
+//     input puts hundreds of points in one box): the wave stages
 //     the box's source points in LDS 64 at a time (one coalesced 16-byte load
 //     per lane) and every lane sums its receiver against the whole tile. With
 //     r < 64 receivers the tile is split over 64 / R lane groups (R = r rounded
@@ -89,15 +89,21 @@ __global__ __launch_bounds__(256) void k_pack_sources(
 // now (380 of it the packing, whose charges are a random read each, 350 the
 // random writes of phi; the walk itself is bound by the cache's one line a
 // cycle: each lane reads its own 16 bytes). 6.0M sources and 5.0M receivers,
-// sphere + clusters, level 9: 3250-3800 -> 790 us. (Blocks not renumbered so that
+// sphere + clusters, level 9: 3250-3800 -> 806-861 us. (Blocks not renumbered so that
 // an XCD takes consecutive receivers: the clustered sum takes a quarter longer.)
 // 29K sources and 15K receivers at level 3: 97 -> 48 us.
 constexpr uint32_t kNearRuns = 512;  // runs staged per wave
 constexpr uint32_t kNearChunks = 4;  // list entries staged at a time, in 64s
 // Lists of more source points go tile by tile: one lane walking such a list
-// alone would outlast its wave (limits of 256 / 512 / 1024 / 2048 points took
-// 1383 / 997 / 982 / 982 us on the clustered sum).
+// alone would outlast its wave (6.0M sources and 5.0M receivers, sphere + clusters,
+// level 9, limits of 512 / 1024 / 2048 points: 811 / 806 / 847 us).
 constexpr uint32_t kNearLongList = 1024;
+// So do boxes of the whole wave, whose lanes all want the same points (boxes of W
+// receivers, 36 sources a box, walked / by tiles: W = 64 487 / 324 us, 32 217 /
+// 149, 16 124 / 97, 8 77 / 71, 4 52 / 61, so waves of 4 walk). Two boxes in a wave
+// are walked at once, but tiled one after the other: with 33 of 64 receivers in
+// the first 555 walked, 762 with that one tiled, with 48 521 and 715.
+constexpr uint32_t kNearTileMin = 8;
 
 struct NearStage {
   float4 tile[64];
@@ -280,7 +286,7 @@ __global__ __launch_bounds__(256, 5) void k_near_field(
     const uint32_t f = 63u - (uint32_t)__clzll((long long)(heads & ((2ull << rec) - 1ull)));
     const uint64_t above = f >= 63u ? 0ull : heads >> (f + 1u);
     const uint32_t nr = above ? (uint32_t)__ffsll((long long)above) : n_here - f;
-    const bool tiled = now && n > 0 && (n > kNearLongList || 2u * nr > W);
+    const bool tiled = now && n > 0 && (n > kNearLongList || (W >= kNearTileMin && nr == W));
     uint64_t todo = __ballot(tiled && part == 0u && rec == f);
     while (todo) {
       const int h = __ffsll((long long)todo) - 1;
