@@ -191,7 +191,7 @@ void launch_list_first(const ListLevelArgs& a, const ScanArgs& sc, hipStream_t s
 // (the parents of the level that the fill before them builds): the fill that
 // writes their counts scans them too (the last of its blocks; `done` counts them,
 // zeroed).
-constexpr uint32_t kScanSmall = 4096, kScanParents = 1024;
+constexpr uint32_t kScanSmall = 4096, kScanParents = 800;
 void launch_list_fill(const ListLevelArgs& a, const uint32_t* off2,
                       const uint32_t* off4, uint32_t* ent2, uint32_t* ent4, hipStream_t s,
                       const ScanArgs& next = {}, uint32_t* done = nullptr);

@@ -512,9 +512,10 @@ __global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(Li
 // points at level 5 88 / 93, 3000 90 / 94, 4096 at level 4 74.6 / 77.5, 65536 at
 // level 5 112 / 114. kScanSmall is what one block's registers hold. The counter
 // releases each block's counts and acquires the others' for the block that scans
-// them, which a grid of many blocks pays for many times: with kScanParents of 512 /
-// 1024 / no limit, 600 points at level 8 took 144 / 138 / 142, 3000 150 / 146 / 167
-// and 4096 153 / 149 / 180.
+// them, which a grid of many blocks pays for many times. Trees whose levels have as
+// many boxes as points, scanned by the fills (without kScanParents) and apart: at
+// level 10 513 points 176 / 180, 700 180 / 184, 800 182 / 184, 900 185.5 / 184.5, 1000
+// 186.5 / 185; at level 8 3000 167 / 150, 4096 180 / 153.
 constexpr uint32_t kScanSmallItems = kScanSmall / 256;
 __global__ __launch_bounds__(256) void k_list_fill_scan(ListLevelArgs a,
                                                            const uint32_t* __restrict__ off2,

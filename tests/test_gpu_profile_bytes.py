@@ -10,7 +10,7 @@ from paper_1301_1704_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-SCAN_SMALL, SCAN_PARENTS = 4096, 1024  # such levels are scanned by the fill above
+SCAN_SMALL, SCAN_PARENTS = 4096, 800  # such levels are scanned by the fill above
 
 
 @pytest.fixture(scope="module")
@@ -55,7 +55,7 @@ def _expected(t, n, m, L, kb):
 
 
 @pytest.mark.parametrize("n,m,L,kb", [(30000, 0, 5, 32), (3000, 5000, 3, 64), (200000, 90000, 8, 64),
-                                      (20000, 0, 2, 32), (1024, 0, 7, 32), (1025, 4000, 8, 64)])
+                                      (20000, 0, 2, 32), (800, 0, 7, 32), (801, 4000, 8, 64)])
 def test_list_bytes(F, n, m, L, kb):
     import torch
     s = parity.to_gpu(I.sphere_cluster_points(861, 862, n))

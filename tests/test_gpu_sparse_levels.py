@@ -25,11 +25,11 @@ def F():
     return F
 
 
-@pytest.mark.parametrize("n,m,L", [(1023, 0, 7), (1024, 0, 7), (1025, 1024, 8), (700, 1025, 9),
+@pytest.mark.parametrize("n,m,L", [(799, 0, 7), (800, 0, 7), (801, 800, 8), (700, 801, 9),
                                    (4096, 0, 8), (4097, 0, 6), (3000, 4096, 21)])
 def test_sparse_levels_match_oracle(F, oracle_lib, n, m, L):
     """Many levels of as many boxes as points: scanned by the fill before them up to
-    1024 parents and 4096 boxes, apart past that."""
+    800 parents and 4096 boxes, apart past that."""
     import torch
     print(n, m, L, file=sys.__stderr__, flush=True)
     src = I.uniform_points(311, n)
