@@ -82,7 +82,8 @@ def test_charge_that_is_not_finite_spoils_other_pairs_only(F, n, m, value, no_al
 
 
 @pytest.mark.parametrize("no_alloc", [False, True])
-@pytest.mark.parametrize("scale", [4e-38, 1e-36, 1e-30, 1.0, 1e30, 3e35, 1e37])
+@pytest.mark.parametrize("scale", [4e-38, 1e-36, 1e-30, 2.0 ** -80.5, 2.0 ** -80, 1.0, 2.0 ** 59,
+                                   2.0 ** 59.75, 1e30, 3e35, 1e37])
 @pytest.mark.parametrize("n,m", SHAPES)
 def test_charges_of_any_size_keep_their_bits(F, n, m, scale, no_alloc):
     """Every term and sum is a normal number, so the bound is the plain one. (A
