@@ -53,7 +53,7 @@ __device__ __forceinline__ void add_term(float& acc, const float4 x, float yx, f
 // The same for charges that near_plain holds for: neither a term nor a sum leaves
 // FP32's normal range while it is kNearScale times too small, and zero times the
 // charge is zero, so the sum is scaled at its end and the reciprocal selected: 10
-// instructions (2^20 sources and receivers at level 2, bound by these: 89.1 -> 79.7
+// instructions (2^20 sources and receivers at level 2, bound by these: 88.8 -> 78.6
 // ms). A record whose charge is another one has a negative x.
 __device__ __forceinline__ void add_plain_term(float& acc, const float4 x, float yx, float yy,
                                                float yz) {
