@@ -495,12 +495,13 @@ __device__ __forceinline__ void fill_wave(const ListLevelArgs& a,
   }
 }
 
+// (As many waves per SIMD as the registers allow without scratch memory, which the
+// runtime takes from the device when a kernel first runs on a queue: on a full
+// device that ends the queue.)
 template <bool NEXT, bool BATCH, uint32_t PAIRS>
-__global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? 7 : 8) void k_list_fill(ListLevelArgs a,
-                                                      const uint32_t* __restrict__ off2,
-                                                      const uint32_t* __restrict__ off4,
-                                                      uint32_t* __restrict__ ent2,
-                                                      uint32_t* __restrict__ ent4) {
+__global__ __launch_bounds__(256, NEXT && PAIRS > 1 ? (BATCH ? 6 : 7) : 8) void k_list_fill(
+    ListLevelArgs a, const uint32_t* __restrict__ off2, const uint32_t* __restrict__ off4,
+    uint32_t* __restrict__ ent2, uint32_t* __restrict__ ent4) {
   __shared__ __align__(16) uint32_t s_all[4][kFillWords];
   fill_wave<NEXT, BATCH, PAIRS>(a, off2, off4, ent2, ent4, s_all);
 }
