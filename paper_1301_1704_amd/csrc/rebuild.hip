@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void k_inc_merge(
   constexpr int kItems = kPlaceTile / 256;
   uint64_t x[kItems];
   uint32_t sl[kItems];
-  P3 p[kItems];
+  float px[kItems], py[kItems], pz[kItems];  // (an array of points would be scratch memory)
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
     const uint64_t i = min<uint64_t>(t0 + (uint64_t)k * 256 + threadIdx.x, t1 - 1);
@@ -219,7 +219,8 @@ __global__ __launch_bounds__(256) void k_inc_merge(
   }
 #pragma unroll
   for (int k = 0; k < kItems; ++k) {
-    p[k] = xyz[sl[k]];
+    const P3 p = xyz[sl[k]];
+    px[k] = p.x, py[k] = p.y, pz[k] = p.z;
     s_st[k * 256 + threadIdx.x] = x[k];  // entries past t1 are never searched
   }
   __syncthreads();
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(256) void k_inc_merge(
       sk[pos] = key;
       sv[pos] = j;
     }
-    sorted_xyz[pos] = p[k];
+    sorted_xyz[pos] = P3{px[k], py[k], pz[k]};
   }
 }
 

@@ -36,11 +36,7 @@ def kernels(tmp_path_factory):
     return got
 
 
-# (a private array there since the merge was written)
-KNOWN = {"rebuild.hip": "k_inc_merge"}
-
-
 def test_no_kernel_needs_scratch(kernels):
     assert len(kernels) > 60
-    bad = {k: b for k, b in kernels.items() if b and KNOWN.get(k[0], "-") not in k[1]}
+    bad = {k: b for k, b in kernels.items() if b}
     assert not bad, bad
