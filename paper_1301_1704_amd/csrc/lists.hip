@@ -31,12 +31,12 @@ namespace fmmds {
 // bits, kept in place, subtract to 0, to the axis' lowest bit (+1) or to both
 // of its bits (-1).
 //
-// Counting (level 2 only; the fill of each level counts the next): one
-// half-wave (32 lanes) per receiver box p of level l - 1; lane j takes the
-// j-th entry s of E2(p) (at most 27) and counts, for each of the 8 receiver
-// octants q, the children of s adjacent to a receiver child in octant q; two
-// packed half-wave scans give the E2 count of every receiver child of p at
-// once (E4 = all children minus E2).
+// Counting (level 2, and every level of a build in the least memory; else the
+// fill of each level counts the next): one half-wave (32 lanes) per receiver box
+// p of level l - 1; lane j takes the j-th entry s of E2(p) (at most 27) and
+// counts, for each of the 8 receiver octants q, the children of s adjacent to a
+// receiver child in octant q; two packed half-wave scans give the E2 count of
+// every receiver child of p at once (E4 = all children minus E2).
 //
 // Filling: two receiver boxes p per wave, one per half-wave for the setup.
 // The children of all s in E2(p), in ascending rank, form one union list U
