@@ -1462,25 +1462,6 @@ void batch_enqueue(BatchImpl& B, const float* xyz, Prof& P) {
   });
   uint32_t max_cap = 1;
   for (uint32_t l = 0; l <= L; ++l) max_cap = std::max(max_cap, B.cap[l]);
-  {
-    RebaseArgs ra{};
-    for (uint32_t l = 0; l <= L; ++l) {
-      ra.n_l[l] = &meta->n_boxes[0][l];
-      ra.gkey[l] = (const uint64_t*)B.g[l].key;
-      ra.gbegin[l] = B.g[l].begin;
-      ra.gparent[l] = l >= 1 ? B.g[l].parent : nullptr;
-      ra.gchild[l] = l < L ? B.g[l].child : nullptr;
-      ra.fkey[l] = B.fkey[l];
-      ra.fbegin[l] = B.fbegin[l];
-      ra.fparent[l] = B.fparent[l];
-      ra.fchild[l] = B.fchild[l];
-    }
-    ra.first = B.first();
-    ra.set_off = B.d_off;
-    ra.n_sets = B.n_sets;
-    ra.L = L;
-    P.run(K_REBASE, 0.0, [&] { launch_batch_rebase(ra, max_cap, st); });
-  }
   for (uint32_t l = 2; l <= L; ++l) {
     ListLevelArgs a{};
     a.level = l;
@@ -1518,6 +1499,26 @@ void batch_enqueue(BatchImpl& B, const float* xyz, Prof& P) {
     P.run(K_FILL, 0.0, [&] {
       launch_list_fill(a, B.goff[l][0], B.goff[l][1], B.ent[l][0], B.ent[l][1], st);
     });
+  }
+  // the set-relative tables, over the list kernels' records
+  {
+    RebaseArgs ra{};
+    for (uint32_t l = 0; l <= L; ++l) {
+      ra.n_l[l] = &meta->n_boxes[0][l];
+      ra.gkey[l] = (const uint64_t*)B.g[l].key;
+      ra.gbegin[l] = B.g[l].begin;
+      ra.gparent[l] = l >= 1 ? B.g[l].parent : nullptr;
+      ra.gchild[l] = l < L ? B.g[l].child : nullptr;
+      ra.fkey[l] = B.fkey[l];
+      ra.fbegin[l] = B.fbegin[l];
+      ra.fparent[l] = B.fparent[l];
+      ra.fchild[l] = B.fchild[l];
+    }
+    ra.first = B.first();
+    ra.set_off = B.d_off;
+    ra.n_sets = B.n_sets;
+    ra.L = L;
+    P.run(K_REBASE, 0.0, [&] { launch_batch_rebase(ra, max_cap, st); });
   }
   {
     ListRebaseArgs la{};
@@ -1703,49 +1704,20 @@ void batch_layout(BatchImpl& B, Carve& M) {
     if (l < L) {
       G.child = M.get<uint32_t>(c + 1);
     }
+    // The set-relative tables (20 bytes a box and more), one after the other. They
+    // are written last of all: until then the list kernels' records (16 bytes a
+    // box) have their space.
     B.fkey[l] = M.get<uint64_t>(c);
     B.fbegin[l] = M.get<uint32_t>(c + n_sets);
     B.fparent[l] = l >= 1 ? M.get<uint32_t>(c) : nullptr;
     B.fchild[l] = l < L ? M.get<uint32_t>(c + n_sets) : nullptr;
+    B.node[l] = l >= 1 && l < L ? (uint4*)B.fkey[l] : nullptr;
     if (l >= 2) {
       for (int k = 0; k < 2; ++k) {
         B.goff[l][k] = M.get<uint32_t>(c + 1);
+        B.loff[l][k] = M.get<uint32_t>(c + n_sets);
         B.ent[l][k] = M.get<uint32_t>((size_t)(k == 0 ? 27 : 189) * B.rcap[l]);
       }
-    }
-  }
-  // every level's set-relative offsets, written last of all, in one block
-  size_t lo_n = 0;
-  for (uint32_t l = 2; l <= L; ++l) lo_n += 2 * round_up((size_t)B.cap[l] + n_sets, 64);
-  uint32_t* lo = M.get<uint32_t>(std::max<size_t>(lo_n, 1));
-  size_t lo_at = 0;
-  for (uint32_t l = 2; l <= L; ++l)
-    for (int k = 0; k < 2; ++k) {
-      B.loff[l][k] = lo ? lo + lo_at : nullptr;
-      lo_at += round_up((size_t)B.cap[l] + n_sets, 64);
-    }
-  // The list kernels' records (16 bytes a box) take no memory of their own where
-  // they fit elsewhere: in the space of the sorted elements, done with by then, of
-  // the set-relative offsets, or of the E4 entries of a level whose fill comes
-  // after the last read of them (level l's are read by the fills of levels l and
-  // l + 1).
-  size_t room[kMaxLevel + 2] = {}, used[kMaxLevel + 2] = {};
-  // (slot 0: the sorted elements; 1: the offsets; m: level m's E4 entries)
-  room[0] = P;
-  room[1] = lo_n / 4;
-  for (uint32_t m = 2; m <= L; ++m) room[m] = (size_t)189 * B.rcap[m] / 4;
-  for (uint32_t l = L - 1; l >= 1 && l < L; --l) {
-    uint32_t at = kMaxLevel + 1;  // (none)
-    for (uint32_t m = L; m >= l + 2 && at > L; --m)
-      if (used[m] + B.cap[l] <= room[m]) at = m;
-    if (at > L && used[1] + B.cap[l] <= room[1]) at = 1;
-    if (used[0] + B.cap[l] <= room[0]) at = 0;
-    if (at > L) {
-      B.node[l] = M.get<uint4>(B.cap[l]);
-    } else {
-      uint4* q = (uint4*)(at == 0 ? (void*)B.sb.k[0] : at == 1 ? (void*)lo : (void*)B.ent[at][1]);
-      B.node[l] = q ? q + used[at] : nullptr;
-      used[at] += B.cap[l];
     }
   }
   B.cnt = M.get<uint32_t>(2 * round_up(std::max<uint32_t>(cmax, 1), 4));
