@@ -335,7 +335,8 @@ fmmds_status fmmds_displace(const fmmds_displace_set* sets, uint32_t n_sets, flo
  * EXPORT if a receiver box of another rank has it in its E4 list, else
  * DOMESTIC; elsewhere it is IMPORT if a receiver box of `rank` has it in its
  * E4 list, else OTHER. Uses a temporary device buffer from the library's
- * cache: 4 bytes per receiver box of levels l_crit and below it.
+ * cache: 4 bytes per receiver box of levels l_crit and below it, or where that
+ * cannot be had of the fullest of those levels.
  */
 enum {
   FMMDS_BOX_DOMESTIC = 0,

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void k_partition(const KeyT* __restrict__ rkey
   }
 }
 
-// Box types, every level in two launches (grid y = level - 2).
+// Box types, every level in two launches (grid y: the levels from a first one on).
 //
 // k_types_init: per source box, the type it has if no list names it (DOMESTIC or
 // OTHER; at the critical level IMPORT, ROOT or DOMESTIC), and per receiver,
@@ -119,8 +119,8 @@ __device__ __forceinline__ void append_work(const BoxTypesLevel& v, uint32_t fir
 }
 
 template <typename KeyT>
-__global__ __launch_bounds__(256) void k_types_init(BoxTypes a) {
-  const uint32_t l = blockIdx.y + 2;
+__global__ __launch_bounds__(256) void k_types_init(BoxTypes a, uint32_t first) {
+  const uint32_t l = first + blockIdx.y;
   const BoxTypesLevel& v = a.lv[l];
   const uint32_t l_crit = a.l_par - 1;
   const uint64_t t0 = blockIdx.x * 256ull + threadIdx.x, step = gridDim.x * 256ull;
@@ -188,8 +188,8 @@ __global__ __launch_bounds__(256) void k_types_init(BoxTypes a) {
 // once, every load before any store (on this GPU a wait for a load also waits
 // for earlier stores).
 template <typename KeyT>
-__global__ __launch_bounds__(256) void k_types_mark(BoxTypes a) {
-  const uint32_t l = blockIdx.y + a.l_par - 1;
+__global__ __launch_bounds__(256) void k_types_mark(BoxTypes a, uint32_t first) {
+  const uint32_t l = first + blockIdx.y;
   const BoxTypesLevel& v = a.lv[l];
   const bool deep = l >= a.l_par;
   const uint32_t sh = deep ? l - a.l_par : 0;
@@ -237,19 +237,20 @@ void launch_partition(bool key64, const void* rkey, const uint32_t* rbegin, uint
                        rbegin, n_boxes, n_points, n_ranks, n_idx, owner);
 }
 
-void launch_box_types(bool key64, const BoxTypes& a, uint32_t depth, hipStream_t s) {
+void launch_box_types(bool key64, const BoxTypes& a, uint32_t first, uint32_t last,
+                      hipStream_t s) {
   uint64_t most = 1;
-  for (uint32_t l = 2; l <= depth; ++l)
+  for (uint32_t l = first; l <= last; ++l)
     most = std::max<uint64_t>(most, std::max(a.lv[l].n_src, a.lv[l].n_recv));
-  const dim3 init((uint32_t)std::min<uint64_t>((most + 255) / 256, 8192), depth - 1);
-  const dim3 mark((uint32_t)std::min<uint64_t>((most + 3) / 4, kMarkBlocks), depth - a.l_par + 2);
-  if (key64) {
-    hipLaunchKernelGGL(k_types_init<uint64_t>, init, dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_types_mark<uint64_t>, mark, dim3(256), 0, s, a);
-  } else {
-    hipLaunchKernelGGL(k_types_init<uint32_t>, init, dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_types_mark<uint32_t>, mark, dim3(256), 0, s, a);
-  }
+  const uint32_t listed = std::max(first, a.l_par - 1);  // no lists are read above
+  const dim3 init((uint32_t)std::min<uint64_t>((most + 255) / 256, 8192), last - first + 1);
+  const dim3 mark((uint32_t)std::min<uint64_t>((most + 3) / 4, kMarkBlocks),
+                  last >= listed ? last - listed + 1 : 0);
+  if (key64) hipLaunchKernelGGL(k_types_init<uint64_t>, init, dim3(256), 0, s, a, first);
+  else hipLaunchKernelGGL(k_types_init<uint32_t>, init, dim3(256), 0, s, a, first);
+  if (mark.y == 0) return;
+  if (key64) hipLaunchKernelGGL(k_types_mark<uint64_t>, mark, dim3(256), 0, s, a, listed);
+  else hipLaunchKernelGGL(k_types_mark<uint32_t>, mark, dim3(256), 0, s, a, listed);
 }
 
 }  // namespace fmmds

@@ -317,7 +317,9 @@ struct BoxTypes {
 void launch_partition(bool key64, const void* rkey, const uint32_t* rbegin, uint32_t n_boxes,
                       uint32_t n_points, uint32_t n_ranks, uint32_t l_par, uint32_t* owner,
                       hipStream_t s);
-void launch_box_types(bool key64, const BoxTypes& a, uint32_t depth, hipStream_t s);
+// Levels first .. last.
+void launch_box_types(bool key64, const BoxTypes& a, uint32_t first, uint32_t last,
+                      hipStream_t s);
 
 // ---- nearfield.hip
 uint64_t near_field_table(uint32_t n_recv);  // entries of wave_box

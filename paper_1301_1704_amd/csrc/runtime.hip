@@ -1982,11 +1982,17 @@ fmmds_status box_types(const fmmds_tree* t, uint32_t l_par, const uint32_t* owne
   if (!par_level_ok(t, l_par)) return FMMDS_ERR_LEVEL;
   const TreeImpl* impl = (const TreeImpl*)t->impl;
   const uint32_t l_crit = l_par - 1;
-  // one counter per level, then the levels' work lists
+  // One counter per level, then the levels' work lists: of every level, or where
+  // memory is short of one level at a time.
   const size_t clear_b = 32 * 4;
-  size_t work = 0;
-  for (uint32_t l = l_crit; l <= t->depth; ++l) work += t->recv[l].n;
-  uint32_t* block = (uint32_t*)cache_alloc(clear_b + std::max<size_t>(work, 1) * 4, st);
+  size_t work = 1, most = 1;
+  for (uint32_t l = l_crit; l <= t->depth; ++l) {
+    work += t->recv[l].n;
+    most = std::max<size_t>(most, t->recv[l].n);
+  }
+  uint32_t* block = (uint32_t*)cache_alloc(clear_b + work * 4, st);
+  const bool all = block != nullptr;
+  if (!all) block = (uint32_t*)cache_alloc(clear_b + most * 4, st);
   if (!block) return FMMDS_ERR_NOMEM;
   launch_zero(block, clear_b, st);
   BoxTypes a{};
@@ -2010,9 +2016,11 @@ fmmds_status box_types(const fmmds_tree* t, uint32_t l_par, const uint32_t* owne
     if (l < l_crit) continue;
     v.n_work = block + l;
     v.work = next;
-    next += v.n_recv;
+    if (all) next += v.n_recv;
   }
-  launch_box_types(t->key_bits == 64, a, t->depth, st);
+  const bool key64 = t->key_bits == 64;
+  if (all) launch_box_types(key64, a, 2, t->depth, st);
+  for (uint32_t l = 2; !all && l <= t->depth; ++l) launch_box_types(key64, a, l, l, st);
   cache_release(block, st);
   return hipGetLastError() == hipSuccess ? FMMDS_OK : FMMDS_ERR_DEVICE;
 }
