@@ -164,6 +164,11 @@ fmmds_status fmmds_build_dense(const float* src_xyz, uint32_t n_src, const float
  * previous tree: only points whose finest-level box changed are sorted, and
  * merged with the others, which are still in order. The result is exactly
  * the tree fmmds_build would return for the same positions and options.
+ * It pays where the sort key is wide or few points change box: one set of 2^24
+ * points at level 10 takes 10.0 ms against 12.1 ms for a fresh build with 1e-4 of
+ * noise per coordinate; at level 8 the two are about equal (3.75 and 3.78 ms for
+ * two such sets), and a fresh build is faster for small sets and where many points
+ * move.
  *   prev:     host; a tree from fmmds_build, fmmds_rebuild or a batch, with
  *             the point counts of this call; read only, and may be freed
  *             once this call returns.
